@@ -195,6 +195,13 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     delete p;
     return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: " + m);
   }
+  if (p->sym.tree) {
+    m = rkkt::build_tree(p->sym, p->tree);
+    if (!m.empty()) {
+      delete p;
+      return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: " + m);
+    }
+  }
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) {
     int rc = hip_fail(nullptr, e, "rkkt_create: hipSetDevice");
@@ -248,6 +255,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
   d.spw = s.spw;
   d.upd_lds = s.upd_lds ? 1 : 0;
   d.variant = s.variant;
+  d.tree = s.tree ? 1 : 0;
   d.nu_pad = s.nu_pad;
   d.nchunk = s.nchunk;
   // per-unit line and cost data
@@ -353,10 +361,30 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = upload_sched(p, s.fac, false, &d.fa_ptr, &d.fa_ent)) != hipSuccess) goto hip_error;
   }
   {
+    if (s.tree) {
+      const rkkt::Tree& t = p->tree;
+      rkkt::TreeDP& r = d.tr;
+      r.host = &t;
+#define UP(field, vec) \
+  if ((e = upload(p, &r.field, vec)) != hipSuccess) goto hip_error;
+      UP(nodes, t.nodes) UP(children, t.children) UP(rows, t.rows) UP(orig, t.orig) UP(optr, t.optr)
+      UP(oent, t.oent) UP(lev_ptr, t.lev_ptr) UP(lev_nodes, t.lev_nodes) UP(job_ptr, t.job_ptr)
+      UP(jobs, t.jobs) UP(uord, t.uord) UP(kuu, t.kuu) UP(pair_g, t.pair_g) UP(pair_ptr, t.pair_ptr)
+      UP(pair_nodes, t.pair_nodes) UP(gstrip, t.gstrip) UP(rmap, t.rmap) UP(smap, t.smap)
+#undef UP
+      r.npool = t.npool; r.nstrip = t.nstrip; r.T = t.T; r.ngroup = t.ngroup; r.parts = t.parts;
+      r.npair = (int)t.pair_g.size() / 2;
+      r.nkuu = (int)t.kuu.size() / 3;
+      r.stride = t.stride;
+      const size_t ld = (size_t)t.ngroup * t.T * rkkt::kTreeB;
+      if ((e = dalloc(p, &r.slab, (size_t)s.N * t.stride)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.pool, (size_t)s.N * t.npool * rkkt::kTreeBlk)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.part, t.parts * ld * ld)) != hipSuccess) goto hip_error;
+    }
     const size_t N = s.N;
     const int ntile = (s.nu + s.col_tile - 1) / s.col_tile;
     size_t panel = d.lds_stp ? 1 : 2 * N * (size_t)s.nx;
-    if (!d.lds_red && d.variant == 1) panel = std::max(panel, N * ntile * 2 * (size_t)s.nx * s.col_tile);
+    if (!d.lds_red && d.variant == 1 && !d.tree) panel = std::max(panel, N * ntile * 2 * (size_t)s.nx * s.col_tile);
     // stacked panels: N n_z rows, then a slab of zero rows that the stacked
     // product's last chunk reads past the last row
     const size_t stacked = d.variant == 2 ? (N * (size_t)s.nz + rkkt::kSpSlab) * s.nu_pad : 1;
@@ -369,7 +397,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = dalloc(p, &d.W, N * s.k_col.size())) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.K, N * s.k_col.size())) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.LU, N * (size_t)d.lu_stride)) != hipSuccess) goto hip_error;
-    if ((e = dalloc(p, &d.part, d.variant == 1 ? N * s.nu * (size_t)s.nu : 1)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.part, d.variant == 1 && !d.tree ? N * s.nu * (size_t)s.nu : 1)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.panel, panel)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.Zst, stacked)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.KZst, stacked)) != hipSuccess) goto hip_error;
@@ -480,7 +508,7 @@ int rkkt_condense(rkkt_problem* p, const double* sigma_x, const double* sigma_u,
         [&] { rkkt::launch_condense_values(p->d, sigma_x, sigma_s, delta_w, stream); });
   stage(p, RKKT_STAGE_REFACTOR, stream, [&] { rkkt::launch_refactor(p->d, stream); });
   stage(p, RKKT_STAGE_REDUCE, stream, [&] { rkkt::launch_reduce(p->d, stream); });
-  if (p->d.variant == 2)
+  if (p->d.variant == 2 || p->d.tree)
     stage(p, RKKT_STAGE_STACKED_PRODUCT, stream, [&] { rkkt::launch_stacked_product(p->d, stream); });
   stage(p, RKKT_STAGE_SCENARIO_SUM, stream,
         [&] { rkkt::launch_scenario_sum(p->d, sigma_u, delta_w, khat, stream); });
@@ -582,7 +610,7 @@ static int iterate_impl(rkkt_problem* p, const rkkt_iteration* it, hipStream_t s
   // first child of the reduction is the stacked product
   e = fork ? hipEventRecord(p->fork_ev[1], stream) : hipSuccess;
   if (e != hipSuccess) return hip_fail(p, e, "rkkt_iterate: fork");
-  if (d.variant == 2)
+  if (d.variant == 2 || d.tree)
     stage(p, RKKT_STAGE_STACKED_PRODUCT, stream, [&] { rkkt::launch_stacked_product(d, stream); });
   e = fork ? hipStreamWaitEvent(side, p->fork_ev[1], 0) : hipSuccess;
   if (e != hipSuccess) return hip_fail(p, e, "rkkt_iterate: fork");
@@ -710,6 +738,7 @@ static hipError_t multi_dispatch(const rkkt_multi* m, const rkkt_multi::Group& g
   const rkkt::MultiBlk* blk = m->blk + g.off;
   hipError_t e = rkkt::multi_eval(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) e = rkkt::multi_lu(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
+  if (!handled) e = rkkt::multi_tree(g.l, g.nblk, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) e = rkkt::multi_dense(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) return hipErrorInvalidValue;
   return e;
@@ -762,6 +791,7 @@ int rkkt_multi_create(rkkt_problem* const* problems, const rkkt_iteration* its, 
     const rkkt::DP& d = problems[i]->d;
     rkkt::launches_eval(d, ls);
     rkkt::launches_lu(d, ls);
+    if (d.tree) rkkt::launches_tree(d, ls);
     rkkt::launches_dense(d, ls);
     for (const auto& l : ls) items.push_back({l, i});
   }

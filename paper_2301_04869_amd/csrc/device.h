@@ -9,8 +9,25 @@
 
 #include "layout.h"
 #include "rkkt.h"
+#include "tree.h"
 
 namespace rkkt {
+
+// Device view of the elimination tree (tree.h); host: the tree itself, for
+// the launchers.
+struct TreeDP {
+  const Tree* host;
+  const TreeNode* nodes;
+  const TreeChild* children;
+  const int *rows, *orig, *optr, *oent, *lev_ptr, *lev_nodes, *job_ptr, *jobs, *uord, *kuu;
+  const int *pair_g, *pair_ptr, *pair_nodes, *gstrip;
+  const short *rmap, *smap;
+  int npool, nstrip, T, ngroup, parts, npair, nkuu;
+  long long stride;
+  double *slab;  // [N][stride] fronts
+  double *pool;  // [N][npool][256] blocks of original entries
+  double *part;  // [parts][16 T ngroup]^2 product parts, lower triangle, tree order of u
+};
 
 struct DP {
   int nb, nl, ng, nload, ref, gref, nx, nu, m, nz, N;
@@ -85,6 +102,8 @@ struct DP {
   double *rpart;   // [N][nu]
   double *qbuf;    // [N][nx] internal order: G_x^-1 r3 of the last step right-hand side
   int *status;     // [2]: code, scenario
+  int tree;        // the reduction runs on the elimination tree (k_tree.hip)
+  TreeDP tr;
 };
 
 // Copy of n 8-byte units (doubles, or pairs of 32-bit words) from global
@@ -195,6 +214,10 @@ void launch_step_rhs(const DP& d, const double* r1x, const double* r2, const dou
 void launch_step_recover(const DP& d, const double* r2, const double* r3, const double* r4,
                          const double* ss, const double* pu, double* px, double* ps,
                          double* py, double* pz, hipStream_t s);
+// (k_tree.hip) fronts up the tree; product over the control columns; K_hat
+void launch_tree_reduce(const DP& d, hipStream_t s);
+void launch_tree_product(const DP& d, hipStream_t s);
+void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s);
 // (k_dense.hip)
 void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s);
 void launch_stacked_product(const DP& d, hipStream_t s);
@@ -222,7 +245,8 @@ enum : int {
   kKLineEvalGather = 1, kKLineEval, kKGatherEv, kKAssemble, kKLineHess, kKWGather, kKCondense,
   kKRefactor, kKReduce64, kKReduce, kKStepRhs2, kKStepRhs, kKStepRec2, kKStepRec,
   kKStacked, kKSymSum, kKCholSmall, kKCopyChol, kKSetInfo, kKCholDiag, kKCholTrsm, kKCholUpdate,
-  kKRSolveBlk, kKRSolve, kKCondenseLds
+  kKRSolveBlk, kKRSolve, kKCondenseLds,
+  kKTreeOrig, kKTreeFront, kKTreeCols, kKTreeProduct, kKTreeSum, kKTreeKuu
 };
 enum : int {
   kStEvalValues = 0, kStEvalRest, kStCondense, kStRefactor, kStReduce, kStStepRhs, kStStacked,
@@ -232,6 +256,7 @@ enum : int {
 void launches_eval(const DP& d, std::vector<Launch>& out);        // values, rest, condensed values
 void launches_lu(const DP& d, std::vector<Launch>& out);          // refactor, reduce, step kernels
 void launches_dense(const DP& d, std::vector<Launch>& out);       // product, sum, Cholesky, solve
+void launches_tree(const DP& d, std::vector<Launch>& out);        // the reduction on the tree, to K_hat
 // One multi-instance launch of l's kernel over nblk blocks (or, with
 // prepare, only the dynamic-LDS limit of that kernel); *handled is false when
 // the kernel is not in this file.
@@ -239,6 +264,8 @@ hipError_t multi_eval(const Launch& l, unsigned nblk, long long lds, const DP* d
                       const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
 hipError_t multi_lu(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
                     const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
+hipError_t multi_tree(const Launch& l, unsigned nblk, const DP* dps, const rkkt_iteration* its, const MultiBlk* blk,
+                      hipStream_t s, bool prepare, bool* handled);
 hipError_t multi_dense(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
                        const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
 

@@ -9,9 +9,11 @@
 #include "ipm.h"
 #include "rkkt.h"
 #include "symbolic.h"
+#include "tree.h"
 
 struct rkkt_problem {
   rkkt::Sym sym;
+  rkkt::Tree tree;  // empty unless sym.tree
   rkkt::DP d{};
   int device = 0;
   std::vector<void*> allocs;

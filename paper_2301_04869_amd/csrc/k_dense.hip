@@ -1104,6 +1104,7 @@ void launch_copy(const double* a, double* b, long long n, hipStream_t s) {
 }
 
 void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s) {
+  if (d.tree) return launch_tree_sum(d, su, dw, khat, s);
   const long long ntri = (long long)d.nu * (d.nu + 1) / 2;
   const double* src = d.variant == 2 ? d.gpart : d.part;
   const int cnt = d.variant == 2 ? d.nchunk : d.N;
@@ -1118,6 +1119,7 @@ void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat,
 }
 
 void launch_stacked_product(const DP& d, hipStream_t s) {
+  if (d.tree) return launch_tree_product(d, s);
   const int T = sp_nsuper(d.nu), nblk = sp_nblk(d.nu);
   const long long per = sp_rows_per_chunk((long long)d.N * d.nz, d.nchunk);
   // blocks per wavefront: the largest super-tile's count over 4 wavefronts
@@ -1237,7 +1239,8 @@ void launches_dense(const DP& d, std::vector<Launch>& out) {
                          0, 0});
   }
   const long long ntri = (long long)n * (n + 1) / 2;
-  out.push_back(Launch{kStSum * 4096, kKSymSum, 0, (int)((ntri + kSumEntries - 1) / kSumEntries), 1,
+  if (!d.tree)
+    out.push_back(Launch{kStSum * 4096, kKSymSum, 0, (int)((ntri + kSumEntries - 1) / kSumEntries), 1,
                        kSumEntries * kSumWaves, 0, 0});
   const int F = kStFactor * 4096;
   if (n <= kSmallN) {

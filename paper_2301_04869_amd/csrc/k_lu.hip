@@ -1972,6 +1972,7 @@ void launch_refactor(const DP& d, hipStream_t s) {
 }
 
 void launch_reduce(const DP& d, hipStream_t s) {
+  if (d.tree) return launch_tree_reduce(d, s);
   dim3 grid(ntiles(d), d.N);
   // LDS mode: the staged data; global mode: only the chain block's values
   const size_t lds = d.lds_red ? reduce_lds_bytes(sizes_of(d)) : 8 * (size_t)d.chain_t * d.chain_t;
@@ -2037,7 +2038,8 @@ void launches_lu(const DP& d, std::vector<Launch>& out) {
     else
       out.push_back(Launch{kStRefactor * 4096, kKRefactor, 2, d.N, 1, kRT, 0, 0});
     const long long lds = d.lds_red ? reduce_lds_bytes(z) : 8LL * d.chain_t * d.chain_t;
-    out.push_back(Launch{kStReduce * 4096, d.col_tile == kW64 ? kKReduce64 : kKReduce,
+    if (!d.tree)
+      out.push_back(Launch{kStReduce * 4096, d.col_tile == kW64 ? kKReduce64 : kKReduce,
                          2 * (d.lds_red ? 1 : 0) + (d.variant == 2 ? 1 : 0), ntiles(d), d.N, kRT, 0, lds});
     if (step2(d)) {
       out.push_back(Launch{kStStepRhs * 4096, kKStepRhs2, 0, d.N, 1, kGT, 0, step2_lds_bytes(z, kGT)});

@@ -838,6 +838,12 @@ std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* o
   s.lds_reduce = form_req != 2 && fits(s.col_tile, s.variant);
   s.sweep_form = form_req != 0 ? form_req : s.lds_reduce ? 1 : 2;
   s.lds_resident = s.lds_reduce && s.lds_group && s.lds_step;
+  // the adjoint closure off chip, unless another shape than its own (64-column
+  // panels, pull form) is asked for, runs on the elimination tree.  Whole
+  // passes, panels in device memory against the tree: 9241 buses x 16
+  // scenarios 114.6 / 28.3 ms, 2869 x 8 11.1 / 5.9, 1354 x 8 3.70 / 2.47; at
+  // 300 x 16 (0.85 / 0.85), where the panels begin to leave the chip, equal
+  s.tree = s.variant == 1 && !s.lds_reduce && s.col_tile == std::min(64, nu) && s.sweep_form == 2;
   // stacked panels of the product variant: rows (x rows then u rows) of every
   // scenario, columns padded to a multiple of 64 (the reduction's widest tile)
   s.nu_pad = (nu + 63) / 64 * 64;

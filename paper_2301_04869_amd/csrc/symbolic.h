@@ -114,6 +114,7 @@ struct Sym {
   int spw = 1;               // scenarios per workgroup in those kernels (LDS mode)
   bool upd_lds = true;       // LDS refactorisation stages its update targets
   int variant = 1;           // reduction: 1 adjoint solves, 2 stacked product
+  bool tree = false;         // variant 1 on the elimination tree of dense fronts (tree.h)
   int nu_pad = 0;            // row pitch of the stacked panels (multiple of 32)
   int nchunk = 1;            // contraction chunks of the stacked product
 };

@@ -1,0 +1,85 @@
+// Elimination tree of dense fronts for the reduction on grids whose panels do
+// not fit on chip (kernels in k_tree.hip).
+//
+// The filled LU pattern of G_x (internal order) is cut into nodes of at most
+// kTreeRows pivot rows each, joined where the elimination tree allows it and
+// little fill is added.  Every node is a dense front over its pivot rows J,
+// its interface rows I (rows of ancestors that its subtree touches) and its
+// control columns U (columns of u that its subtree touches).  Control columns
+// are renumbered in the order in which a post-order walk meets them and kept
+// in strips of 16, so a subtree's columns are a few whole strips and parent
+// and child agree on what a strip holds.
+#pragma once
+
+#include <string>
+#include <vector>
+
+#include "layout.h"
+
+namespace rkkt {
+
+struct Sym;
+
+constexpr int kTreeB = 16;                     // block side (one FP64 matrix instruction)
+constexpr int kTreeNB = 4;                     // pivot block rows of a node, at most
+constexpr int kTreeRows = kTreeB * kTreeNB;    // pivot rows of a node, at most
+constexpr int kTreeBlk = kTreeB * kTreeB;      // doubles of a block
+
+// One node.  Blocks are 16 x 16, row-major and contiguous; nb pivot block
+// rows, ib interface strips, us control strips, cs = ib + us strips in all.
+// Offsets are doubles within a scenario's slab:
+//   lu   [nb][nb]  block LU of G_JJ, every block transposed: (r, c) with
+//                  r > c holds L_rc^T (unit block lower), r < c holds U_rc^T
+//                  and r == c the transposed inverse of the pivot block
+//   kjj  [nb][nb]  K_JJ
+//   gijt [ib][nb]  G_IJ^T (row: pivot row, column: interface row)
+//   v, y [cs][nb]  V = G_JJ^-1 G_JC and Y = K_JC - K_JJ V / 2
+//   gu, ku [cs][ib]  updated G_IC and K_IC, read by the parent
+struct TreeNode {
+  int s, i, nb, ib, us, cs;
+  int level, parent;
+  int row0;        // rows[row0 ..]: internal row of every pivot row, then of every interface row
+  int child0, nchild;
+  int strip0;      // strips[strip0 .. + us]: global strip of every control strip
+  int oblk;        // orig table: lu nb nb, kjj nb nb, gijt ib nb, v cs nb, y cs nb
+  long long lu, kjj, gijt, v, y, gu, ku;
+};
+
+// A child as its parent sees it: rmap[rmap0 + r] is the child's interface
+// index of the parent's padded row r (pivot block rows, then interface block
+// rows) or -1; smap[smap0 + t] the child's control strip of the parent's
+// control strip t or -1.
+struct TreeChild {
+  int node, rmap0, smap0;
+};
+
+struct Tree {
+  std::vector<TreeNode> nodes;      // post-order
+  std::vector<TreeChild> children;
+  std::vector<int> rows, strips;
+  std::vector<short> rmap, smap;
+  long long stride = 0;             // doubles of a scenario's slab
+  // original entries (G_x, G_u, K) as blocks: orig[t] is the pool block of a
+  // node's block or -1; entries of pool block b are oent[2 optr[b] ..): the
+  // place in the block and the source, >= 0 in EV, ~source in K
+  std::vector<int> orig, optr, oent;
+  int npool = 0;
+  // nodes of every level; strip jobs of every level (node, first strip), four
+  // strips each, interface strips first
+  std::vector<int> lev_ptr, lev_nodes, job_ptr, jobs;
+  // control columns: uord[p] = u of place p, upos the inverse; nstrip strips
+  std::vector<int> uord, upos;
+  int nstrip = 0;
+  // K_uu entries of the lower triangle (user order): (row u, column u, K index)
+  std::vector<int> kuu;
+  // product over the control columns: groups of T strips; pair q = (ga, gb),
+  // gb <= ga, with the nodes pair_nodes[pair_ptr[q] ..) that touch both;
+  // gstrip[node * ngroup + g] = first strip index | mask << 16 (mask 0: none)
+  int T = 0, ngroup = 0, parts = 1;
+  std::vector<int> pair_g, pair_ptr, pair_nodes, gstrip;
+};
+
+// Builds the tree from the filled pattern; empty string on success.
+std::string build_tree(const Sym& s, Tree& t);
+
+}  // namespace rkkt
