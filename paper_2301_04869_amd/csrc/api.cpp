@@ -190,7 +190,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
   if (net->n_load > 0 && (!pd || !qd)) return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: null loads");
   rkkt_problem* p = new rkkt_problem();
   p->device = opt ? opt->device : 0;
-  std::string m = rkkt::build_symbolic(*net, n_scen, opt, p->sym);
+  std::string m = rkkt::build_symbolic(*net, n_scen, opt, p->sym, true);
   if (!m.empty()) {
     delete p;
     return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: " + m);
@@ -312,7 +312,9 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
 #undef UP
   // schedules: LDS images (packed entries and every index array the kernel
   // stages, in its LDS order) for the LDS kernels, int4 entries otherwise
-  if (s.lds_reduce && s.col_tile != 64) {
+  if (s.tree) {
+    // no kernel follows them
+  } else if (s.lds_reduce && s.col_tile != 64) {
     std::vector<unsigned> b;
     pack_entries(s.red_up, b);
     pack_entries(s.red_dn, b);
@@ -326,7 +328,9 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = upload_sched(p, s.red_up, false, &d.ru_ptr, &d.ru_ent)) != hipSuccess) goto hip_error;
     if ((e = upload_sched(p, s.red_dn, false, &d.rd_ptr, &d.rd_ent)) != hipSuccess) goto hip_error;
   }
-  if (s.lds_step) {
+  if (s.tree) {
+    // the step sweeps the tree
+  } else if (s.lds_step) {
     std::vector<unsigned> b;
     pack_entries(s.stp_up, b);
     pack_entries(s.stp_dn, b);
@@ -348,7 +352,9 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = upload_sched(p, s.stp_up, false, &d.su_ptr, &d.su_ent)) != hipSuccess) goto hip_error;
     if ((e = upload_sched(p, s.stp_dn, false, &d.sd_ptr, &d.sd_ent)) != hipSuccess) goto hip_error;
   }
-  if (s.lds_group) {
+  if (s.tree) {
+    // the fronts factorise G_x
+  } else if (s.lds_group) {
     std::vector<unsigned> f;
     pack_entries(s.fac, f);
     for (const std::vector<int>* v : {&s.fac.ptr, &s.lvu_ptr, &s.lvu_rows, &s.f_diag, &s.f_ptr})
@@ -367,23 +373,31 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
       r.host = &t;
 #define UP(field, vec) \
   if ((e = upload(p, &r.field, vec)) != hipSuccess) goto hip_error;
-      UP(nodes, t.nodes) UP(children, t.children) UP(rows, t.rows) UP(orig, t.orig) UP(optr, t.optr)
+      UP(nodes, t.nodes) UP(children, t.children) UP(rows, t.rows) UP(strips, t.strips) UP(orig, t.orig) UP(optr, t.optr)
       UP(oent, t.oent) UP(lev_ptr, t.lev_ptr) UP(lev_nodes, t.lev_nodes) UP(job_ptr, t.job_ptr)
       UP(jobs, t.jobs) UP(uord, t.uord) UP(kuu, t.kuu) UP(pair_g, t.pair_g) UP(pair_ptr, t.pair_ptr)
       UP(pair_nodes, t.pair_nodes) UP(gstrip, t.gstrip) UP(rmap, t.rmap) UP(smap, t.smap)
+      UP(cjobs, t.cjobs) UP(sn_ptr, t.sn_ptr) UP(sn, t.sn)
 #undef UP
       r.npool = t.npool; r.nstrip = t.nstrip; r.T = t.T; r.ngroup = t.ngroup; r.parts = t.parts;
       r.npair = (int)t.pair_g.size() / 2;
       r.nkuu = (int)t.kuu.size() / 3;
       r.stride = t.stride;
+      r.vstride = t.vstride;
+      r.ncjob = (int)t.cjobs.size() / 2;
+      r.nlev = (int)t.lev_ptr.size() - 1;
       const size_t ld = (size_t)t.ngroup * t.T * rkkt::kTreeB;
       if ((e = dalloc(p, &r.slab, (size_t)s.N * t.stride)) != hipSuccess) goto hip_error;
       if ((e = dalloc(p, &r.pool, (size_t)s.N * t.npool * rkkt::kTreeBlk)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.vec, (size_t)s.N * t.vstride)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.x, (size_t)s.N * s.nx)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.y, (size_t)s.N * s.nx)) != hipSuccess) goto hip_error;
+      if ((e = dalloc(p, &r.upart, (size_t)s.N * r.ncjob * 2 * rkkt::kTreeRows)) != hipSuccess) goto hip_error;
       if ((e = dalloc(p, &r.part, t.parts * ld * ld)) != hipSuccess) goto hip_error;
     }
     const size_t N = s.N;
     const int ntile = (s.nu + s.col_tile - 1) / s.col_tile;
-    size_t panel = d.lds_stp ? 1 : 2 * N * (size_t)s.nx;
+    size_t panel = d.lds_stp || d.tree ? 1 : 2 * N * (size_t)s.nx;
     if (!d.lds_red && d.variant == 1 && !d.tree) panel = std::max(panel, N * ntile * 2 * (size_t)s.nx * s.col_tile);
     // stacked panels: N n_z rows, then a slab of zero rows that the stacked
     // product's last chunk reads past the last row
@@ -396,7 +410,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = dalloc(p, &d.EV, N * s.n_ev)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.W, N * s.k_col.size())) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.K, N * s.k_col.size())) != hipSuccess) goto hip_error;
-    if ((e = dalloc(p, &d.LU, N * (size_t)d.lu_stride)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.LU, d.tree ? 1 : N * (size_t)d.lu_stride)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.part, d.variant == 1 && !d.tree ? N * s.nu * (size_t)s.nu : 1)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.panel, panel)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.Zst, stacked)) != hipSuccess) goto hip_error;
@@ -412,7 +426,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
       if ((e = hipDeviceSynchronize()) != hipSuccess) goto hip_error;
     }
     if ((e = dalloc(p, &d.rhat1, N * s.nx)) != hipSuccess) goto hip_error;
-    if ((e = dalloc(p, &d.wbuf, d.lds_stp ? 1 : N * (size_t)s.m)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.wbuf, d.lds_stp || d.tree ? 1 : N * (size_t)s.m)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.rpart, N * s.nu)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.qbuf, N * s.nx)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.status, 2)) != hipSuccess) goto hip_error;

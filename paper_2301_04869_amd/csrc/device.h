@@ -19,13 +19,18 @@ struct TreeDP {
   const Tree* host;
   const TreeNode* nodes;
   const TreeChild* children;
-  const int *rows, *orig, *optr, *oent, *lev_ptr, *lev_nodes, *job_ptr, *jobs, *uord, *kuu;
+  const int *rows, *strips, *orig, *optr, *oent, *lev_ptr, *lev_nodes, *job_ptr, *jobs, *uord, *kuu;
   const int *pair_g, *pair_ptr, *pair_nodes, *gstrip;
+  const int *cjobs, *sn_ptr, *sn;
   const short *rmap, *smap;
+  int vstride, ncjob, nlev;
   int npool, nstrip, T, ngroup, parts, npair, nkuu;
   long long stride;
   double *slab;  // [N][stride] fronts
   double *pool;  // [N][npool][256] blocks of original entries
+  double *vec;   // [N][vstride] step vectors of the nodes
+  double *x, *y;  // [N][nx] p_x, p_y, internal order
+  double *upart;  // [N][ncjob][2][64] V_U p_u and Y_U p_u of every recovery job
   double *part;  // [parts][16 T ngroup]^2 product parts, lower triangle, tree order of u
 };
 
@@ -218,6 +223,10 @@ void launch_step_recover(const DP& d, const double* r2, const double* r3, const 
 void launch_tree_reduce(const DP& d, hipStream_t s);
 void launch_tree_product(const DP& d, hipStream_t s);
 void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s);
+void launch_tree_rhs(const DP& d, const double* r1x, const double* r2, const double* r3, const double* r4,
+                     const double* ss, hipStream_t s);
+void launch_tree_recover(const DP& d, const double* r2, const double* r4, const double* ss, const double* pu,
+                         double* px, double* ps, double* py, double* pz, hipStream_t s);
 // (k_dense.hip)
 void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s);
 void launch_stacked_product(const DP& d, hipStream_t s);
@@ -246,7 +255,8 @@ enum : int {
   kKRefactor, kKReduce64, kKReduce, kKStepRhs2, kKStepRhs, kKStepRec2, kKStepRec,
   kKStacked, kKSymSum, kKCholSmall, kKCopyChol, kKSetInfo, kKCholDiag, kKCholTrsm, kKCholUpdate,
   kKRSolveBlk, kKRSolve, kKCondenseLds,
-  kKTreeOrig, kKTreeFront, kKTreeCols, kKTreeProduct, kKTreeSum, kKTreeKuu
+  kKTreeOrig, kKTreeFront, kKTreeCols, kKTreeProduct, kKTreeSum,
+  kKTreeResid, kKTreeUp, kKTreeRhsU, kKTreeRecU, kKTreeDown, kKTreeHp, kKTreeKuu
 };
 enum : int {
   kStEvalValues = 0, kStEvalRest, kStCondense, kStRefactor, kStReduce, kStStepRhs, kStStacked,
@@ -256,7 +266,7 @@ enum : int {
 void launches_eval(const DP& d, std::vector<Launch>& out);        // values, rest, condensed values
 void launches_lu(const DP& d, std::vector<Launch>& out);          // refactor, reduce, step kernels
 void launches_dense(const DP& d, std::vector<Launch>& out);       // product, sum, Cholesky, solve
-void launches_tree(const DP& d, std::vector<Launch>& out);        // the reduction on the tree, to K_hat
+void launches_tree(const DP& d, std::vector<Launch>& out);        // the reduction on the tree, to K_hat, and the step
 // One multi-instance launch of l's kernel over nblk blocks (or, with
 // prepare, only the dynamic-LDS limit of that kernel); *handled is false when
 // the kernel is not in this file.

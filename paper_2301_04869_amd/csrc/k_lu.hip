@@ -1961,6 +1961,7 @@ void launch_identity_rows(const DP& d, hipStream_t s) {
 }
 
 void launch_refactor(const DP& d, hipStream_t s) {
+  if (d.tree) return;  // the fronts factorise G_x
   const unsigned grid = (d.N + d.spw - 1) / d.spw;
   const size_t lds = refactor_lds_bytes(sizes_of(d));
   if (d.lds_grp && d.upd_lds)
@@ -2000,6 +2001,7 @@ static bool step2(const DP& d) { return d.variant == 2 && d.lds_stp; }
 
 void launch_step_rhs(const DP& d, const double* r1x, const double* r2, const double* r3,
                      const double* r4, const double* ss, hipStream_t s) {
+  if (d.tree) return launch_tree_rhs(d, r1x, r2, r3, r4, ss, s);
   if (step2(d))
     k_step_rhs2<kGT><<<d.N, kGT, step2_lds_bytes(sizes_of(d), kGT), s>>>(d, r1x, r2, r3, r4, ss);
   else if (d.lds_stp)
@@ -2011,6 +2013,7 @@ void launch_step_rhs(const DP& d, const double* r1x, const double* r2, const dou
 void launch_step_recover(const DP& d, const double* r2, const double* r3, const double* r4,
                          const double* ss, const double* pu, double* px, double* ps, double* py,
                          double* pz, hipStream_t s) {
+  if (d.tree) return launch_tree_recover(d, r2, r4, ss, pu, px, ps, py, pz, s);
   if (step2(d))
     k_step_recover2<kGT><<<d.N, kGT, step2_lds_bytes(sizes_of(d), kGT), s>>>(d, r2, r3, r4, ss, pu,
                                                                             px, ps, py, pz);
@@ -2030,7 +2033,7 @@ namespace rkkt {
 // 2 global; reduce (64-column or narrow tiles) 2 (lds ? 1 : 0) + (variant
 // == 2); steps 0 one-solve (stacked variant), 1 LDS, 2 global.
 void launches_lu(const DP& d, std::vector<Launch>& out) {
-  {
+  if (!d.tree) {
     const LdsSizes z = sizes_of(d);
     if (d.lds_grp)
       out.push_back(Launch{kStRefactor * 4096, kKRefactor, d.upd_lds ? 0 : 1, (d.N + d.spw - 1) / d.spw, 1,
@@ -2038,8 +2041,7 @@ void launches_lu(const DP& d, std::vector<Launch>& out) {
     else
       out.push_back(Launch{kStRefactor * 4096, kKRefactor, 2, d.N, 1, kRT, 0, 0});
     const long long lds = d.lds_red ? reduce_lds_bytes(z) : 8LL * d.chain_t * d.chain_t;
-    if (!d.tree)
-      out.push_back(Launch{kStReduce * 4096, d.col_tile == kW64 ? kKReduce64 : kKReduce,
+    out.push_back(Launch{kStReduce * 4096, d.col_tile == kW64 ? kKReduce64 : kKReduce,
                          2 * (d.lds_red ? 1 : 0) + (d.variant == 2 ? 1 : 0), ntiles(d), d.N, kRT, 0, lds});
     if (step2(d)) {
       out.push_back(Launch{kStStepRhs * 4096, kKStepRhs2, 0, d.N, 1, kGT, 0, step2_lds_bytes(z, kGT)});

@@ -511,6 +511,442 @@ __device__ __forceinline__ void tree_kuu_body(const DP& d, int bx, double* khat)
   khat[(long long)b * d.nu + a] = acc;
 }
 
+// ------------------------------------------------------------------ step
+// The right-hand side is one more column b of the fronts: with
+// V_b = G_JJ^-1 r3_J and Y_b = r1_J - K_JJ V_b / 2 a node updates
+//     r3_I <- r3_I - G_IJ V_b,  r1_I <- r1_I - V_I^T Y_b - Y_I^T V_b
+// on the way up, and the reduced right-hand side takes
+// -(V_U^T Y_b + Y_U^T V_b) of all nodes.  On the way down
+//     x_J = -(V_b + V_I x_I + V_U p_u),
+//     y_J = -G_JJ^-T (Y_b + K_JJ x_J / 2 + Y_I x_I + Y_U p_u + G_IJ^T y_I),
+// so a step is one sweep up and one down; the products with the control
+// columns need no order and run over the whole chip.
+constexpr int kTS = 64 * kTreeStepWaves;  // threads of the sweeps
+
+// value summed over the lanes of a row of 16, in every lane
+__device__ __forceinline__ double sum16(double v) {
+  v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false);  // row_ror:8
+  v += __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, false);
+  return v;
+}
+// value summed over the four rows of 16 lanes
+__device__ __forceinline__ double sum_rows(double v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+// acc + sum over the block's rows of blk[row][lane%16] v[row], this lane's share
+__device__ __forceinline__ double dot_rows(const v4d& blk, const double* v, int lk, double acc) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc = fma(blk[r], v[4 * r + lk], acc);
+  return acc;
+}
+// acc[r] + blk[row 4 r + lane/16][lane%16] x, x the lane's column value
+__device__ __forceinline__ void dot_cols(const v4d& blk, double x, v4d& acc) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] = fma(blk[r], x, acc[r]);
+}
+// row 4 r + lane/16 of a reduced acc (sum16 of every acc[r]) to out, 16 rows
+__device__ __forceinline__ void put_rows(const v4d& acc, double* out, int lane) {
+  const int lm = lane & 15, lk = lane >> 4;
+  double v = 0.0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double t = sum16(acc[r]);
+    if (lm == r) v = t;
+  }
+  if (lm < 4) out[4 * lm + lk] = v;
+}
+
+// rhat1 = r1x + H_x^T w and r3 in internal order, -H_u^T w into rpart, with
+// w = Sigma_s r4 - r2 formed per use
+__device__ __forceinline__ void tree_resid_body(const DP& d, int bx, int k, const double* r1x, const double* r2,
+                                                const double* r3, const double* r4, const double* ss) {
+  const int v = bx * kTT + threadIdx.x, nx = d.nx;
+  if (v >= d.nz) return;
+  const double* hv = d.EV + (long long)k * d.n_ev + d.off_h;
+  const double *ssk = ss + (long long)k * d.m, *r2k = r2 + (long long)k * d.m, *r4k = r4 + (long long)k * d.m;
+  const int pi = v < nx ? d.perm[v] : 0;
+  double acc = v < nx ? r1x[(long long)k * nx + pi] : 0.0;
+  const int j1 = d.ht_ptr[v + 1];
+  for (int j = d.ht_ptr[v]; j < j1; j += 4) {
+    double hj[4], wj[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int jj = min(j + u, j1 - 1), r = d.ht_row[jj];
+      hj[u] = hv[d.ht_pos[jj]];
+      wj[u] = ssk[r] * r4k[r] - r2k[r];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (j + u < j1) acc = fma(hj[u], wj[u], acc);
+  }
+  if (v < nx) {
+    d.rhat1[(long long)k * nx + v] = acc;
+    d.qbuf[(long long)k * nx + v] = r3[(long long)k * nx + pi];
+  } else {
+    d.rpart[(long long)k * d.nu + v - nx] = -acc;
+  }
+}
+
+// V_b and Y_b of one node by one wavefront; b: 2 x 64 doubles of LDS of its own
+template <int NB>
+__device__ __forceinline__ void up_pivot(const DP& d, const TreeNode& n, int k, double* b, int lane) {
+  const int lm = lane & 15, lk = lane >> 4;
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  v4d lu[NB * NB];
+#pragma unroll
+  for (int q = 0; q < NB * NB; ++q) lu[q] = load_blk(slab + n.lu + q * kTreeBlk, lane);
+  // lane: padded pivot row
+  double b3 = 0.0, b1 = 0.0;
+  if (lane < n.s) {
+    const long long at = (long long)k * d.nx + d.tr.rows[n.row0 + lane];
+    b3 = d.qbuf[at];
+    b1 = d.rhat1[at];
+  }
+  if (lane < NB * kTreeB)
+    for (int a = 0; a < n.nchild; ++a) {
+      const TreeChild ch = d.tr.children[n.child0 + a];
+      const TreeNode& c = d.tr.nodes[ch.node];
+      const int ci = d.tr.rmap[ch.rmap0 + lane];
+      if (ci >= 0) {
+        const double* cv = vec + c.vec + 2 * kTreeB * c.nb + ci;
+        b3 += cv[0];
+        b1 += cv[kTreeB * c.ib];
+      }
+    }
+  b[lane] = b3;
+  wave_sync();
+#pragma unroll
+  for (int p = 1; p < NB; ++p) {
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < p; ++j) acc = dot_rows(lu[p * NB + j], b + j * kTreeB, lk, acc);
+    acc = sum_rows(acc);
+    if (lk == 0) b[p * kTreeB + lm] -= acc;
+    wave_sync();
+  }
+#pragma unroll
+  for (int p = NB - 1; p >= 0; --p) {
+    double acc = 0.0;
+#pragma unroll
+    for (int j = p + 1; j < NB; ++j) acc = dot_rows(lu[p * NB + j], b + j * kTreeB, lk, acc);
+    acc = sum_rows(acc);
+    if (lk == 0) b[p * kTreeB + lm] -= acc;
+    wave_sync();
+    acc = sum_rows(dot_rows(lu[p * NB + p], b + p * kTreeB, lk, 0.0));
+    wave_sync();
+    if (lk == 0) b[p * kTreeB + lm] = acc;
+    wave_sync();
+  }
+  double* y = b + 64;
+  y[lane] = b1;
+  wave_sync();
+#pragma unroll
+  for (int p = 0; p < NB; ++p) {
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      acc = dot_rows(load_blk(slab + n.kjj + (j * NB + p) * kTreeBlk, lane), b + j * kTreeB, lk, acc);
+    acc = sum_rows(acc);
+    if (lk == 0) y[p * kTreeB + lm] = fma(-0.5, acc, y[p * kTreeB + lm]);
+  }
+  wave_sync();
+  if (lane < NB * kTreeB) {
+    vec[n.vec + lane] = b[lane];
+    vec[n.vec + NB * kTreeB + lane] = y[lane];
+  }
+}
+
+// Sweep up over the levels [l0, l1): a node's V_b and Y_b by one wavefront,
+// then its interface strips, one wavefront each.  Workgroup bx of gx takes
+// every gx-th node of a level (gx > 1 for one level only).
+__device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k, int l0, int l1) {
+  __shared__ double sb[kTreeStepWaves][2 * 64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lm = lane & 15, lk = lane >> 4;
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  for (int l = l0; l < l1; ++l) {
+    const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
+    for (int q = q0 + bx + wv * gx; q < q1; q += kTreeStepWaves * gx) {
+      const TreeNode n = d.tr.nodes[d.tr.lev_nodes[q]];
+      switch (n.nb) {
+        case 1: up_pivot<1>(d, n, k, sb[wv], lane); break;
+        case 2: up_pivot<2>(d, n, k, sb[wv], lane); break;
+        case 3: up_pivot<3>(d, n, k, sb[wv], lane); break;
+        default: up_pivot<4>(d, n, k, sb[wv], lane); break;
+      }
+    }
+    __syncthreads();
+    int turn = wv;  // strips of the workgroup's nodes, dealt out in turn
+    for (int q = q0 + bx; q < q1; q += gx) {
+      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[q]];
+      const int nb = n.nb, ib = n.ib;
+      int m = turn;
+      for (; m < ib; m += kTreeStepWaves) {
+        const double *vb = vec + n.vec, *yb = vb + nb * kTreeB;
+        double a3 = 0.0, a1 = 0.0;
+        for (int p = 0; p < nb; ++p) {
+          const long long at = (long long)(m * nb + p) * kTreeBlk;
+          const v4d g = load_blk(slab + n.gijt + at, lane), v = load_blk(slab + n.v + at, lane),
+                    y = load_blk(slab + n.y + at, lane);
+          a3 = dot_rows(g, vb + p * kTreeB, lk, a3);
+          a1 = dot_rows(v, yb + p * kTreeB, lk, a1);
+          a1 = dot_rows(y, vb + p * kTreeB, lk, a1);
+        }
+        a3 = -sum_rows(a3);
+        a1 = -sum_rows(a1);
+        const int row = (nb + m) * kTreeB + lm;
+        for (int a = 0; a < n.nchild; ++a) {
+          const TreeChild ch = d.tr.children[n.child0 + a];
+          const TreeNode& c = d.tr.nodes[ch.node];
+          const int ci = d.tr.rmap[ch.rmap0 + row];
+          if (ci >= 0) {
+            const double* cv = vec + c.vec + 2 * kTreeB * c.nb + ci;
+            a3 += cv[0];
+            a1 += cv[kTreeB * c.ib];
+          }
+        }
+        if (lk == 0) {
+          double* o = vec + n.vec + 2 * kTreeB * nb + m * kTreeB + lm;
+          o[0] = a3;
+          o[kTreeB * ib] = a1;
+        }
+      }
+      turn = m - ib;
+    }
+    __syncthreads();
+  }
+}
+
+// rpart of one control strip: the nodes that hold it, dealt to the wavefronts
+__device__ __forceinline__ void tree_rhs_u_body(const DP& d, int z, int k) {
+  __shared__ double red[4][kTreeB];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lm = lane & 15, lk = lane >> 4;
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  const double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  double acc = 0.0;
+  const int e1 = d.tr.sn_ptr[z + 1];
+  for (int e = d.tr.sn_ptr[z] + wv; e < e1; e += 4) {
+    const TreeNode& n = d.tr.nodes[d.tr.sn[2 * e]];
+    const int nb = n.nb;
+    const long long at = (long long)(n.ib + d.tr.sn[2 * e + 1]) * nb * kTreeBlk;
+    const double *vb = vec + n.vec, *yb = vb + nb * kTreeB;
+    for (int p = 0; p < nb; ++p) {
+      acc = dot_rows(load_blk(slab + n.v + at + p * kTreeBlk, lane), yb + p * kTreeB, lk, acc);
+      acc = dot_rows(load_blk(slab + n.y + at + p * kTreeBlk, lane), vb + p * kTreeB, lk, acc);
+    }
+  }
+  acc = sum_rows(acc);
+  if (lk == 0) red[wv][lm] = acc;
+  __syncthreads();
+  const int p = z * kTreeB + threadIdx.x;
+  if (threadIdx.x < kTreeB && p < d.nu) {
+    const int t = threadIdx.x;
+    d.rpart[(long long)k * d.nu + d.tr.uord[p]] += (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+  }
+}
+
+// V_U p_u and Y_U p_u of kTreeCJob control strips of a node
+template <int NB>
+__device__ __forceinline__ void rec_u(const DP& d, const TreeNode& n, int c0, int job, int k, const double* pu,
+                                      double (*red)[2][kTreeRows], int lane, int wv) {
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  const int lm = lane & 15;
+  v4d av[NB], ay[NB];
+#pragma unroll
+  for (int p = 0; p < NB; ++p) av[p] = ay[p] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int c1 = min(n.us, c0 + kTreeCJob);
+  for (int c = c0 + wv; c < c1; c += 4) {
+    const int z = d.tr.strips[n.strip0 + c] * kTreeB + lm;
+    const double x = z < d.nu ? pu[d.tr.uord[z]] : 0.0;
+    const long long at = (long long)(n.ib + c) * NB * kTreeBlk;
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      dot_cols(load_blk(slab + n.v + at + p * kTreeBlk, lane), x, av[p]);
+      dot_cols(load_blk(slab + n.y + at + p * kTreeBlk, lane), x, ay[p]);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NB; ++p) {
+    put_rows(av[p], &red[wv][0][p * kTreeB], lane);
+    put_rows(ay[p], &red[wv][1][p * kTreeB], lane);
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < 2 * NB * kTreeB) {
+    const int h = t / (NB * kTreeB), r = t % (NB * kTreeB);
+    d.tr.upart[(((long long)k * d.tr.ncjob + job) * 2 + h) * kTreeRows + r] =
+        (red[0][h][r] + red[1][h][r]) + (red[2][h][r] + red[3][h][r]);
+  }
+}
+
+__device__ __forceinline__ void tree_rec_u_body(const DP& d, int job, int k, const double* pu) {
+  __shared__ double red[4][2][kTreeRows];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const TreeNode n = d.tr.nodes[d.tr.cjobs[2 * job]];
+  const int c0 = d.tr.cjobs[2 * job + 1];
+  switch (n.nb) {
+    case 1: rec_u<1>(d, n, c0, job, k, pu, red, lane, wv); break;
+    case 2: rec_u<2>(d, n, c0, job, k, pu, red, lane, wv); break;
+    case 3: rec_u<3>(d, n, c0, job, k, pu, red, lane, wv); break;
+    default: rec_u<4>(d, n, c0, job, k, pu, red, lane, wv); break;
+  }
+}
+
+// y_J = -G_JJ^-T t of one node by one wavefront; t: 64 doubles of LDS
+template <int NB>
+__device__ __forceinline__ void down_pivot(const DP& d, const TreeNode& n, int k, double* t, double* py, int lane) {
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  const int lm = lane & 15;
+  v4d lu[NB * NB];
+#pragma unroll
+  for (int q = 0; q < NB * NB; ++q) lu[q] = load_blk(slab + n.lu + q * kTreeBlk, lane);
+#pragma unroll
+  for (int p = 0; p < NB; ++p) {
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < p; ++j) dot_cols(lu[j * NB + p], -t[j * kTreeB + lm], acc);
+    if (p > 0) {
+      double* s = t + 64;
+      put_rows(acc, s, lane);
+      wave_sync();
+      if (lane < kTreeB) t[p * kTreeB + lane] += s[lane];
+      wave_sync();
+    }
+    v4d z = {0.0, 0.0, 0.0, 0.0};
+    dot_cols(lu[p * NB + p], t[p * kTreeB + lm], z);
+    wave_sync();
+    put_rows(z, t + p * kTreeB, lane);
+    wave_sync();
+  }
+#pragma unroll
+  for (int p = NB - 2; p >= 0; --p) {
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = p + 1; j < NB; ++j) dot_cols(lu[j * NB + p], -t[j * kTreeB + lm], acc);
+    double* s = t + 64;
+    put_rows(acc, s, lane);
+    wave_sync();
+    if (lane < kTreeB) t[p * kTreeB + lane] += s[lane];
+    wave_sync();
+  }
+  if (lane < n.s) {
+    const int row = d.tr.rows[n.row0 + lane];
+    const double v = -t[lane];
+    d.tr.y[(long long)k * d.nx + row] = v;
+    py[(long long)k * d.nx + d.perm[row]] = v;
+  }
+}
+
+// Sweep down over the levels l1 - 1 .. l0, split over workgroups like the
+// sweep up: x_J, then the right-hand side of y_J (both by pivot block rows,
+// one wavefront each), then y_J by one wavefront.
+__device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int k, int l0, int l1, double* px,
+                                               double* py) {
+  __shared__ double sb[kTreeStepWaves][80];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lm = lane & 15;
+  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
+  double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  double* xk = d.tr.x + (long long)k * d.nx;
+  double* yk = d.tr.y + (long long)k * d.nx;
+  const double* up = d.tr.upart + (long long)k * d.tr.ncjob * 2 * kTreeRows;
+  for (int l = l1 - 1; l >= l0; --l) {
+    const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
+    for (int ph = 0; ph < 2; ++ph) {
+      int turn = wv;
+      for (int q = q0 + bx; q < q1; q += gx) {
+        const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[q]];
+        const int nb = n.nb, ib = n.ib;
+        int p = turn;
+        for (; p < nb; p += kTreeStepWaves) {
+          v4d acc = {0.0, 0.0, 0.0, 0.0};
+          const double* blk = slab + (ph ? n.y : n.v);
+          for (int m = 0; m < ib; ++m) {
+            const int j = m * kTreeB + lm;
+            const int row = j < n.i ? d.tr.rows[n.row0 + n.s + j] : -1;
+            const double x = row >= 0 ? xk[row] : 0.0;
+            dot_cols(load_blk(blk + (long long)(m * nb + p) * kTreeBlk, lane), x, acc);
+            if (ph) {
+              const double y = row >= 0 ? yk[row] : 0.0;
+              dot_cols(load_blk(slab + n.gijt + (long long)(m * nb + p) * kTreeBlk, lane), y, acc);
+            }
+          }
+          if (ph)
+            for (int j = 0; j < nb; ++j) {
+              const int at = j * kTreeB + lm;
+              const double x = at < n.s ? 0.5 * xk[d.tr.rows[n.row0 + at]] : 0.0;
+              dot_cols(load_blk(slab + n.kjj + (long long)(p * nb + j) * kTreeBlk, lane), x, acc);
+            }
+          put_rows(acc, sb[wv], lane);
+          wave_sync();
+          if (lane < kTreeB) {
+            double v = sb[wv][lane];
+            double* o = vec + n.vec + ph * nb * kTreeB + p * kTreeB + lane;
+            v += *o;
+            for (int c = 0; c < n.ncjob; ++c) v += up[((long long)(n.cjob0 + c) * 2 + ph) * kTreeRows + p * kTreeB + lane];
+            const int at = p * kTreeB + lane;
+            if (ph) {
+              *o = v;  // Y_b becomes the right-hand side of y_J
+            } else if (at < n.s) {
+              const int row = d.tr.rows[n.row0 + at];
+              xk[row] = -v;
+              px[(long long)k * d.nx + d.perm[row]] = -v;
+            }
+          }
+          wave_sync();
+        }
+        turn = p - nb;
+      }
+      __syncthreads();
+    }
+    for (int q = q0 + bx + wv * gx; q < q1; q += kTreeStepWaves * gx) {
+      const TreeNode n = d.tr.nodes[d.tr.lev_nodes[q]];
+      if (lane < n.nb * kTreeB) sb[wv][lane] = vec[n.vec + n.nb * kTreeB + lane];
+      wave_sync();
+      switch (n.nb) {
+        case 1: down_pivot<1>(d, n, k, sb[wv], py, lane); break;
+        case 2: down_pivot<2>(d, n, k, sb[wv], py, lane); break;
+        case 3: down_pivot<3>(d, n, k, sb[wv], py, lane); break;
+        default: down_pivot<4>(d, n, k, sb[wv], py, lane); break;
+      }
+      wave_sync();
+    }
+    __syncthreads();
+  }
+}
+
+// p_s = -(r4 + H p_d), p_z = Sigma_s (H p_d + r4) - r2
+__device__ __forceinline__ void tree_hp_body(const DP& d, int bx, int k, const double* r2, const double* r4,
+                                             const double* ss, const double* pu, double* ps, double* pz) {
+  const int r = bx * kTT + threadIdx.x;
+  if (r >= d.m) return;
+  const double* hv = d.EV + (long long)k * d.n_ev + d.off_h;
+  const double* xk = d.tr.x + (long long)k * d.nx;
+  double hp = 0.0;
+  const int e1 = d.h_ptr[r + 1];
+  for (int e = d.h_ptr[r]; e < e1; e += 4) {
+    double h[4], x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int ee = min(e + u, e1 - 1), c = d.h_col[ee];
+      h[u] = hv[ee];
+      x[u] = c < d.nx ? xk[c] : pu[c - d.nx];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (e + u < e1) hp = fma(h[u], x[u], hp);
+  }
+  const long long at = (long long)k * d.m + r;
+  ps[at] = -(r4[at] + hp);
+  pz[at] = ss[at] * (hp + r4[at]) - r2[at];
+}
+
 __global__ __launch_bounds__(kTT) void k_tree_orig(DP d) { tree_orig_body(d, blockIdx.x, blockIdx.y); }
 __global__ __launch_bounds__(kTT) void k_tree_front(DP d, int first) {
   tree_front_body(d, d.tr.lev_nodes[first + blockIdx.x], blockIdx.y);
@@ -524,6 +960,24 @@ __global__ __launch_bounds__(kTT) void k_tree_sum(DP d, const double* su, double
   tree_sum_body(d, blockIdx.x, blockIdx.y, su, dw, khat);
 }
 __global__ __launch_bounds__(kTT) void k_tree_kuu(DP d, double* khat) { tree_kuu_body(d, blockIdx.x, khat); }
+__global__ __launch_bounds__(kTT) void k_tree_resid(DP d, const double* r1x, const double* r2, const double* r3,
+                                                    const double* r4, const double* ss) {
+  tree_resid_body(d, blockIdx.x, blockIdx.y, r1x, r2, r3, r4, ss);
+}
+__global__ __launch_bounds__(kTS) void k_tree_up(DP d, int l0, int l1) {
+  tree_up_body(d, blockIdx.x, gridDim.x, blockIdx.y, l0, l1);
+}
+__global__ __launch_bounds__(kTT) void k_tree_rhs_u(DP d) { tree_rhs_u_body(d, blockIdx.x, blockIdx.y); }
+__global__ __launch_bounds__(kTT) void k_tree_rec_u(DP d, const double* pu) {
+  tree_rec_u_body(d, blockIdx.x, blockIdx.y, pu);
+}
+__global__ __launch_bounds__(kTS) void k_tree_down(DP d, int l0, int l1, double* px, double* py) {
+  tree_down_body(d, blockIdx.x, gridDim.x, blockIdx.y, l0, l1, px, py);
+}
+__global__ __launch_bounds__(kTT) void k_tree_hp(DP d, const double* r2, const double* r4, const double* ss,
+                                                 const double* pu, double* ps, double* pz) {
+  tree_hp_body(d, blockIdx.x, blockIdx.y, r2, r4, ss, pu, ps, pz);
+}
 
 #define RKKT_MULTI_ARGS \
   const DP* __restrict__ dps, const rkkt_iteration* __restrict__ its, const MultiBlk* __restrict__ blk
@@ -559,6 +1013,31 @@ __global__ __launch_bounds__(kTT) void k_tree_kuu_m(RKKT_MULTI_ARGS) {
   tree_kuu_body(d, mb.bx, it.khat);
 }
 
+__global__ __launch_bounds__(kTT) void k_tree_resid_m(RKKT_MULTI_ARGS) {
+  RKKT_MULTI_PROLOGUE
+  tree_resid_body(d, mb.bx, mb.by, it.r1x, it.r2, it.r3, it.r4, it.sigma_s);
+}
+__global__ __launch_bounds__(kTS) void k_tree_up_m(RKKT_MULTI_ARGS, int l0, int l1) {
+  RKKT_MULTI_PROLOGUE
+  tree_up_body(d, mb.bx, mb.gx, mb.by, l0, l1 ? l1 : d.tr.nlev);
+}
+__global__ __launch_bounds__(kTT) void k_tree_rhs_u_m(RKKT_MULTI_ARGS) {
+  RKKT_MULTI_PROLOGUE
+  tree_rhs_u_body(d, mb.bx, mb.by);
+}
+__global__ __launch_bounds__(kTT) void k_tree_rec_u_m(RKKT_MULTI_ARGS) {
+  RKKT_MULTI_PROLOGUE
+  tree_rec_u_body(d, mb.bx, mb.by, it.pu);
+}
+__global__ __launch_bounds__(kTS) void k_tree_down_m(RKKT_MULTI_ARGS, int l0, int l1) {
+  RKKT_MULTI_PROLOGUE
+  tree_down_body(d, mb.bx, mb.gx, mb.by, l0, l1 ? l1 : d.tr.nlev, it.px, it.py);
+}
+__global__ __launch_bounds__(kTT) void k_tree_hp_m(RKKT_MULTI_ARGS) {
+  RKKT_MULTI_PROLOGUE
+  tree_hp_body(d, mb.bx, mb.by, it.r2, it.r4, it.sigma_s, it.pu, it.ps, it.pz);
+}
+
 unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 
 }  // namespace
@@ -585,6 +1064,30 @@ void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hip
   k_tree_kuu<<<cdiv(d.tr.nkuu, kTT), kTT, 0, s>>>(d, khat);
 }
 
+// workgroups per scenario of a level's part of a sweep
+static int wide_groups(const Tree& t, int l) { return (int)cdiv(t.lev_ptr[l + 1] - t.lev_ptr[l], kTreeStepWaves); }
+
+void launch_tree_rhs(const DP& d, const double* r1x, const double* r2, const double* r3, const double* r4,
+                     const double* ss, hipStream_t s) {
+  const Tree& t = *d.tr.host;
+  k_tree_resid<<<dim3(cdiv(d.nz, kTT), d.N), kTT, 0, s>>>(d, r1x, r2, r3, r4, ss);
+  const int nw = tree_wide_levels(t);
+  for (int l = 0; l < nw; ++l) k_tree_up<<<dim3(wide_groups(t, l), d.N), kTS, 0, s>>>(d, l, l + 1);
+  if (nw < d.tr.nlev) k_tree_up<<<dim3(1, d.N), kTS, 0, s>>>(d, nw, d.tr.nlev);
+  k_tree_rhs_u<<<dim3(d.tr.nstrip, d.N), kTT, 0, s>>>(d);
+}
+
+void launch_tree_recover(const DP& d, const double* r2, const double* r4, const double* ss, const double* pu,
+                         double* px, double* ps, double* py, double* pz, hipStream_t s) {
+  const Tree& t = *d.tr.host;
+  if (d.tr.ncjob > 0) k_tree_rec_u<<<dim3(d.tr.ncjob, d.N), kTT, 0, s>>>(d, pu);
+  const int nw = tree_wide_levels(t);
+  if (nw < d.tr.nlev) k_tree_down<<<dim3(1, d.N), kTS, 0, s>>>(d, nw, d.tr.nlev, px, py);
+  for (int l = nw - 1; l >= 0; --l) k_tree_down<<<dim3(wide_groups(t, l), d.N), kTS, 0, s>>>(d, l, l + 1, px, py);
+  k_tree_hp<<<dim3(cdiv(d.m, kTT), d.N), kTT, 0, s>>>(d, r2, r4, ss, pu, ps, pz);
+}
+
+// jb of a sweep's launch: first level | level after the last << 16 (0: the tree's last)
 void launches_tree(const DP& d, std::vector<Launch>& out) {
   const Tree& t = *d.tr.host;
   const int R = kStReduce * 4096;
@@ -599,6 +1102,20 @@ void launches_tree(const DP& d, std::vector<Launch>& out) {
                        kTT, 0, 0});
   out.push_back(Launch{kStSum * 4096, kKTreeSum, 0, d.tr.nstrip, d.tr.nstrip, kTT, 0, 0});
   out.push_back(Launch{kStSum * 4096 + 1, kKTreeKuu, 0, (int)cdiv(d.tr.nkuu, kTT), 1, kTT, 0, 0});
+  const int nw = tree_wide_levels(t);
+  const int H = kStStepRhs * 4096, B = kStRecover * 4096;
+  out.push_back(Launch{H, kKTreeResid, 0, (int)cdiv(d.nz, kTT), d.N, kTT, 0, 0});
+  out.push_back(Launch{B, kKTreeRecU, 0, d.tr.ncjob, d.N, kTT, 0, 0});
+  for (int l = 0; l < nw; ++l) {
+    out.push_back(Launch{H + 1 + l, kKTreeUp, 0, wide_groups(t, l), d.N, kTS, l | (l + 1) << 16, 0});
+    out.push_back(Launch{B + 2047 - l, kKTreeDown, 0, wide_groups(t, l), d.N, kTS, l | (l + 1) << 16, 0});
+  }
+  if (nw < nlev) {
+    out.push_back(Launch{H + 2048, kKTreeUp, 0, 1, d.N, kTS, nw, 0});
+    out.push_back(Launch{B + 1, kKTreeDown, 0, 1, d.N, kTS, nw, 0});
+  }
+  out.push_back(Launch{H + 2049, kKTreeRhsU, 0, d.tr.nstrip, d.N, kTT, 0, 0});
+  out.push_back(Launch{B + 2048, kKTreeHp, 0, (int)cdiv(d.m, kTT), d.N, kTT, 0, 0});
 }
 
 hipError_t multi_tree(const Launch& l, unsigned nblk, const DP* dps, const rkkt_iteration* its, const MultiBlk* blk,
@@ -613,6 +1130,12 @@ hipError_t multi_tree(const Launch& l, unsigned nblk, const DP* dps, const rkkt_
       if (l.variant) k_tree_product_m<4><<<nblk, kTT, 0, s>>>(dps, its, blk);
       else k_tree_product_m<2><<<nblk, kTT, 0, s>>>(dps, its, blk);
       break;
+    case kKTreeResid: k_tree_resid_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
+    case kKTreeUp: k_tree_up_m<<<nblk, kTS, 0, s>>>(dps, its, blk, l.jb & 0xffff, l.jb >> 16); break;
+    case kKTreeRhsU: k_tree_rhs_u_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
+    case kKTreeRecU: k_tree_rec_u_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
+    case kKTreeDown: k_tree_down_m<<<nblk, kTS, 0, s>>>(dps, its, blk, l.jb & 0xffff, l.jb >> 16); break;
+    case kKTreeHp: k_tree_hp_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
     case kKTreeSum: k_tree_sum_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
     default: k_tree_kuu_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
   }

@@ -364,7 +364,7 @@ LdsSizes lds_sizes(const Sym& s, int w, int variant, int spw) {
   return z;
 }
 
-std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* opt, Sym& s) {
+std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* opt, Sym& s, bool for_device) {
   const int col_tile_req = opt ? opt->col_tile : 0, variant_req = opt ? opt->variant : 0;
   const int spw_req = opt ? opt->scen_per_group : 0, chain_req = opt ? opt->chain_rows : 0;
   if (spw_req != 0 && spw_req != 1 && spw_req != 2 && spw_req != 4) return "scen_per_group must be 0, 1, 2 or 4";
@@ -860,6 +860,7 @@ std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* o
     nc = (rows + per - 1) / per;
     s.nchunk = (int)nc;
   }
+  if (for_device && s.tree) return "";
   // schedules
   if (s.sweep_form == 2) {
     build_pull_sched(s, true, kRedThreads / s.col_tile, s.red_up);

@@ -119,8 +119,10 @@ struct Sym {
   int nchunk = 1;            // contraction chunks of the stacked product
 };
 
-// Returns an empty string on success, else the error message.
-std::string build_symbolic(const rkkt_network& net, int n_scen, const rkkt_options* opt, Sym& s);
+// Returns an empty string on success, else the error message.  for_device:
+// leaves out the level-sliced schedules where no kernel follows them (tree).
+std::string build_symbolic(const rkkt_network& net, int n_scen, const rkkt_options* opt, Sym& s,
+                           bool for_device = false);
 
 // sizes fixing the LDS layouts, for a tile width
 LdsSizes lds_sizes(const Sym& s, int w, int variant, int spw);

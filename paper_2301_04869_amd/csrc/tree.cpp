@@ -252,6 +252,14 @@ std::string build_tree(const Sym& s, Tree& t) {
     n.y = take((long long)n.cs * n.nb);
     n.gu = take((long long)n.cs * n.ib);
     n.ku = take((long long)n.cs * n.ib);
+    n.vec = t.vstride;
+    t.vstride += 2 * kTreeB * (n.nb + n.ib);
+    n.cjob0 = (int)t.cjobs.size() / 2;
+    for (int c = 0; c < n.us; c += kTreeCJob) {
+      t.cjobs.push_back(q);
+      t.cjobs.push_back(c);
+    }
+    n.ncjob = (int)t.cjobs.size() / 2 - n.cjob0;
     n.oblk = (int)t.orig.size();
     t.orig.resize(t.orig.size() + 2 * n.nb * n.nb + n.ib * n.nb + 2 * n.cs * n.nb, -1);
   }
@@ -361,6 +369,21 @@ std::string build_tree(const Sym& s, Tree& t) {
   t.lev_ptr.push_back((int)t.lev_nodes.size());
   t.job_ptr.push_back((int)t.jobs.size() / 2);
 
+  // nodes of every global strip
+  {
+    std::vector<std::vector<int>> of(t.nstrip);
+    for (int q = 0; q < nn; ++q)
+      for (int k = 0; k < (int)strips[q].size(); ++k) {
+        of[strips[q][k]].push_back(q);
+        of[strips[q][k]].push_back(k);
+      }
+    t.sn_ptr.push_back(0);
+    for (auto& v : of) {
+      t.sn.insert(t.sn.end(), v.begin(), v.end());
+      t.sn_ptr.push_back((int)t.sn.size() / 2);
+    }
+  }
+
   // K_uu
   for (int r = nx; r < s.nz; ++r)
     for (int e = s.k_usplit[r]; e < s.k_ptr[r + 1]; ++e)
@@ -406,6 +429,12 @@ std::string build_tree(const Sym& s, Tree& t) {
   for (const auto& l : lists) longest = std::max(longest, (long long)l.size());
   t.parts = (int)std::max(1LL, std::min({32LL, longest * s.N, (4096 + npair - 1) / npair}));
   return "";
+}
+
+int tree_wide_levels(const Tree& t) {
+  int l = 0;
+  while (l + 1 < (int)t.lev_ptr.size() && t.lev_ptr[l + 1] - t.lev_ptr[l] > kTreeWide) ++l;
+  return l;
 }
 
 }  // namespace rkkt

@@ -24,6 +24,7 @@ constexpr int kTreeB = 16;                     // block side (one FP64 matrix in
 constexpr int kTreeNB = 4;                     // pivot block rows of a node, at most
 constexpr int kTreeRows = kTreeB * kTreeNB;    // pivot rows of a node, at most
 constexpr int kTreeBlk = kTreeB * kTreeB;      // doubles of a block
+constexpr int kTreeCJob = 16;                  // control strips of a recovery job
 
 // One node.  Blocks are 16 x 16, row-major and contiguous; nb pivot block
 // rows, ib interface strips, us control strips, cs = ib + us strips in all.
@@ -41,6 +42,9 @@ struct TreeNode {
   int row0;        // rows[row0 ..]: internal row of every pivot row, then of every interface row
   int child0, nchild;
   int strip0;      // strips[strip0 .. + us]: global strip of every control strip
+  int vec;         // offset in the scenario's step vectors: V_b, Y_b (16 nb each), then the updates
+                   // of r3 and r1 in the interface rows (16 ib each)
+  int cjob0, ncjob;  // control-part jobs of the step's recovery
   int oblk;        // orig table: lu nb nb, kjj nb nb, gijt ib nb, v cs nb, y cs nb
   long long lu, kjj, gijt, v, y, gu, ku;
 };
@@ -67,6 +71,11 @@ struct Tree {
   // nodes of every level; strip jobs of every level (node, first strip), four
   // strips each, interface strips first
   std::vector<int> lev_ptr, lev_nodes, job_ptr, jobs;
+  // step: length of a scenario's vectors; recovery jobs (node, first control
+  // strip), kTreeCJob strips each; nodes of every global strip with their
+  // local strip, sn[2 sn_ptr[z] ..)
+  int vstride = 0;
+  std::vector<int> cjobs, sn_ptr, sn;
   // control columns: uord[p] = u of place p, upos the inverse; nstrip strips
   std::vector<int> uord, upos;
   int nstrip = 0;
@@ -81,5 +90,11 @@ struct Tree {
 
 // Builds the tree from the filled pattern; empty string on success.
 std::string build_tree(const Sym& s, Tree& t);
+
+// Levels whose nodes are spread over several workgroups per scenario in the
+// step's sweeps (one launch each): the first levels, while they hold more
+// than kTreeWide nodes.  The rest run in one workgroup per scenario.
+constexpr int kTreeWide = 32, kTreeStepWaves = 8;
+int tree_wide_levels(const Tree& t);
 
 }  // namespace rkkt
