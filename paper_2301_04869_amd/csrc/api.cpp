@@ -197,6 +197,10 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
   }
   if (p->sym.tree) {
     m = rkkt::build_tree(p->sym, p->tree);
+    if (m.empty() && !rkkt::tree_fits(p->tree)) {
+      p->tree = rkkt::Tree();
+      m = rkkt::build_symbolic(*net, n_scen, opt, p->sym, true, false);
+    }
     if (!m.empty()) {
       delete p;
       return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: " + m);
@@ -430,6 +434,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = dalloc(p, &d.rpart, N * s.nu)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.qbuf, N * s.nx)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.status, 2)) != hipSuccess) goto hip_error;
+    if (d.tree && (e = rkkt::configure_tree_kernels()) != hipSuccess) goto hip_error;
     if ((e = rkkt::configure_lu_kernels(d)) != hipSuccess) goto hip_error;
     if ((e = rkkt::configure_dense_kernels(d)) != hipSuccess) goto hip_error;
     if ((e = rkkt::configure_eval_kernels(d)) != hipSuccess) goto hip_error;
@@ -752,7 +757,7 @@ static hipError_t multi_dispatch(const rkkt_multi* m, const rkkt_multi::Group& g
   const rkkt::MultiBlk* blk = m->blk + g.off;
   hipError_t e = rkkt::multi_eval(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) e = rkkt::multi_lu(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
-  if (!handled) e = rkkt::multi_tree(g.l, g.nblk, m->dps, m->its, blk, s, prepare, &handled);
+  if (!handled) e = rkkt::multi_tree(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) e = rkkt::multi_dense(g.l, g.nblk, g.lds, m->dps, m->its, blk, s, prepare, &handled);
   if (!handled) return hipErrorInvalidValue;
   return e;

@@ -220,6 +220,8 @@ void launch_step_recover(const DP& d, const double* r2, const double* r3, const 
                          const double* ss, const double* pu, double* px, double* ps,
                          double* py, double* pz, hipStream_t s);
 // (k_tree.hip) fronts up the tree; product over the control columns; K_hat
+bool tree_fits(const Tree& t);        // index data of every level fit the pivot kernel's LDS
+hipError_t configure_tree_kernels();  // dynamic LDS limits; called by rkkt_create
 void launch_tree_reduce(const DP& d, hipStream_t s);
 void launch_tree_product(const DP& d, hipStream_t s);
 void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s);
@@ -274,8 +276,8 @@ hipError_t multi_eval(const Launch& l, unsigned nblk, long long lds, const DP* d
                       const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
 hipError_t multi_lu(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
                     const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
-hipError_t multi_tree(const Launch& l, unsigned nblk, const DP* dps, const rkkt_iteration* its, const MultiBlk* blk,
-                      hipStream_t s, bool prepare, bool* handled);
+hipError_t multi_tree(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
+                      const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
 hipError_t multi_dense(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
                        const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled);
 

@@ -29,7 +29,27 @@ namespace {
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kTT = 256;  // threads of the tree kernels (4 wavefronts)
-constexpr int kTld = kTreeRows + 1;
+constexpr int kTF = 512;  // threads of the pivot kernel
+constexpr int kFrontKids = 32;  // children whose records it keeps in LDS
+constexpr int kTld = kTreeRows + 4;  // rows of G_JJ in LDS four 8-byte banks apart
+
+// pivot kernel of a level: 1 maps in LDS, 2 all strips in the same launch
+// (levels whose nodes hold at most kFuseStrips strips: beyond, one workgroup's
+// matrix cores take longer over them than a second launch over many.  Limits
+// 0, 3, 6, 10, 16 at 300 buses x 16: 617, 610, 586, 577, 584 us per pass; at
+// 1354 x 8: 1653, 1636, 1623, 1610, 1603; at 2869 x 8 3401 to 3379)
+constexpr int kFuseStrips = 10;
+int front_variant(const Tree& t, int l) {
+  return (t.lev_map[l] <= kTreeMapLds ? 1 : 0) + (t.lev_cs[l] <= kFuseStrips ? 2 : 0);
+}
+// its LDS: G_JJ, the pool blocks and the children's maps
+size_t front_lds(const Tree& t, int l) {
+  const int v = front_variant(t, l), ib = t.lev_ib[l], st = v & 2 ? t.lev_cs[l] : ib;
+  const size_t blocks = 2 * kTreeNB * kTreeNB + (size_t)kTreeNB * (ib + 2 * st);
+  return 8 * (size_t)kTreeRows * kTld + 4 * blocks + (v & 1 ? 2 * (size_t)t.lev_map[l] + 4 : 0);
+}
+// the most that the device allows it next to its static arrays
+constexpr int kFrontLdsMax = 120 * 1024;
 
 __device__ inline void tree_status(const DP& d, int code, int k) {
   if (atomicCAS(d.status, 0, code) == 0) d.status[1] = k;
@@ -65,7 +85,7 @@ __device__ __forceinline__ v4d mul_add(const v4d& at, const v4d& b, v4d acc) {
 // elsewhere.  One wavefront per block.
 __device__ __forceinline__ void tree_orig_body(const DP& d, int bx, int k) {
   __shared__ double blk[4][kTreeBlk];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = bx * 4 + wv;
   if (b >= d.tr.npool) return;
   double* s = blk[wv];
@@ -85,83 +105,146 @@ __device__ __forceinline__ void tree_orig_body(const DP& d, int bx, int k) {
   for (int r = 0; r < 4; ++r) o[64 * r + lane] = s[64 * r + lane];
 }
 
-__device__ __forceinline__ v4d pool_blk(const DP& d, const double* pool, int slot, int lane) {
-  const int b = d.tr.orig[slot];
+__device__ __forceinline__ v4d pool_blk(const double* pool, int b, int lane) {
   return b >= 0 ? load_blk(pool + (long long)b * kTreeBlk, lane) : v4d{0.0, 0.0, 0.0, 0.0};
 }
 
-// adds the children's updates to one block whose rows and columns are both
-// interface-mapped: element (row, col) of the parent (padded places row0 +
-// lane/16 + 4 r, col0 + lane%16); kK: K_IC, else G_IC; kT: the block holds
-// the transpose of the element (row, col) -> child's (col, row)
-template <bool kT>
-__device__ __forceinline__ void add_mapped(const DP& d, const TreeNode& n, const double* slab, int row0, int col0,
-                                           int lane, bool isk, v4d& acc) {
+// The children of a node and their row maps; kLds: maps staged in LDS.
+struct Kids {
+  const TreeChild* ch;
+  const short *map, *smap;  // of child a: map + a * len, smap + a * us
+  int n, len, us;
+};
+__device__ __forceinline__ Kids kids_global(const DP& d, const TreeNode& n) {
+  return Kids{d.tr.children + n.child0, d.tr.rmap + n.rmap0, d.tr.smap + n.smap0, n.nchild,
+              kTreeB * (n.nb + n.ib),   n.us};
+}
+
+// Adds the children's updates to the blocks of rows row0 .. of G_.U and K_.U
+// in control strip c.  Two children's loads are in flight together.
+__device__ __forceinline__ void add_ctrl(const Kids& kd, const double* slab, int row0, int c, int lane, v4d& g,
+                                         v4d& kk) {
   const int lm = lane & 15, lk = lane >> 4;
-  for (int a = 0; a < n.nchild; ++a) {
-    const TreeChild ch = d.tr.children[n.child0 + a];
-    const TreeNode& c = d.tr.nodes[ch.node];
-    const short* rm = d.tr.rmap + ch.rmap0;
-    const int cj = rm[col0 + lm];
-    const double* src = slab + (isk ? c.ku : c.gu);
-    const int pitch = c.ib * kTreeBlk;
+  for (int a0 = 0; a0 < kd.n; a0 += 2) {
+    v4d vg[2], vk[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ci = rm[row0 + 4 * r + lk];
-      if (ci >= 0 && cj >= 0) {
-        const int rr = kT ? cj : ci, cc = kT ? ci : cj;
-        acc[r] += src[(cc >> 4) * pitch + rr * kTreeB + (cc & 15)];
+    for (int w = 0; w < 2; ++w) {
+      const int a = min(a0 + w, kd.n - 1);
+      const int cst = a0 + w < kd.n ? kd.smap[a * kd.us + c] : -1;
+      const short* rm = kd.map + a * kd.len;
+      const int ib = kd.ch[a].ib;
+      const long long so = (long long)(ib + cst) * ib * kTreeBlk + lm;
+      const long long gu = kd.ch[a].gu + so, ku = kd.ch[a].ku + so;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ci = rm[row0 + 4 * r + lk];
+        const bool in = ci >= 0 && cst >= 0;
+        vg[w][r] = in ? slab[gu + ci * kTreeB] : 0.0;
+        vk[w][r] = in ? slab[ku + ci * kTreeB] : 0.0;
       }
     }
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        g[r] += vg[w][r];
+        kk[r] += vk[w][r];
+      }
+  }
+}
+
+// Adds the children's updates to one block whose rows and columns are both
+// interface-mapped: element (row, col) of the parent (padded places row0 +
+// 4 r + lane/16, col0 + lane%16).  kG / kK: to g from G_IC, to kk from K_IC;
+// kT: the block holds the transpose, element (row, col) taken from the
+// child's (col, row).  Two children's loads are in flight together.
+template <bool kT, bool kG, bool kK>
+__device__ __forceinline__ void add_mapped(const Kids& kd, const double* slab, int row0, int col0, int lane, v4d& g,
+                                           v4d& kk) {
+  const int lm = lane & 15, lk = lane >> 4;
+  for (int a0 = 0; a0 < kd.n; a0 += 2) {
+    v4d vg[2], vk[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const int a = min(a0 + w, kd.n - 1);
+      const short* rm = kd.map + a * kd.len;
+      const int cj = a0 + w < kd.n ? rm[col0 + lm] : -1;
+      const long long gu = kd.ch[a].gu, ku = kd.ch[a].ku;
+      const int pitch = kd.ch[a].ib * kTreeBlk;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ci = rm[row0 + 4 * r + lk];
+        const bool in = ci >= 0 && cj >= 0;
+        const int rr = kT ? cj : ci, cc = kT ? ci : cj;
+        const long long at = in ? (long long)(cc >> 4) * pitch + rr * kTreeB + (cc & 15) : 0;
+        if (kG) vg[w][r] = in ? slab[gu + at] : 0.0;
+        if (kK) vk[w][r] = in ? slab[ku + at] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (kG) g[r] += vg[w][r];
+        if (kK) kk[r] += vk[w][r];
+      }
   }
 }
 
 // ------------------------------------------------------------ pivot blocks
 // One Gauss-Jordan step of the in-place inverse of a 16 x 16 block held as
-// x[r] = element (4 r + lane/16, lane%16): pivot P.  Returns the pivot.
+// x[r] = element (4 r + lane/16, lane%16): the 2 x 2 pivot block of rows and
+// columns P and P + 1 (two rows per step, for half the dependent chains of a
+// scalar step: 44 cycles per FP64 operation).  1/det from the reciprocal
+// estimate r0 (good to about 2^-24) as r0 (1 + e + e^2), e = 1 - det r0.
+// Lanes P and P + 1 of `pivots` get the two scalar pivots.
 template <int P>
-__device__ __forceinline__ double gj_step(double (&x)[4], int lane) {
+__device__ __forceinline__ void gj_step(double (&x)[4], double& pivots, int lane) {
   constexpr int q = P & 3, rr = P >> 2;
   const int lm = lane & 15, lk = lane >> 4;
-  const double rowv = __shfl(x[rr], (q << 4) | lm);
-  const double piv = readlane_d(x[rr], (q << 4) | P);
-  const double inv = 1.0 / piv;
-  const double rp = lm == P ? inv : rowv * inv;
+  const double r0v = __shfl(x[rr], (q << 4) | lm), r1v = __shfl(x[rr], ((q + 1) << 4) | lm);
+  const double a = readlane_d(x[rr], (q << 4) | P), b = readlane_d(x[rr], (q << 4) | (P + 1));
+  const double c = readlane_d(x[rr], ((q + 1) << 4) | P), dd = readlane_d(x[rr], ((q + 1) << 4) | (P + 1));
+  const double det = fma(a, dd, -(b * c));
+  const double r0 = __builtin_amdgcn_rcp(det), e = fma(-det, r0, 1.0), t = fma(e, e, e);
+  const double u0 = lm == P ? 1.0 : lm == P + 1 ? 0.0 : r0v, u1 = lm == P ? 0.0 : lm == P + 1 ? 1.0 : r1v;
+  const double n0 = fma(dd, u0, -(b * u1)) * r0, n1 = fma(a, u1, -(c * u0)) * r0;
+  const double rp0 = fma(n0, t, n0), rp1 = fma(n1, t, n1);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const double f = row_bcast<P>(x[r]);
-    const double v = fma(-f, rp, lm == P ? 0.0 : x[r]);
-    x[r] = (r == rr && lk == q) ? rp : v;
+    const double f0 = row_bcast<P>(x[r]), f1 = row_bcast<P + 1>(x[r]);
+    const double v = fma(-f1, rp1, fma(-f0, rp0, lm == P || lm == P + 1 ? 0.0 : x[r]));
+    x[r] = r != rr ? v : lk == q ? rp0 : lk == q + 1 ? rp1 : v;
   }
-  return piv;
+  if (lm == P) pivots = a;
+  if (lm == P + 1) pivots = det / a;
 }
 
 template <int... P>
 __device__ __forceinline__ void gj_invert(double (&x)[4], double& pivots, int lane,
                                           std::integer_sequence<int, P...>) {
   auto one = [&](auto pc) {
-    constexpr int p = decltype(pc)::value;
-    const double v = gj_step<p>(x, lane);
-    if ((lane & 15) == p) pivots = v;
+    gj_step<2 * decltype(pc)::value>(x, pivots, lane);
+    __builtin_amdgcn_sched_barrier(0);
   };
   (one(std::integral_constant<int, P>{}), ...);
 }
 
 // V and Y of one strip of columns whose assembled G_JC and K_JC blocks are in
-// g and kj: block substitution with the node's block LU, then K_JJ.
-template <int NB>
-__device__ __forceinline__ void strip_solve(const TreeNode& n, const double* slab, int lane, v4d (&g)[NB],
+// g and kj: block substitution with the node's block LU (lu(r, c): block (r,
+// c) as an A operand), then K_JJ.
+template <int NB, typename F>
+__device__ __forceinline__ void strip_solve(const TreeNode& n, const double* slab, F lu, int lane, v4d (&g)[NB],
                                             v4d (&kj)[NB]) {
-  const double* lu = slab + n.lu;
 #pragma unroll
   for (int k = 1; k < NB; ++k)
 #pragma unroll
-    for (int j = 0; j < k; ++j) g[k] = mul_sub(load_blk(lu + (k * NB + j) * kTreeBlk, lane), g[j], g[k]);
+    for (int j = 0; j < k; ++j) g[k] = mul_sub(lu(k, j), g[j], g[k]);
 #pragma unroll
   for (int k = NB - 1; k >= 0; --k) {
 #pragma unroll
-    for (int j = k + 1; j < NB; ++j) g[k] = mul_sub(load_blk(lu + (k * NB + j) * kTreeBlk, lane), g[j], g[k]);
-    g[k] = mul_add(load_blk(lu + (k * NB + k) * kTreeBlk, lane), g[k], v4d{0.0, 0.0, 0.0, 0.0});
+    for (int j = k + 1; j < NB; ++j) g[k] = mul_sub(lu(k, j), g[j], g[k]);
+    g[k] = mul_add(lu(k, k), g[k], v4d{0.0, 0.0, 0.0, 0.0});
   }
   const double* kjj = slab + n.kjj;
 #pragma unroll
@@ -175,44 +258,145 @@ __device__ __forceinline__ void strip_solve(const TreeNode& n, const double* sla
 }
 
 template <int NB>
-__device__ __forceinline__ void istrip_solve(const DP& d, const TreeNode& n, double* slab, const double* pool,
-                                             int strip, int lane) {
+__device__ __forceinline__ void strip_in_place(const TreeNode& n, double* slab, const double* sa, int strip, int lane) {
   v4d g[NB], kj[NB];
-  const int v0 = n.oblk + 2 * NB * NB + n.ib * NB + strip * NB;
+  double *v = slab + n.v + strip * NB * kTreeBlk, *y = slab + n.y + strip * NB * kTreeBlk;
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
-    g[k] = pool_blk(d, pool, v0 + k, lane);
-    kj[k] = pool_blk(d, pool, v0 + n.cs * NB + k, lane);
-    add_mapped<false>(d, n, slab, k * kTreeB, (NB + strip) * kTreeB, lane, false, g[k]);
-    add_mapped<false>(d, n, slab, k * kTreeB, (NB + strip) * kTreeB, lane, true, kj[k]);
+    g[k] = load_blk(v + k * kTreeBlk, lane);
+    kj[k] = load_blk(y + k * kTreeBlk, lane);
   }
-  strip_solve<NB>(n, slab, lane, g, kj);
+  auto lu = [&](int r, int c) {
+    v4d a;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = sa[(r * kTreeB + (lane & 15)) * kTld + c * kTreeB + 4 * q + (lane >> 4)];
+    return a;
+  };
+  strip_solve<NB>(n, slab, lu, lane, g, kj);
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
-    store_blk(slab + n.v + (strip * NB + k) * kTreeBlk, g[k], lane);
-    store_blk(slab + n.y + (strip * NB + k) * kTreeBlk, kj[k], lane);
+    store_blk(v + k * kTreeBlk, g[k], lane);
+    store_blk(y + k * kTreeBlk, kj[k], lane);
   }
 }
 
-// Pivot part of one node and scenario: assembles G_JJ, K_JJ and G_IJ,
-// factorises G_JJ by 16-row blocks without pivoting (pivot blocks inverted in
-// registers by one wavefront, block products on the matrix cores), tests the
-// pivots, and solves the interface strips.
-__device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
-  __shared__ double sa[kTreeRows * kTld];
-  __shared__ double rmax[kTreeRows];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// G_JJ in sa (row pitch kTld) by one wavefront: block LU without pivoting,
+// 16 rows at a time; a pivot block is inverted in registers, the block
+// products run on the matrix cores.  The pivots go to spiv.
+__device__ __forceinline__ void front_factor(double* sa, double* spiv, int nb, int lane) {
   const int lm = lane & 15, lk = lane >> 4;
-  const TreeNode n = d.tr.nodes[node];
+  for (int p = 0; p < nb; ++p) {
+    const int p0 = p * kTreeB;
+    double x[4], pivots = 1.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = sa[(p0 + 4 * r + lk) * kTld + p0 + lm];
+    gj_invert(x, pivots, lane, std::make_integer_sequence<int, kTreeB / 2>{});
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sa[(p0 + 4 * r + lk) * kTld + p0 + lm] = x[r];
+    if (lane < kTreeB) spiv[p0 + lane] = pivots;
+    // L_jp = A_jp D_p^-1, then A_ji -= L_jp A_pi along block row j
+    for (int j = p + 1; j < nb; ++j) {
+      v4d l = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        l = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[(j * kTreeB + lm) * kTld + p0 + 4 * r + lk], x[r], l, 0, 0, 0);
+      wave_sync();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sa[(j * kTreeB + 4 * r + lk) * kTld + p0 + lm] = l[r];
+      wave_sync();
+      double la[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) la[r] = -sa[(j * kTreeB + lm) * kTld + p0 + 4 * r + lk];
+      for (int i = p + 1; i < nb; ++i) {
+        v4d acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = sa[(j * kTreeB + 4 * r + lk) * kTld + i * kTreeB + lm];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(la[r], sa[(p0 + 4 * r + lk) * kTld + i * kTreeB + lm], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sa[(j * kTreeB + 4 * r + lk) * kTld + i * kTreeB + lm] = acc[r];
+      }
+    }
+    wave_sync();
+  }
+}
+
+// G_I. and K_I. of one strip and interface block row m, from the children and
+// the strip's V and Y (all in the slab)
+__device__ __forceinline__ void update_block(const TreeNode& n, const Kids& kd, double* slab, int strip, int m,
+                                             int lane) {
   const int nb = n.nb;
+  v4d ga = {0.0, 0.0, 0.0, 0.0}, ka = {0.0, 0.0, 0.0, 0.0};
+  const int row0 = (nb + m) * kTreeB;
+  if (strip >= n.ib) add_ctrl(kd, slab, row0, strip - n.ib, lane, ga, ka);
+  else add_mapped<false, true, true>(kd, slab, row0, (nb + strip) * kTreeB, lane, ga, ka);
+  const double *gt = slab + n.gijt + (long long)m * nb * kTreeBlk, *vm = slab + n.v + (long long)m * nb * kTreeBlk,
+               *ym = slab + n.y + (long long)m * nb * kTreeBlk, *vs = slab + n.v + (long long)strip * nb * kTreeBlk,
+               *ys = slab + n.y + (long long)strip * nb * kTreeBlk;
+  for (int p = 0; p < nb; ++p) {
+    const int o = p * kTreeBlk;
+    const v4d v = load_blk(vs + o, lane), y = load_blk(ys + o, lane);
+    ga = mul_sub(load_blk(gt + o, lane), v, ga);
+    ka = mul_sub(load_blk(vm + o, lane), y, ka);
+    ka = mul_sub(load_blk(ym + o, lane), v, ka);
+  }
+  const long long o = ((long long)strip * n.ib + m) * kTreeBlk;
+  store_blk(slab + n.gu + o, ga, lane);
+  store_blk(slab + n.ku + o, ka, lane);
+}
+
+// Pivot part of one node and scenario.  The children's maps go to LDS first
+// (with them in global memory every child cost each block a chain of
+// dependent loads: 41 against 26 us per level at 300 buses, 69 against 31 at
+// 1354).  All wavefronts assemble G_JJ and K_JJ; then wavefront 0 factorises
+// G_JJ while the others assemble G_IJ and the strips, whose V and Y follow:
+// the interface strips only, or, for levels of narrow nodes (kAll), every
+// strip and the updates for the parent too, which saves tree_cols_body's
+// launch.  Bound by latency: at the upper levels one workgroup per scenario
+// runs.
+template <bool kMapLds, bool kAll>
+__device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
+  extern __shared__ double fsm[];
+  __shared__ double rmax[kTreeRows], spiv[kTreeRows];
+  __shared__ TreeChild sch[kFrontKids];
+  constexpr int kW = kTF / 64;
+  double* sa = fsm;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lm = lane & 15, lk = lane >> 4;
+  const TreeNode& n = d.tr.nodes[node];
+  const int nb = n.nb, ib = n.ib, nbb = nb * nb, nstrip = kAll ? n.cs : ib;
   double* slab = d.tr.slab + (long long)k * d.tr.stride;
   const double* pool = d.tr.pool + (long long)k * d.tr.npool * kTreeBlk;
-  // G_JJ into LDS, K_JJ and G_IJ^T into the slab
-  for (int b = wv; b < nb * nb; b += 4) {
+  // index data into LDS: the pool blocks (G_JJ, K_JJ, G_IJ, the strips of V,
+  // those of Y), the children and their maps
+  int* so = reinterpret_cast<int*>(fsm + kTreeRows * kTld);
+  const int nfix = 2 * nbb + ib * nb, nst = nstrip * nb;
+  for (int t = tid; t < nfix + 2 * nst; t += kTF)
+    so[t] = d.tr.orig[n.oblk + (t < nfix + nst ? t : t - nst + n.cs * nb)];
+  Kids kd = kids_global(d, n);
+  if (kMapLds) {
+    int* sm = so + nfix + 2 * nst;
+    const int* src = reinterpret_cast<const int*>(kd.map);
+    const int words = n.nchild * kd.len / 2;
+    for (int t = tid; t < words; t += kTF) sm[t] = src[t];
+    kd.map = reinterpret_cast<const short*>(sm);
+    if (kAll) {
+      short* ss = reinterpret_cast<short*>(sm + words);
+      for (int t = tid; t < n.nchild * n.us; t += kTF) ss[t] = kd.smap[t];
+      kd.smap = ss;
+    }
+    if (n.nchild <= kFrontKids) {
+      if (tid < n.nchild) sch[tid] = kd.ch[tid];
+      kd.ch = sch;
+    }
+  }
+  __syncthreads();
+  // G_JJ into LDS, K_JJ into the slab
+  for (int b = wv; b < nbb; b += kW) {
     const int rb = b / nb, cb = b % nb;
-    v4d g = pool_blk(d, pool, n.oblk + b, lane), kk = pool_blk(d, pool, n.oblk + nb * nb + b, lane);
-    add_mapped<false>(d, n, slab, rb * kTreeB, cb * kTreeB, lane, false, g);
-    add_mapped<false>(d, n, slab, rb * kTreeB, cb * kTreeB, lane, true, kk);
+    v4d g = pool_blk(pool, so[b], lane), kk = pool_blk(pool, so[nbb + b], lane);
+    add_mapped<false, true, true>(kd, slab, rb * kTreeB, cb * kTreeB, lane, g, kk);
     store_blk(slab + n.kjj + b * kTreeBlk, kk, lane);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -220,79 +404,58 @@ __device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
       sa[row * kTld + col] = row >= n.s ? (row == col ? 1.0 : 0.0) : g[r];
     }
   }
-  for (int b = wv; b < n.ib * nb; b += 4) {
-    const int ist = b / nb, kb = b % nb;
-    v4d g = pool_blk(d, pool, n.oblk + 2 * nb * nb + b, lane);
-    add_mapped<true>(d, n, slab, kb * kTreeB, (nb + ist) * kTreeB, lane, false, g);
-    store_blk(slab + n.gijt + b * kTreeBlk, g, lane);
-  }
-  // largest |entry| of every pivot row of G_x, for the pivot test
-  if (tid < n.s) {
-    const int row = d.tr.rows[n.row0 + tid];
-    const double* gv = d.EV + (long long)k * d.n_ev + d.off_gx;
-    double mx = 0.0;
-    const int e1 = d.gx_ptr[row + 1];
-    for (int e = d.gx_ptr[row]; e < e1; ++e) mx = fmax(mx, fabs(gv[e]));
-    rmax[tid] = mx;
-  }
   __syncthreads();
-  for (int p = 0; p < nb; ++p) {
-    const int p0 = p * kTreeB;
-    if (wv == 0) {
-      double x[4], pivots = 1.0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) x[r] = sa[(p0 + 4 * r + lk) * kTld + p0 + lm];
-      gj_invert(x, pivots, lane, std::make_integer_sequence<int, kTreeB>{});
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sa[(p0 + 4 * r + lk) * kTld + p0 + lm] = x[r];
-      if (lane < kTreeB && p0 + lane < n.s) {
-        const double a = fabs(pivots);
-        if (!(a > 0.0 && a >= 1e-10 * rmax[p0 + lane]) || !isfinite(pivots)) tree_status(d, RKKT_ERR_SINGULAR_GX, k);
+  if (wv == 0) {
+    front_factor(sa, spiv, nb, lane);
+  } else {
+    // G_IJ^T, then G_J. and K_J. of the strips (in the places of V and Y)
+    for (int b = wv - 1; b < ib * nb + nst; b += kW - 1) {
+      v4d g = pool_blk(pool, so[2 * nbb + b], lane), kk = {0.0, 0.0, 0.0, 0.0};
+      if (b < ib * nb) {
+        const int ist = b / nb, kb = b % nb;
+        add_mapped<true, true, false>(kd, slab, kb * kTreeB, (nb + ist) * kTreeB, lane, g, kk);
+        store_blk(slab + n.gijt + b * kTreeBlk, g, lane);
+      } else {
+        const int q = b - ib * nb, ist = q / nb, kb = q % nb;
+        kk = pool_blk(pool, so[nfix + nst + q], lane);
+        if (kAll && ist >= ib) add_ctrl(kd, slab, kb * kTreeB, ist - ib, lane, g, kk);
+        else add_mapped<false, true, true>(kd, slab, kb * kTreeB, (nb + ist) * kTreeB, lane, g, kk);
+        store_blk(slab + n.v + q * kTreeBlk, g, lane);
+        store_blk(slab + n.y + q * kTreeBlk, kk, lane);
       }
     }
-    __syncthreads();
-    // L_jp = A_jp D_p^-1
-    for (int j = p + 1 + wv; j < nb; j += 4) {
-      v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sa[(j * kTreeB + lm) * kTld + p0 + 4 * r + lk],
-                                                   sa[(p0 + 4 * r + lk) * kTld + p0 + lm], acc, 0, 0, 0);
-      wave_sync();
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sa[(j * kTreeB + 4 * r + lk) * kTld + p0 + lm] = acc[r];
+    // largest |entry| of every pivot row of G_x, for the pivot test
+    if (wv == kW - 1 && lane < n.s) {
+      const int row = d.tr.rows[n.row0 + lane];
+      const double* gv = d.EV + (long long)k * d.n_ev + d.off_gx;
+      double mx = 0.0;
+      const int e1 = d.gx_ptr[row + 1];
+      for (int e = d.gx_ptr[row]; e < e1; ++e) mx = fmax(mx, fabs(gv[e]));
+      rmax[lane] = mx;
     }
-    __syncthreads();
-    // A_ij -= L_ip A_pj
-    const int m = nb - 1 - p;
-    for (int t = wv; t < m * m; t += 4) {
-      const int i0 = (p + 1 + t / m) * kTreeB, j0 = (p + 1 + t % m) * kTreeB;
-      v4d acc;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] = sa[(i0 + 4 * r + lk) * kTld + j0 + lm];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-sa[(i0 + lm) * kTld + p0 + 4 * r + lk],
-                                                   sa[(p0 + 4 * r + lk) * kTld + j0 + lm], acc, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sa[(i0 + 4 * r + lk) * kTld + j0 + lm] = acc[r];
-    }
-    __syncthreads();
   }
-  for (int b = wv; b < nb * nb; b += 4) {
+  __syncthreads();
+  if (tid < n.s) {
+    const double a = fabs(spiv[tid]);
+    if (!(a > 0.0 && a >= 1e-10 * rmax[tid]) || !isfinite(a)) tree_status(d, RKKT_ERR_SINGULAR_GX, k);
+  }
+  for (int b = wv; b < nbb; b += kW) {
     const int r0 = b / nb * kTreeB, c0 = b % nb * kTreeB;
     double* o = slab + n.lu + b * kTreeBlk;
 #pragma unroll
     for (int r = 0; r < 4; ++r) o[64 * r + lane] = sa[(r0 + lm) * kTld + c0 + 4 * r + lk];
   }
-  __syncthreads();
-  for (int st = wv; st < n.ib; st += 4) {
+  for (int st = wv; st < nstrip; st += kW) {
     switch (nb) {
-      case 1: istrip_solve<1>(d, n, slab, pool, st, lane); break;
-      case 2: istrip_solve<2>(d, n, slab, pool, st, lane); break;
-      case 3: istrip_solve<3>(d, n, slab, pool, st, lane); break;
-      default: istrip_solve<4>(d, n, slab, pool, st, lane); break;
+      case 1: strip_in_place<1>(n, slab, sa, st, lane); break;
+      case 2: strip_in_place<2>(n, slab, sa, st, lane); break;
+      case 3: strip_in_place<3>(n, slab, sa, st, lane); break;
+      default: strip_in_place<4>(n, slab, sa, st, lane); break;
     }
+  }
+  if (kAll) {
+    __syncthreads();
+    for (int t = wv; t < n.cs * ib; t += kW) update_block(n, kd, slab, t / ib, t % ib, lane);
   }
 }
 
@@ -303,36 +466,21 @@ __device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
 template <int NB>
 __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, double* slab, const double* pool,
                                            int strip, int lane) {
-  const int lm = lane & 15, lk = lane >> 4;
   v4d g[NB], kj[NB];
+  const Kids kd = kids_global(d, n);
   const bool ctrl = strip >= n.ib;
   if (ctrl) {
     const int v0 = n.oblk + 2 * NB * NB + n.ib * NB + strip * NB;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-      g[k] = pool_blk(d, pool, v0 + k, lane);
-      kj[k] = pool_blk(d, pool, v0 + n.cs * NB + k, lane);
+      g[k] = pool_blk(pool, d.tr.orig[v0 + k], lane);
+      kj[k] = pool_blk(pool, d.tr.orig[v0 + n.cs * NB + k], lane);
     }
-    for (int a = 0; a < n.nchild; ++a) {
-      const TreeChild ch = d.tr.children[n.child0 + a];
-      const int cst = d.tr.smap[ch.smap0 + strip - n.ib];
-      if (cst < 0) continue;
-      const TreeNode& c = d.tr.nodes[ch.node];
-      const long long so = (long long)(c.ib + cst) * c.ib * kTreeBlk;
-      const double *gu = slab + c.gu + so, *ku = slab + c.ku + so;
-      const short* rm = d.tr.rmap + ch.rmap0;
 #pragma unroll
-      for (int k = 0; k < NB; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ci = rm[k * kTreeB + 4 * r + lk];
-          if (ci >= 0) {
-            g[k][r] += gu[ci * kTreeB + lm];
-            kj[k][r] += ku[ci * kTreeB + lm];
-          }
-        }
-    }
-    strip_solve<NB>(n, slab, lane, g, kj);
+    for (int k = 0; k < NB; ++k) add_ctrl(kd, slab, k * kTreeB, strip - n.ib, lane, g[k], kj[k]);
+    const double* lu = slab + n.lu;
+    strip_solve<NB>(
+        n, slab, [&](int r, int c) { return load_blk(lu + (r * NB + c) * kTreeBlk, lane); }, lane, g, kj);
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       store_blk(slab + n.v + (strip * NB + k) * kTreeBlk, g[k], lane);
@@ -348,28 +496,8 @@ __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, doubl
   for (int m = 0; m < n.ib; ++m) {
     v4d ga = {0.0, 0.0, 0.0, 0.0}, ka = {0.0, 0.0, 0.0, 0.0};
     const int row0 = (NB + m) * kTreeB;
-    if (ctrl) {
-      for (int a = 0; a < n.nchild; ++a) {
-        const TreeChild ch = d.tr.children[n.child0 + a];
-        const int cst = d.tr.smap[ch.smap0 + strip - n.ib];
-        if (cst < 0) continue;
-        const TreeNode& c = d.tr.nodes[ch.node];
-        const long long so = (long long)(c.ib + cst) * c.ib * kTreeBlk;
-        const double *gu = slab + c.gu + so, *ku = slab + c.ku + so;
-        const short* rm = d.tr.rmap + ch.rmap0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ci = rm[row0 + 4 * r + lk];
-          if (ci >= 0) {
-            ga[r] += gu[ci * kTreeB + lm];
-            ka[r] += ku[ci * kTreeB + lm];
-          }
-        }
-      }
-    } else {
-      add_mapped<false>(d, n, slab, row0, (NB + strip) * kTreeB, lane, false, ga);
-      add_mapped<false>(d, n, slab, row0, (NB + strip) * kTreeB, lane, true, ka);
-    }
+    if (ctrl) add_ctrl(kd, slab, row0, strip - n.ib, lane, ga, ka);
+    else add_mapped<false, true, true>(kd, slab, row0, (NB + strip) * kTreeB, lane, ga, ka);
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const long long at = (long long)(m * NB + k) * kTreeBlk;
@@ -384,7 +512,7 @@ __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, doubl
 }
 
 __device__ __forceinline__ void tree_cols_body(const DP& d, int job, int k) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TreeNode n = d.tr.nodes[d.tr.jobs[2 * job]];
   const int strip = d.tr.jobs[2 * job + 1] + wv;
   if (strip >= n.cs) return;
@@ -405,7 +533,7 @@ __device__ __forceinline__ void tree_cols_body(const DP& d, int job, int k) {
 // instruction's own layout.
 template <int T>
 __device__ __forceinline__ void tree_product_body(const DP& d, int bx, int part) {
-  const int lane = threadIdx.x & 63, q = bx * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, q = bx * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (q >= d.tr.npair) return;
   const int a = d.tr.pair_g[2 * q], b = d.tr.pair_g[2 * q + 1];
   v4d acc[T][T];
@@ -665,7 +793,7 @@ __device__ __forceinline__ void up_pivot(const DP& d, const TreeNode& n, int k, 
 // every gx-th node of a level (gx > 1 for one level only).
 __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k, int l0, int l1) {
   __shared__ double sb[kTreeStepWaves][2 * 64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lk = lane >> 4;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
   double* vec = d.tr.vec + (long long)k * d.tr.vstride;
@@ -725,7 +853,7 @@ __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k,
 // rpart of one control strip: the nodes that hold it, dealt to the wavefronts
 __device__ __forceinline__ void tree_rhs_u_body(const DP& d, int z, int k) {
   __shared__ double red[4][kTreeB];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lk = lane >> 4;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
   const double* vec = d.tr.vec + (long long)k * d.tr.vstride;
@@ -787,7 +915,7 @@ __device__ __forceinline__ void rec_u(const DP& d, const TreeNode& n, int c0, in
 
 __device__ __forceinline__ void tree_rec_u_body(const DP& d, int job, int k, const double* pu) {
   __shared__ double red[4][2][kTreeRows];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const TreeNode n = d.tr.nodes[d.tr.cjobs[2 * job]];
   const int c0 = d.tr.cjobs[2 * job + 1];
   switch (n.nb) {
@@ -849,7 +977,7 @@ __device__ __forceinline__ void down_pivot(const DP& d, const TreeNode& n, int k
 __device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int k, int l0, int l1, double* px,
                                                double* py) {
   __shared__ double sb[kTreeStepWaves][80];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
   double* vec = d.tr.vec + (long long)k * d.tr.vstride;
@@ -948,8 +1076,9 @@ __device__ __forceinline__ void tree_hp_body(const DP& d, int bx, int k, const d
 }
 
 __global__ __launch_bounds__(kTT) void k_tree_orig(DP d) { tree_orig_body(d, blockIdx.x, blockIdx.y); }
-__global__ __launch_bounds__(kTT) void k_tree_front(DP d, int first) {
-  tree_front_body(d, d.tr.lev_nodes[first + blockIdx.x], blockIdx.y);
+template <bool kMapLds, bool kAll>
+__global__ __launch_bounds__(kTF) void k_tree_front(DP d, int first) {
+  tree_front_body<kMapLds, kAll>(d, d.tr.lev_nodes[first + blockIdx.x], blockIdx.y);
 }
 __global__ __launch_bounds__(kTT) void k_tree_cols(DP d, int first) { tree_cols_body(d, first + blockIdx.x, blockIdx.y); }
 template <int T>
@@ -991,9 +1120,10 @@ __global__ __launch_bounds__(kTT) void k_tree_orig_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
   tree_orig_body(d, mb.bx, mb.by);
 }
-__global__ __launch_bounds__(kTT) void k_tree_front_m(RKKT_MULTI_ARGS, int level) {
+template <bool kMapLds>
+__global__ __launch_bounds__(kTF) void k_tree_front_m(RKKT_MULTI_ARGS, int level) {
   RKKT_MULTI_PROLOGUE
-  tree_front_body(d, d.tr.lev_nodes[d.tr.lev_ptr[level] + mb.bx], mb.by);
+  tree_front_body<kMapLds, false>(d, d.tr.lev_nodes[d.tr.lev_ptr[level] + mb.bx], mb.by);
 }
 __global__ __launch_bounds__(kTT) void k_tree_cols_m(RKKT_MULTI_ARGS, int level) {
   RKKT_MULTI_PROLOGUE
@@ -1047,7 +1177,14 @@ void launch_tree_reduce(const DP& d, hipStream_t s) {
   k_tree_orig<<<dim3(cdiv(t.npool, 4), d.N), kTT, 0, s>>>(d);
   const int nlev = (int)t.lev_ptr.size() - 1;
   for (int l = 0; l < nlev; ++l) {
-    k_tree_front<<<dim3(t.lev_ptr[l + 1] - t.lev_ptr[l], d.N), kTT, 0, s>>>(d, t.lev_ptr[l]);
+    const dim3 grid(t.lev_ptr[l + 1] - t.lev_ptr[l], d.N);
+    const size_t lds = front_lds(t, l);
+    const int v = front_variant(t, l);
+    if (v == 3) k_tree_front<true, true><<<grid, kTF, lds, s>>>(d, t.lev_ptr[l]);
+    else if (v == 2) k_tree_front<false, true><<<grid, kTF, lds, s>>>(d, t.lev_ptr[l]);
+    else if (v == 1) k_tree_front<true, false><<<grid, kTF, lds, s>>>(d, t.lev_ptr[l]);
+    else k_tree_front<false, false><<<grid, kTF, lds, s>>>(d, t.lev_ptr[l]);
+    if (v & 2) continue;
     const int nj = t.job_ptr[l + 1] - t.job_ptr[l];
     if (nj > 0) k_tree_cols<<<dim3(nj, d.N), kTT, 0, s>>>(d, t.job_ptr[l]);
   }
@@ -1094,7 +1231,11 @@ void launches_tree(const DP& d, std::vector<Launch>& out) {
   out.push_back(Launch{R, kKTreeOrig, 0, (int)cdiv(t.npool, 4), d.N, kTT, 0, 0});
   const int nlev = (int)t.lev_ptr.size() - 1;
   for (int l = 0; l < nlev; ++l) {
-    out.push_back(Launch{R + 1 + 2 * l, kKTreeFront, 0, t.lev_ptr[l + 1] - t.lev_ptr[l], d.N, kTT, l, 0});
+    // never fused: an instance fused at a level where another is not would
+    // make two launches of the level, one after the other (16 grids 2.88
+    // against 3.05 ms per pass)
+    out.push_back(Launch{R + 1 + 2 * l, kKTreeFront, front_variant(t, l) & 1, t.lev_ptr[l + 1] - t.lev_ptr[l], d.N,
+                         kTF, l, (long long)front_lds(t, l)});
     const int nj = t.job_ptr[l + 1] - t.job_ptr[l];
     if (nj > 0) out.push_back(Launch{R + 2 + 2 * l, kKTreeCols, 0, nj, d.N, kTT, l, 0});
   }
@@ -1118,13 +1259,37 @@ void launches_tree(const DP& d, std::vector<Launch>& out) {
   out.push_back(Launch{B + 2048, kKTreeHp, 0, (int)cdiv(d.m, kTT), d.N, kTT, 0, 0});
 }
 
-hipError_t multi_tree(const Launch& l, unsigned nblk, const DP* dps, const rkkt_iteration* its, const MultiBlk* blk,
+bool tree_fits(const Tree& t) {
+  for (size_t l = 0; l + 1 < t.lev_ptr.size(); ++l)
+    if (front_lds(t, (int)l) > (size_t)kFrontLdsMax) return false;
+  return true;
+}
+
+hipError_t configure_tree_kernels() {
+  // the pivot kernel's LDS never passes 64 KiB + 1 KiB of statics by more
+  // than the row maps it accepts
+  static bool done = false;
+  if (done) return hipSuccess;
+  const int need = kFrontLdsMax;
+  hipError_t e = hipSuccess;
+  for (const void* fn : {(const void*)k_tree_front<true, true>, (const void*)k_tree_front<false, true>,
+                         (const void*)k_tree_front<true, false>, (const void*)k_tree_front<false, false>,
+                         (const void*)k_tree_front_m<true>, (const void*)k_tree_front_m<false>})
+    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, need);
+  done = e == hipSuccess;
+  return e;
+}
+
+hipError_t multi_tree(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its, const MultiBlk* blk,
                       hipStream_t s, bool prepare, bool* handled) {
   *handled = l.kernel >= kKTreeOrig && l.kernel <= kKTreeKuu;
   if (!*handled || prepare) return hipSuccess;
   switch (l.kernel) {
     case kKTreeOrig: k_tree_orig_m<<<nblk, kTT, 0, s>>>(dps, its, blk); break;
-    case kKTreeFront: k_tree_front_m<<<nblk, kTT, 0, s>>>(dps, its, blk, l.jb); break;
+    case kKTreeFront:
+      if (l.variant == 1) k_tree_front_m<true><<<nblk, kTF, (size_t)lds, s>>>(dps, its, blk, l.jb);
+      else k_tree_front_m<false><<<nblk, kTF, (size_t)lds, s>>>(dps, its, blk, l.jb);
+      break;
     case kKTreeCols: k_tree_cols_m<<<nblk, kTT, 0, s>>>(dps, its, blk, l.jb); break;
     case kKTreeProduct:
       if (l.variant) k_tree_product_m<4><<<nblk, kTT, 0, s>>>(dps, its, blk);

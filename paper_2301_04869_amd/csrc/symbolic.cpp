@@ -364,7 +364,8 @@ LdsSizes lds_sizes(const Sym& s, int w, int variant, int spw) {
   return z;
 }
 
-std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* opt, Sym& s, bool for_device) {
+std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* opt, Sym& s, bool for_device,
+                           bool allow_tree) {
   const int col_tile_req = opt ? opt->col_tile : 0, variant_req = opt ? opt->variant : 0;
   const int spw_req = opt ? opt->scen_per_group : 0, chain_req = opt ? opt->chain_rows : 0;
   if (spw_req != 0 && spw_req != 1 && spw_req != 2 && spw_req != 4) return "scen_per_group must be 0, 1, 2 or 4";
@@ -843,7 +844,7 @@ std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* o
   // passes, panels in device memory against the tree: 9241 buses x 16
   // scenarios 114.6 / 28.3 ms, 2869 x 8 11.1 / 5.9, 1354 x 8 3.70 / 2.47; at
   // 300 x 16 (0.85 / 0.85), where the panels begin to leave the chip, equal
-  s.tree = s.variant == 1 && !s.lds_reduce && s.col_tile == std::min(64, nu) && s.sweep_form == 2;
+  s.tree = allow_tree && s.variant == 1 && !s.lds_reduce && s.col_tile == std::min(64, nu) && s.sweep_form == 2;
   // stacked panels of the product variant: rows (x rows then u rows) of every
   // scenario, columns padded to a multiple of 64 (the reduction's widest tile)
   s.nu_pad = (nu + 63) / 64 * 64;

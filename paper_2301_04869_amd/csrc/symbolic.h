@@ -121,8 +121,9 @@ struct Sym {
 
 // Returns an empty string on success, else the error message.  for_device:
 // leaves out the level-sliced schedules where no kernel follows them (tree).
+// allow_tree: false keeps the panels in device memory.
 std::string build_symbolic(const rkkt_network& net, int n_scen, const rkkt_options* opt, Sym& s,
-                           bool for_device = false);
+                           bool for_device = false, bool allow_tree = true);
 
 // sizes fixing the LDS layouts, for a tile width
 LdsSizes lds_sizes(const Sym& s, int w, int variant, int spw);

@@ -230,7 +230,7 @@ std::string build_tree(const Sym& s, Tree& t) {
     for (int u : own[q]) hit[t.upos[u] / kTreeB] = 1;
     for (int c0 : kids[post[q]]) {
       const int c = where[c0];
-      t.children.push_back({c, 0, 0});
+      t.children.push_back({c, 0, 0, t.nodes[c].ib, t.nodes[c].nb, t.nodes[c].vec, t.nodes[c].gu, t.nodes[c].ku});
       n.level = std::max(n.level, t.nodes[c].level + 1);
       for (int z : strips[c]) hit[z] = 1;
     }
@@ -272,7 +272,9 @@ std::string build_tree(const Sym& s, Tree& t) {
     return f != e && *f == r ? n.nb * kTreeB + (int)(f - b) : -1;
   };
   for (int q = 0; q < nn; ++q) {
-    const TreeNode& n = t.nodes[q];
+    TreeNode& n = t.nodes[q];
+    n.rmap0 = (int)t.rmap.size();
+    n.smap0 = (int)t.smap.size();
     for (int a = 0; a < n.nchild; ++a) {
       TreeChild& ch = t.children[n.child0 + a];
       const TreeNode& c = t.nodes[ch.node];
@@ -357,8 +359,15 @@ std::string build_tree(const Sym& s, Tree& t) {
   for (int l = 0; l < nlev; ++l) {
     t.lev_ptr.push_back((int)t.lev_nodes.size());
     t.job_ptr.push_back((int)t.jobs.size() / 2);
+    t.lev_map.push_back(0);
+    t.lev_cs.push_back(0);
+    t.lev_ib.push_back(0);
     for (int q = 0; q < nn; ++q)
       if (t.nodes[q].level == l) {
+        const TreeNode& n = t.nodes[q];
+        t.lev_map[l] = std::max(t.lev_map[l], n.nchild * (kTreeB * (n.nb + n.ib) + n.us));
+        t.lev_cs[l] = std::max(t.lev_cs[l], n.cs);
+        t.lev_ib[l] = std::max(t.lev_ib[l], n.ib);
         t.lev_nodes.push_back(q);
         for (int c = 0; c < t.nodes[q].cs; c += 4) {
           t.jobs.push_back(q);

@@ -41,6 +41,7 @@ struct TreeNode {
   int level, parent;
   int row0;        // rows[row0 ..]: internal row of every pivot row, then of every interface row
   int child0, nchild;
+  int rmap0, smap0;  // maps of the first child (the others' follow)
   int strip0;      // strips[strip0 .. + us]: global strip of every control strip
   int vec;         // offset in the scenario's step vectors: V_b, Y_b (16 nb each), then the updates
                    // of r3 and r1 in the interface rows (16 ib each)
@@ -52,9 +53,12 @@ struct TreeNode {
 // A child as its parent sees it: rmap[rmap0 + r] is the child's interface
 // index of the parent's padded row r (pivot block rows, then interface block
 // rows) or -1; smap[smap0 + t] the child's control strip of the parent's
-// control strip t or -1.
+// control strip t or -1.  The children of a node have their maps one after the
+// other.  ib, nb, vec, gu, ku: the child's own.
 struct TreeChild {
   int node, rmap0, smap0;
+  int ib, nb, vec;
+  long long gu, ku;
 };
 
 struct Tree {
@@ -68,6 +72,8 @@ struct Tree {
   // place in the block and the source, >= 0 in EV, ~source in K
   std::vector<int> orig, optr, oent;
   int npool = 0;
+  std::vector<int> lev_map;         // most shorts of row and strip maps of a node, per level
+  std::vector<int> lev_cs, lev_ib;  // most strips and interface strips of a node, per level
   // nodes of every level; strip jobs of every level (node, first strip), four
   // strips each, interface strips first
   std::vector<int> lev_ptr, lev_nodes, job_ptr, jobs;
@@ -87,6 +93,10 @@ struct Tree {
   int T = 0, ngroup = 0, parts = 1;
   std::vector<int> pair_g, pair_ptr, pair_nodes, gstrip;
 };
+
+// The pivot kernel keeps the maps of a node's children in LDS up to this many
+// shorts.
+constexpr int kTreeMapLds = 16384;
 
 // Builds the tree from the filled pattern; empty string on success.
 std::string build_tree(const Sym& s, Tree& t);
