@@ -433,6 +433,9 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
     if ((e = dalloc(p, &d.wbuf, d.lds_stp || d.tree ? 1 : N * (size_t)s.m)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.rpart, N * s.nu)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.qbuf, N * s.nx)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.cw, (size_t)((s.nu + 63) / 64) * 4096)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.rinv, (size_t)((s.nu + 63) / 64) * 4096)) != hipSuccess) goto hip_error;
+    if ((e = dalloc(p, &d.ry, s.nu)) != hipSuccess) goto hip_error;
     if ((e = dalloc(p, &d.status, 2)) != hipSuccess) goto hip_error;
     if (d.tree && (e = rkkt::configure_tree_kernels()) != hipSuccess) goto hip_error;
     if ((e = rkkt::configure_lu_kernels(d)) != hipSuccess) goto hip_error;

@@ -105,6 +105,8 @@ struct DP {
   double *rhat1;   // [N][nx] internal order
   double *wbuf;    // [N][m] step work vector (global-memory step kernels)
   double *rpart;   // [N][nu]
+  double *cw;      // factorised diagonal tiles of the blocked Cholesky (n_u > 128), 4096 per 64 columns
+  double *rinv, *ry;  // reduced solve beyond n_u = 128: inverses of the factor's diagonal tiles, right-hand side
   double *qbuf;    // [N][nx] internal order: G_x^-1 r3 of the last step right-hand side
   int *status;     // [2]: code, scenario
   int tree;        // the reduction runs on the elimination tree (k_tree.hip)
@@ -192,7 +194,6 @@ __device__ __forceinline__ void wave_sync() {
 // dynamic LDS limits of the kernels for this problem's sizes; called by rkkt_create
 hipError_t configure_lu_kernels(const DP& d);
 hipError_t configure_dense_kernels(const DP& d);
-void launch_copy(const double* a, double* b, long long n, hipStream_t s);
 
 // launchers (k_eval.hip)
 void launch_bus_loads(const DP& d, const double* pd, const double* qd, hipStream_t s);
@@ -241,8 +242,8 @@ void launch_reduced_solve(const DP& d, const double* r1u, const double* chol, do
 // ---- several independent instances, one launch per kernel configuration
 // (rkkt_multi_*).  A Launch is one kernel launch of an instance's pass as its
 // single-instance launcher issues it: kernel, template variant, grid gx x gy,
-// block threads, dynamic LDS bytes, and for the blocked Cholesky the panel's
-// first column jb.  key orders the launches of a pass (stage * 4096 + place
+// block threads, dynamic LDS bytes, and jb: the blocked Cholesky's panel, the
+// tree's level.  key orders the launches of a pass (stage * 4096 + place
 // in the stage), so launches of equal key, kernel, variant and threads from
 // several instances become one launch whose blocks map back through MultiBlk.
 struct Launch {
@@ -255,8 +256,8 @@ struct MultiBlk {
 enum : int {
   kKLineEvalGather = 1, kKLineEval, kKGatherEv, kKAssemble, kKLineHess, kKWGather, kKCondense,
   kKRefactor, kKReduce64, kKReduce, kKStepRhs2, kKStepRhs, kKStepRec2, kKStepRec,
-  kKStacked, kKSymSum, kKCholSmall, kKCopyChol, kKSetInfo, kKCholDiag, kKCholTrsm, kKCholUpdate,
-  kKRSolveBlk, kKRSolve, kKCondenseLds,
+  kKStacked, kKSymSum, kKCholSmall, kKCholFirst, kKCholStep,
+  kKRSolveBlk, kKRSolvePrep, kKRSolvePanel, kKRSolveUpdate, kKCondenseLds,
   kKTreeOrig, kKTreeFront, kKTreeCols, kKTreeProduct, kKTreeSum,
   kKTreeResid, kKTreeUp, kKTreeRhsU, kKTreeRecU, kKTreeDown, kKTreeHp, kKTreeKuu
 };

@@ -2,6 +2,7 @@
 // paper's MPI all-reduce of K_hat, here a fixed-order on-device sum), the
 // Cholesky factorisation of K_hat (the paper factorises it densely with
 // LAPACK on the GPU) and the two triangular solves for p_u.
+#include <algorithm>
 #include <utility>
 
 #include "device.h"
@@ -13,9 +14,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kNB = 64;          // panel width of the blocked factorisation
 constexpr int kSmallN = 128;     // whole matrix (padded to a multiple of 16) in LDS up to this order
-constexpr int kWavesD = kThreads / 64;
-
-__global__ void k_set_int(int* p, int v) { *p = v; }
 
 // K_hat = sum_c src_c + diag(sigma_u) + delta_w I over `cnt` n_u x n_u
 // matrices (the scenario contributions, or the chunk partials of the stacked
@@ -312,122 +310,7 @@ __device__ __forceinline__ double rcp_nr(double d) {
   return fma(r, fma(-d, r, 1.0), r);
 }
 
-// Right-looking blocked Cholesky of the lower triangle of an n x n block held
-// in LDS (row-major, leading dimension ld), n a multiple of kPB (callers pad
-// with identity rows and columns) and n <= 64 kR, by a workgroup of 64 kWaves
-// threads.  Panels of kPB columns: wavefront 0 factorises the panel in
-// registers (lane l holds rows jb + l + 64 t; the diagonal row jb + p is in
-// lane p).  Inside the panel the elimination runs in the square-root-free
-// form A = W D^-1 W^T (column p of W is the updated column p of A, D its
-// diagonal): for column p one vector multiply forms every multiplier
-// w_qp / d_p in lane q, and readlane broadcasts each to the rows, so the
-// chain from one column to the next holds one reciprocal.  The panel's
-// columns are then scaled to L = W D^-1/2 together, and its pivots checked
-// once.  The inverse of each 16 x 16 diagonal block of L is formed on the way
-// and left, transposed, in the block's strict upper triangle (its diagonal is
-// 1 / L_aa).  The trailing lower triangle is updated in 16 x 16 tiles on the FP64
-// matrix cores (v_mfma_f64_16x16x4f64: A operand lane holds row lane%16,
-// k = lane/16; B operand k = lane/16, column lane%16; result register r of a
-// lane is row lane/16 + 4 r, column lane%16).
-// Returns 0 or the 1-based first column whose pivot is not positive.
 constexpr int kPB = 16;
-
-// identity rows n .. np - 1 (columns 0 .. np - 1) below an n x n block in LDS
-__device__ __forceinline__ void pad_identity(double* sa, int ld, int n, int np, int t0, int ts) {
-  const int cnt = (np - n) * np;
-  for (int t = t0; t < cnt; t += ts) {
-    const int r = n + t / np, c = t % np;
-    sa[r * ld + c] = r == c ? 1.0 : 0.0;
-  }
-}
-
-template <int kWaves, int kR>
-__device__ int chol_blocked_lds(double* sa, int n, int ld, int* sflag) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (tid == 0) *sflag = 0;
-  __syncthreads();
-  for (int jb = 0; jb < n; jb += kPB) {
-    if (wv == 0) {
-      double x[kR][kPB];
-#pragma unroll
-      for (int t = 0; t < kR; ++t) {
-        const int r = jb + lane + 64 * t;
-#pragma unroll
-        for (int p = 0; p < kPB; ++p) x[t][p] = r < n ? sa[r * ld + jb + p] : 0.0;
-      }
-      double dpiv[kPB];
-      // lanes 0..15 also carry row `lane` of the identity through the same
-      // column operations, which leaves row r of W_bb^-T D_bb (the inverse
-      // of the diagonal block's unit factor, transposed) in lane r
-      double y[kPB];
-#pragma unroll
-      for (int q = 0; q < kPB; ++q) y[q] = q == lane ? 1.0 : 0.0;
-      double dv = readlane_d(x[0][0], 0);
-#pragma unroll
-      for (int p = 0; p < kPB; ++p) {
-        dpiv[p] = dv;
-        const double m = x[0][p] * rcp_nr(dv);  // lane q: w_qp / d_p
-        // the next pivot from lane p + 1's own multiplier: the same operands
-        // as its update below, taken first to keep the column chain short
-        if (p + 1 < kPB) dv = readlane_d(fma(-x[0][p], m, x[0][p + 1]), p + 1);
-#pragma unroll
-        for (int q = p + 1; q < kPB; ++q) {
-          const double mq = readlane_d(m, q);
-#pragma unroll
-          for (int t = 0; t < kR; ++t) x[t][q] = fma(-x[t][p], mq, x[t][q]);
-          y[q] = fma(-y[p], mq, y[q]);
-        }
-      }
-      int bad = 0;
-#pragma unroll
-      for (int p = kPB - 1; p >= 0; --p)
-        if (!(dpiv[p] > 0.0) || !isfinite(dpiv[p])) bad = jb + p + 1;
-      if (bad) {
-        if (lane == 0) *sflag = bad;
-      } else {
-        // L = W D^-1/2 for the whole panel (independent chains); the
-        // diagonal block's inverse, (L_bb^-1)[q][r] = y_q(lane r) / sqrt(d_q),
-        // goes transposed into the block's strict upper triangle
-#pragma unroll
-        for (int p = 0; p < kPB; ++p) {
-          const double rs = rsqrt_nr(dpiv[p]);
-#pragma unroll
-          for (int t = 0; t < kR; ++t) {
-            const int r = jb + lane + 64 * t;
-            if (r < n && jb + p <= r) sa[r * ld + jb + p] = r == jb + p ? dpiv[p] * rs : x[t][p] * rs;
-          }
-          if (lane < p) sa[(jb + lane) * ld + jb + p] = y[p] * rs;
-        }
-      }
-    }
-    __syncthreads();
-    if (*sflag) return *sflag;
-    const int s0 = jb + kPB, rest = n - s0;
-    if (rest <= 0) break;
-    const int nt = rest / 16;
-    const int lm = lane & 15, lk = lane >> 4;
-    int cnt = 0;
-    for (int ti = 0; ti < nt; ++ti)
-      for (int tl = 0; tl <= ti; ++tl, ++cnt) {
-        if (cnt % kWaves != wv) continue;
-        const int i0 = s0 + 16 * ti, l0 = s0 + 16 * tl;
-        v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k0 = 0; k0 < kPB; k0 += 4) {
-          const double a = sa[(i0 + lm) * ld + jb + k0 + lk];
-          const double b = sa[(l0 + lm) * ld + jb + k0 + lk];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = i0 + lk + 4 * r, l = l0 + lm;
-          if (l <= i) sa[i * ld + l] -= acc[r];
-        }
-      }
-    __syncthreads();
-  }
-  return 0;
-}
 
 // Factor of an n x n matrix (n <= kSmallN) in one workgroup of 8 wavefronts,
 // the matrix padded in LDS to a multiple of 16 with identity rows and its
@@ -672,243 +555,499 @@ __global__ __launch_bounds__(kCholSmallThreads) void k_chol_small(const double* 
   chol_small_body((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, src, A, n, info);
 }
 
-// blocked: factor the 64 x 64 diagonal block at jb
-__device__ __forceinline__ void chol_diag_body(int bx_, int by_, int gx_, double* A, int n, int jb, int* info) {
-  if (*info != 0) return;
-  __shared__ double sa[kNB * (kNB + 1)];
-  __shared__ int sflag;
-  const int nb = min(kNB, n - jb), ld = kNB + 1;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int nbp = (nb + kPB - 1) / kPB * kPB;
-  copy2d_overlapped(sa, ld, A + (long long)jb * n + jb, n, nb, nb, threadIdx.x, kThreads);
-  pad_identity(sa, ld, nb, nbp, threadIdx.x, kThreads);
-  __syncthreads();
-  const int r = chol_blocked_lds<kWavesD, 1>(sa, nbp, ld, &sflag);
-  for (int i = wv; i < nb; i += kWavesD)
-    for (int l = lane; l <= i; l += 64) A[(long long)(jb + i) * n + jb + l] = sa[i * ld + l];
-  if (threadIdx.x == 0 && r) *info = jb + r;
-}
+// Blocked factorisation (n > kSmallN): one launch per panel of kNB = 64
+// columns.  Launch k has, for every tile (i, j) of the trailing matrix, i >= j
+// > k, one workgroup that forms L_ik = A_ik L_kk^-T and L_jk itself from the
+// raw panel (block substitution with the panel's 16 x 16 inverses, on the
+// matrix cores) and subtracts L_ik L_jk^T; the workgroup of tile (k + 1, k +
+// 1) then factorises it, so that the chain from panel to panel is one tile's
+// update and factorisation behind the other tiles' updates.  Workgroups of
+// the same launch write L over the raw panel k - 1, which nobody reads any
+// more.  Forming the L tiles in every workgroup costs up to 2.5 times the
+// update's own products, but the three launches per panel that it replaces
+// (diagonal, panel solve, update) took 27 + 20 + 15..22 us each, nearly all
+// latency.
+//
+// cw holds the factorised diagonal tiles, kCwTile doubles each: 16 blocks in
+// the matrix instruction's A operand layout, L_cb^T below the diagonal (row c,
+// column b of 16 x 16 blocks at (4 c + b) 256) and the transposed inverses
+// L_cc^-T on it.
+constexpr int kNBB = kNB / kPB;
+constexpr int kCwTile = kNBB * kNBB * kPB * kPB;
+constexpr int kCtLd = kNB + 1;  // row pitch of a tile in LDS
 
-__global__ __launch_bounds__(kThreads) void k_chol_diag(double* A, int n, int jb, int* info) {
-  chol_diag_body((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, A, n, jb, info);
-}
-
-// blocked: A[i, jb:jb+nb] <- A[i, jb:jb+nb] L_jj^-T for rows below the block.
-// A wavefront takes one row at a time with lane q holding column q; lane q
-// keeps row q of L_jj in registers, so the forward substitution is 64
-// readlane broadcasts and fused multiply-adds with no memory traffic.
-constexpr int kTrsmRowsPerWave = 4;
-
-__device__ __forceinline__ void chol_trsm_body(int bx_, int by_, int gx_, double* A, int n, int jb, const int* info) {
-  if (*info != 0) return;
-  __shared__ double sinv[kNB];
-  const int nb = min(kNB, n - jb);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  double lrow[kNB];
+__device__ __forceinline__ v4d blk_load(const double* p, int lane) {
+  v4d v;
 #pragma unroll
-  for (int p = 0; p < kNB; ++p)
-    lrow[p] = (lane < nb && p <= lane) ? A[(long long)(jb + lane) * n + jb + p] : 0.0;
-  if (threadIdx.x < kNB)
-    sinv[threadIdx.x] = threadIdx.x < nb ? 1.0 / A[(long long)(jb + threadIdx.x) * n + jb + threadIdx.x] : 0.0;
-  __syncthreads();
-  const int rows = n - jb - nb;
-  for (int r = bx_ * kWavesD + wv; r < rows; r += gx_ * kWavesD) {
-    double* row = A + (long long)(jb + nb + r) * n + jb;
-    double v = lane < nb ? row[lane] : 0.0;
-#pragma unroll
-    for (int p = 0; p < kNB; ++p) {
-      if (p < nb) {
-        const double xp = readlane_d(v, p) * sinv[p];
-        if (lane == p) v = xp;
-        else if (lane > p) v = fma(-xp, lrow[p], v);
-      }
-    }
-    if (lane < nb) row[lane] = v;
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void k_chol_trsm(double* A, int n, int jb, const int* info) {
-  chol_trsm_body((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, A, n, jb, info);
-}
-
-// blocked: trailing update A[i, l] -= sum_p A[i, p] A[l, p] over the lower
-// 64 x 64 tiles, on the FP64 matrix cores.  Each of the 4 waves owns a 32 x 32
-// quarter as 2 x 2 blocks of v_mfma_f64_16x16x4f64 (A operand: lane holds
-// row lane%16, k = lane/16; B operand: k = lane/16, column lane%16; result
-// register r of a lane: row lane/16 + 4 r, column lane%16).
-
-__device__ __forceinline__ void chol_update_body(int bx_, int by_, int gx_, double* A, int n, int jb, const int* info) {
-  if (*info != 0) return;
-  const int nb = min(kNB, n - jb);
-  const int s0 = jb + nb;
-  const int ti = by_, tl = bx_;
-  if (tl > ti) return;
-  const int i0 = s0 + ti * 64, l0 = s0 + tl * 64;
-  __shared__ double sa[64][kNB + 1];
-  __shared__ double sb[64][kNB + 1];
-  for (int t = threadIdx.x; t < 64 * kNB; t += blockDim.x) {
-    const int r = t / kNB, p = t % kNB;
-    const bool kin = p < nb;
-    sa[r][p] = (kin && i0 + r < n) ? A[(long long)(i0 + r) * n + jb + p] : 0.0;
-    sb[r][p] = (kin && l0 + r < n) ? A[(long long)(l0 + r) * n + jb + p] : 0.0;
-  }
-  __syncthreads();
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int rb = (wv >> 1) * 32, cb = (wv & 1) * 32;   // wave's quarter
-  const int lm = lane & 15, lk = lane >> 4;
-  v4d acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < kNB; k0 += 4) {
-    const double a0 = sa[rb + lm][k0 + lk], a1 = sa[rb + 16 + lm][k0 + lk];
-    const double b0 = sb[cb + lm][k0 + lk], b1 = sb[cb + 16 + lm][k0 + lk];
-    acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-  }
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + rb + 16 * a + lk + 4 * r, l = l0 + cb + 16 * b + lm;
-        if (i < n && l <= i) A[(long long)i * n + l] -= acc[a][b][r];
-      }
-}
-
-__global__ __launch_bounds__(kThreads) void k_chol_update(double* A, int n, int jb, const int* info) {
-  chol_update_body((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, A, n, jb, info);
-}
-
-// p_u = K_hat^-1 rhs with rhs = -r1u + sum_i rpart_i, from the Cholesky
-// factor L (lower triangle of `L`, row-major).  One workgroup of kRThreads
-// (16 wavefronts).  The right-hand side is summed over scenarios in a fixed
-// order (wavefront w takes a contiguous 1/16 of the scenarios, partial sums
-// added in wavefront order).  Both triangular solves go by blocks of 16 rows:
-// the off-diagonal part is a matrix-vector product (one wavefront per row of
-// the block for L, per column for L^T, lanes over the long dimension, then a
-// shuffle reduction), and the 16 x 16 diagonal triangle is solved by one
-// wavefront in registers (lane r holds unknown r; readlane broadcasts).
-// kLDS: L staged in LDS (leading dimension n + 1); else read from global.
-constexpr int kRB = 16, kRThreads = 1024, kRWaves = kRThreads / 64;
-
-// the reduced solve stages L in LDS when it fits next to its reduction buffer
-__host__ __device__ inline bool rsolve_lds(int n) {
-  return 8LL * ((long long)n * (n + 1) + n) + 8LL * kRWaves * 64 <= 160 * 1024;
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  for (int r = 0; r < 4; ++r) v[r] = p[64 * r + lane];
   return v;
 }
 
-template <bool kLDS>
-__device__ __forceinline__ void reduced_solve_body(int bx_, int by_, int gx_, const DP& d, const double* r1u, const double* Lg,
-                                                             double* pu) {
-  extern __shared__ double sm[];
-  __shared__ double red[kRWaves][64];
-  const int n = d.nu, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int ld = kLDS ? n + 1 : n;
-  double* y = sm;
-  const double* L = Lg;
-  if (kLDS) {
-    double* sl = sm + n;
-    copy2d_overlapped(sl, ld, Lg, n, n, n, tid, kRThreads);
-    L = sl;
+// X_c = (L^-1 A^T) block rows of one strip of 16 rows (row0 ..) of a raw
+// panel: x[c] holds element (16 c + 4 r + lane/16, lane%16) of the 64 x 16
+// transposed strip.
+__device__ __forceinline__ void chol_strip(const double* A, int n, int row0, int jb, const double* cw, int lane,
+                                           v4d (&x)[kNBB]) {
+  const int lm = lane & 15, lk = lane >> 4;
+  const int row = row0 + lm;
+  const double* src = A + (long long)min(row, n - 1) * n;
+#pragma unroll
+  for (int c = 0; c < kNBB; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int col = jb + kPB * c + 4 * r + lk;
+      x[c][r] = row < n && col < n ? src[min(col, n - 1)] : 0.0;
+    }
+#pragma unroll
+  for (int c = 0; c < kNBB; ++c) {
+#pragma unroll
+    for (int b = 0; b < c; ++b) {
+      const v4d l = blk_load(cw + (kNBB * c + b) * kPB * kPB, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[r], x[b][r], x[c], 0, 0, 0);
+    }
+    const v4d inv = blk_load(cw + (kNBB + 1) * c * kPB * kPB, lane);
+    v4d y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y = __builtin_amdgcn_mfma_f64_16x16x4f64(inv[r], x[c][r], y, 0, 0, 0);
+    x[c] = y;
   }
-  // right-hand side
-  const int per = (d.N + kRWaves - 1) / kRWaves;
-  const int k0 = wv * per, k1 = min(d.N, k0 + per);
-  for (int c0 = 0; c0 < n; c0 += 64) {
-    const int c = c0 + lane;
-    double acc = 0.0;
-    if (c < n) {
-      // loads in batches of 8 so that they are in flight together
-      int k = k0;
-      for (; k + 8 <= k1; k += 8) {
-        double v[8];
+}
+
+// Factorises the 64 x 64 tile at jb held (lower triangle, padded with identity
+// rows) in sa: L to A's lower triangle, the blocks to cw.  256 threads:
+// wavefront 0 takes the pivots of each 16-column panel (tile_chain, which also
+// gives the block's inverse), the others the blocks below; two barriers per
+// panel.  Returns 0 or the 1-based column (in the tile) of the first bad pivot.
+__device__ __forceinline__ int chol_tile64(double* sa, double* raw, int* sflag, double* A, int n, int jb, double* cw) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int lm = lane & 15, lk = lane >> 4;
+  if (tid == 0) *sflag = 0;
+  __syncthreads();
+  for (int k = 0; k < kNBB; ++k) {
+    const int b0 = kPB * k;
+    if (wv == 0) {
+      double x[kPB], y[kPB], dpv = 0.0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = d.rpart[(long long)(k + u) * n + c];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
+      for (int q = 0; q < kPB; ++q) {
+        x[q] = lane < kPB ? sa[(b0 + lane) * kCtLd + b0 + q] : 0.0;
+        y[q] = lane == q ? 1.0 : 0.0;
       }
-      for (; k < k1; ++k) acc += d.rpart[(long long)k * n + c];
+      tile_chain<0>(x, y, row_bcast<0>(x[0]), 0.0, dpv, lane);
+      const int bad = chol_tile16_stage(x, y, dpv, b0, raw, lane);
+      if (bad && lane == 0) *sflag = bad;
+    }
+    __syncthreads();
+    if (*sflag) return *sflag;
+    // block row of this wavefront (wavefront 0 writes the diagonal block)
+    const int i = k + wv;
+    v4d li = {0.0, 0.0, 0.0, 0.0};
+    if (wv == 0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = lane + 64 * u, r = t / kPB, p = t % kPB;
+        // cw: [p][r] = (L^-1)[r][p] = d_r^-1/2 (W^-T D)[p][r]
+        const double rs = raw[kRawRs + p];
+        cw[(kNBB + 1) * k * kPB * kPB + r * kPB + p] = r <= p ? rs * raw[kRawE + r * kTileLd + p] : 0.0;
+        if (p <= r && jb + b0 + r < n)
+          A[(long long)(jb + b0 + r) * n + jb + b0 + p] =
+              p < r ? raw[kRawW + r * kTileLd + p] * rs : raw[kRawD + p] * rs;
+      }
+    } else if (i < kNBB) {
+      const int i0 = kPB * i;
+      const double rsl = raw[kRawRs + lm];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double m1 = 4 * j + lk <= lm ? rsl * raw[kRawE + (4 * j + lk) * kTileLd + lm] : 0.0;
+        const double b = sa[(i0 + lm) * kCtLd + b0 + 4 * j + lk];
+        li = __builtin_amdgcn_mfma_f64_16x16x4f64(m1, b, li, 0, 0, 0);
+      }
+      // register r: L[i0 + lm][b0 + lk + 4 r], the A operand's transposed block
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        sa[(i0 + lm) * kCtLd + b0 + lk + 4 * r] = li[r];
+        cw[(kNBB * i + k) * kPB * kPB + 64 * r + lane] = li[r];
+        if (jb + i0 + lm < n) A[(long long)(jb + i0 + lm) * n + jb + b0 + lk + 4 * r] = li[r];
+      }
+    }
+    __syncthreads();
+    if (wv > 0 && i < kNBB) {
+      const int i0 = kPB * i;
+      for (int l = k + 1; l <= i; ++l) {
+        const int l0 = kPB * l;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(li[j], sa[(l0 + lm) * kCtLd + b0 + 4 * j + lk], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sa[(i0 + lk + 4 * r) * kCtLd + l0 + lm] -= acc[r];
+      }
+    }
+    __syncthreads();
+  }
+  return 0;
+}
+
+// first launch: block 0 factorises tile (0, 0) of src into A; the others copy
+// the rest of src to A (when they differ)
+__device__ __forceinline__ void chol_first_body(int bx_, int gx_, const double* src, double* A, int n, int* info,
+                                                double* cw) {
+  if (bx_ > 0) {
+    const long long nn = (long long)n * n, step = (long long)(gx_ - 1) * kThreads;
+    for (long long t = (long long)(bx_ - 1) * kThreads + threadIdx.x; t < nn; t += step) {
+      const int r = (int)(t / n), c = (int)(t % n);
+      if (r >= kNB || c > r) A[t] = src[t];
+    }
+    return;
+  }
+  __shared__ double sa[kNB * kCtLd];
+  __shared__ double raw[kRawSize];
+  __shared__ int sflag;
+  for (int t = threadIdx.x; t < kNB * kNB; t += kThreads) {
+    const int r = t / kNB, c = t % kNB;
+    sa[r * kCtLd + c] = src[(long long)r * n + c];
+  }
+  const int bad = chol_tile64(sa, raw, &sflag, A, n, 0, cw);
+  if (threadIdx.x == 0) *info = bad;
+}
+
+// launch k: see above.  bx: tiles of the trailing matrix (row by row, its
+// first tile first), then the tiles of panel k - 1
+__device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k, int* info, double* cw) {
+  if (*info != 0) return;
+  __shared__ double sx[kNB * kNB];   // L_jk^T, block rows by strips of 16
+  __shared__ double sa[kNB * kCtLd];
+  __shared__ double raw[kRawSize];
+  __shared__ int sflag;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lm = lane & 15, lk = lane >> 4;
+  const int nt = (n + kNB - 1) / kNB, T = nt - 1 - k;
+  const double* cwk = cw + (long long)k * kCwTile;
+  v4d x[kNBB];
+  if (bx_ >= T * (T + 1) / 2) {
+    // L over the raw panel k - 1
+    const int row0 = (k + bx_ - T * (T + 1) / 2) * kNB + kPB * wv, jb = (k - 1) * kNB;
+    if (row0 >= n) return;
+    chol_strip(A, n, row0, jb, cwk - kCwTile, lane, x);
+    wave_sync();
+    if (row0 + lm < n) {
+      double* o = A + (long long)(row0 + lm) * n + jb;
+#pragma unroll
+      for (int c = 0; c < kNBB; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[kPB * c + 4 * r + lk] = x[c][r];
+    }
+    return;
+  }
+  int ti = (int)((sqrt(8.0 * (double)bx_ + 1.0) - 1.0) * 0.5);
+  while (ti * (ti + 1) / 2 > bx_) --ti;
+  while ((ti + 1) * (ti + 2) / 2 <= bx_) ++ti;
+  const int tj = bx_ - ti * (ti + 1) / 2;
+  const int i0 = (k + 1 + ti) * kNB, j0 = (k + 1 + tj) * kNB, jb = k * kNB;
+  // L_jk^T strips to LDS, L_ik^T strip of this wavefront in registers
+  chol_strip(A, n, j0 + kPB * wv, jb, cwk, lane, x);
+#pragma unroll
+  for (int c = 0; c < kNBB; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sx[(wv * kNBB + c) * kPB * kPB + 64 * r + lane] = x[c][r];
+  if (ti != tj) chol_strip(A, n, i0 + kPB * wv, jb, cwk, lane, x);
+  __syncthreads();
+  const bool next = bx_ == 0;
+#pragma unroll
+  for (int q = 0; q < kNBB; ++q) {
+    if (ti == tj && q > wv) break;
+    // rows i0 + 16 wv + lk + 4 r, column j0 + 16 q + lm
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    const int col = j0 + kPB * q + lm;
+#pragma unroll
+    for (int c = 0; c < kNBB; ++c) {
+      const v4d b = blk_load(sx + (q * kNBB + c) * kPB * kPB, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[c][r], b[r], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = i0 + kPB * wv + lk + 4 * r;
+      if (next) {
+        const bool in = row < n && col < n;
+        sa[(row - i0) * kCtLd + col - j0] =
+            in ? A[(long long)row * n + col] - acc[r] : (row == col ? 1.0 : 0.0);
+      } else if (row < n && col <= row) {
+        A[(long long)row * n + col] -= acc[r];
+      }
+    }
+  }
+  if (next) {
+    const int bad = chol_tile64(sa, raw, &sflag, A, n, i0, cw + (long long)(k + 1) * kCwTile);
+    if (threadIdx.x == 0 && bad) *info = i0 + bad;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_chol_first(const double* src, double* A, int n, int* info, double* cw) {
+  chol_first_body(blockIdx.x, gridDim.x, src, A, n, info, cw);
+}
+__global__ __launch_bounds__(kThreads) void k_chol_step(double* A, int n, int k, int* info, double* cw) {
+  chol_step_body(blockIdx.x, A, n, k, info, cw);
+}
+
+int chol_tiles(int n) { return (n + kNB - 1) / kNB; }
+// workgroups of launch k, and of the first launch
+int chol_step_blocks(int n, int k) {
+  const int nt = chol_tiles(n), T = nt - 1 - k;
+  return T * (T + 1) / 2 + (k > 0 ? nt - k : 0);
+}
+int chol_first_blocks(int n) { return 1 + std::min(512, (n * n + 4 * kThreads - 1) / (4 * kThreads)); }
+
+// p_u = K_hat^-1 rhs, rhs = -r1u + sum_i rpart_i, from the Cholesky factor of
+// more than kSmallN columns (lower triangle of `L`, row-major), by tiles of 64
+// columns:
+//  - k_rsolve_prep, one workgroup per tile, inverts the diagonal tiles and
+//    sums the scenario parts in scenario order;
+//  - k_rsolve_panel substitutes a panel of up to kRsTiles tiles in one
+//    workgroup, each tile's row (forward) or column (backward) of L against
+//    the solved part, then the tile's inverse;
+//  - k_rsolve_update takes a solved panel out of the rows (columns) outside
+//    it, over the chip; not needed up to kRsTiles tiles, where one panel
+//    launch runs both directions.
+// One workgroup that solved every 16-row block with a chain of broadcasts and
+// read the whole factor took 196 us at n_u = 519 and 3.2 ms at 2889.
+constexpr int kRsThreads = 1024, kRsWaves = kRsThreads / 64;
+constexpr int kRsTiles = 10;  // tiles of a panel: one CU reads their 1.6 MB of L in about 15 us
+
+// value summed over the lanes of a row of 16 (DPP row_ror), then over the four rows
+__device__ __forceinline__ double lanes_sum(double v) {
+  v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, false);
+  v += __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, false);
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+
+__device__ __forceinline__ void rsolve_prep_body(const DP& d, int bx_, const double* r1u, const double* L) {
+  __shared__ double sl[kNB * kCtLd];
+  __shared__ double si[kNBB][kPB * kTileLd];
+  const int n = d.nu, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lm = lane & 15, lk = lane >> 4, jb = bx_ * kNB;
+  for (int t = tid; t < kNB * kNB; t += kThreads) {
+    const int r = t / kNB, c = t % kNB;
+    sl[r * kCtLd + c] = jb + r < n && jb + c < n ? (c <= r ? L[(long long)(jb + r) * n + jb + c] : 0.0)
+                                                 : (r == c ? 1.0 : 0.0);
+  }
+  // right-hand side of the tile's columns: wavefront w a quarter of the scenarios
+  {
+    __shared__ double red[kThreads / 64][kNB];
+    const int c = jb + lane, per = (d.N + 3) / 4, k1 = min(d.N, (wv + 1) * per);
+    double acc = 0.0;
+    for (int k = wv * per; k < k1; k += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = k + u < k1 && c < n ? d.rpart[(long long)(k + u) * n + c] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
     }
     red[wv][lane] = acc;
     __syncthreads();
-    if (wv == 0 && c < n) {
-      double sum = -r1u[c];
-      for (int q = 0; q < kRWaves; ++q) sum += red[q][lane];
-      y[c] = sum;
-    }
-    __syncthreads();
+    if (wv == 0 && c < n) d.ry[c] = -r1u[c] + ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
   }
-  // forward: L y = b
-  for (int jb = 0; jb < n; jb += kRB) {
-    const int nb = min(kRB, n - jb);
-    if (wv < nb) {
-      const double* row = L + (long long)(jb + wv) * ld;
-      double acc = 0.0;
-      for (int q = lane; q < jb; q += 64) acc = fma(row[q], y[q], acc);
-      acc = wave_sum(acc);
-      if (lane == 0) y[jb + wv] -= acc;
-    }
-    __syncthreads();
-    if (wv == 0) {
-      const int r = lane;
-      double lrow[kRB];
+  // 16 x 16 inverse of diagonal block wv, lane = column
+  {
+    double x[kPB];
+    const int b0 = kPB * wv;
 #pragma unroll
-      for (int p = 0; p < kRB; ++p) lrow[p] = (r < nb && p <= r) ? L[(long long)(jb + r) * ld + jb + p] : 0.0;
-      const double myinv = r < nb ? rcp_nr(L[(long long)(jb + r) * ld + jb + r]) : 0.0;  // 1/L_rr
-      double v = r < nb ? y[jb + r] : 0.0;
+    for (int r = 0; r < kPB; ++r) x[r] = r == lm ? 1.0 : 0.0;
 #pragma unroll
-      for (int p = 0; p < kRB; ++p) {
-        if (p < nb) {
-          const double vp = readlane_d(v, p) * readlane_d(myinv, p);
-          if (r == p) v = vp;
-          else if (r > p) v = fma(-lrow[p], vp, v);
-        }
-      }
-      if (r < nb) y[jb + r] = v;
+    for (int p = 0; p < kPB; ++p) {
+      x[p] *= 1.0 / sl[(b0 + p) * kCtLd + b0 + p];
+#pragma unroll
+      for (int r = p + 1; r < kPB; ++r) x[r] = fma(-sl[(b0 + r) * kCtLd + b0 + p], x[p], x[r]);
     }
-    __syncthreads();
+    if (lk == 0)
+#pragma unroll
+      for (int r = 0; r < kPB; ++r) si[wv][r * kTileLd + lm] = x[r];
   }
-  // backward: L^T x = y
-  for (int jb = ((n - 1) / kRB) * kRB; jb >= 0; jb -= kRB) {
-    const int nb = min(kRB, n - jb);
-    if (wv < nb) {
-      double acc = 0.0;
-      for (int i = jb + nb + lane; i < n; i += 64) acc = fma(L[(long long)i * ld + jb + wv], y[i], acc);
-      acc = wave_sum(acc);
-      if (lane == 0) y[jb + wv] -= acc;
-    }
-    __syncthreads();
-    if (wv == 0) {
-      const int r = lane;
-      // lane r holds column r of the diagonal block: L[jb + p][jb + r], p >= r
-      double lcol[kRB];
+  __syncthreads();
+  // strip wv of the inverse: X_c = I_c (E_c - sum_{b < c} L_cb X_b)
+  v4d x[kNBB];
+  double* o = d.rinv + (long long)bx_ * kNB * kNB;
 #pragma unroll
-      for (int p = 0; p < kRB; ++p) lcol[p] = (r < nb && p < nb && p >= r) ? L[(long long)(jb + p) * ld + jb + r] : 0.0;
-      const double myinv = r < nb ? rcp_nr(L[(long long)(jb + r) * ld + jb + r]) : 0.0;
-      double v = r < nb ? y[jb + r] : 0.0;
+  for (int c = 0; c < kNBB; ++c) {
+    v4d t = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int p = kRB - 1; p >= 0; --p) {
-        if (p < nb) {
-          const double vp = readlane_d(v, p) * readlane_d(myinv, p);
-          if (r == p) v = vp;
-          else if (r < p) v = fma(-lcol[p], vp, v);
-        }
-      }
-      if (r < nb) y[jb + r] = v;
-    }
-    __syncthreads();
+    for (int b = 0; b < c; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        t = __builtin_amdgcn_mfma_f64_16x16x4f64(-sl[(kPB * c + lm) * kCtLd + kPB * b + 4 * r + lk], x[b][r], t, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (c == wv) t[r] = 4 * r + lk == lm ? 1.0 : 0.0;
+    x[c] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      x[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(si[c][lm * kTileLd + 4 * r + lk], t[r], x[c], 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[(kPB * c + 4 * r + lk) * kNB + kPB * wv + lm] = x[c][r];
   }
-  for (int c = tid; c < n; c += kRThreads) pu[c] = y[c];
 }
 
-template <bool kLDS>
-__global__ __launch_bounds__(kRThreads) void k_reduced_solve(DP d, const double* r1u, const double* Lg,
-                                                             double* pu) {
-  reduced_solve_body<kLDS>((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, d, r1u, Lg, pu);
+// Tiles [t0, t1): forward substitution (kFwd), backward, or both.
+__device__ __forceinline__ void rsolve_panel_body(const DP& d, int t0, int t1, bool fwd, bool bwd, const double* L,
+                                                  double* pu) {
+  __shared__ double y[kRsTiles * kNB];
+  __shared__ double t[kNB];
+  __shared__ double red[kRsWaves][kNB], red2[kRsWaves][kNB];
+  const int n = d.nu, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int p0 = t0 * kNB, np = (t1 - t0) * kNB;
+  for (int c = tid; c < np; c += kRsThreads) y[c] = p0 + c < n ? d.ry[p0 + c] : 0.0;
+  __syncthreads();
+  constexpr int kR = kNB / kRsWaves;  // rows of a tile per wavefront
+  if (fwd) {
+    for (int k = 0; k < t1 - t0; ++k) {
+      const int r0 = p0 + k * kNB + kR * wv;
+      const double* inv = d.rinv + (long long)(t0 + k) * kNB * kNB + kR * wv * kNB + lane;
+      double iv[kR], acc[kR];
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        iv[r] = inv[r * kNB];
+        acc[r] = 0.0;
+      }
+      for (int q = 0; q < k; ++q) {
+        const double yq = y[q * kNB + lane];
+#pragma unroll
+        for (int r = 0; r < kR; ++r)
+          acc[r] = fma(r0 + r < n ? L[(long long)(r0 + r) * n + p0 + q * kNB + lane] : 0.0, yq, acc[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        const double a = lanes_sum(acc[r]);
+        if (lane == 0) t[kR * wv + r] = y[k * kNB + kR * wv + r] - a;
+      }
+      __syncthreads();
+      const double tl = t[lane];
+#pragma unroll
+      for (int r = 0; r < kR; ++r) {
+        const double a = lanes_sum(iv[r] * tl);
+        if (lane == 0) y[k * kNB + kR * wv + r] = a;
+      }
+      __syncthreads();
+    }
+  }
+  if (bwd) {
+    for (int k = t1 - t0 - 1; k >= 0; --k) {
+      const int c = p0 + k * kNB + lane;
+      const double* inv = d.rinv + (long long)(t0 + k) * kNB * kNB + kR * wv * kNB + lane;
+      double iv[kR], acc = 0.0;
+#pragma unroll
+      for (int r = 0; r < kR; ++r) iv[r] = inv[r * kNB];
+      // rows of the later tiles, kRsWaves apart
+      const int i1 = min(n - p0, np);
+      for (int i = (k + 1) * kNB + wv; i < i1; i += 8 * kRsWaves) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int ii = i + u * kRsWaves;
+          v[u] = ii < i1 && c < n ? L[(long long)(p0 + ii) * n + c] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = fma(v[u], y[min(i + u * kRsWaves, np - 1)], acc);
+      }
+      red[wv][lane] = acc;
+      __syncthreads();
+      double tl = y[k * kNB + lane];
+#pragma unroll
+      for (int w = 0; w < kRsWaves; ++w) tl -= red[w][lane];
+      double p = 0.0;
+#pragma unroll
+      for (int r = 0; r < kR; ++r) p = fma(iv[r], readlane_d(tl, kR * wv + r), p);
+      red2[wv][lane] = p;
+      __syncthreads();
+      if (wv == 0) {
+        double x = 0.0;
+#pragma unroll
+        for (int w = 0; w < kRsWaves; ++w) x += red2[w][lane];
+        y[k * kNB + lane] = x;
+      }
+      __syncthreads();
+    }
+  }
+  for (int c = tid; c < np; c += kRsThreads)
+    if (p0 + c < n) {
+      d.ry[p0 + c] = y[c];
+      if (bwd) pu[p0 + c] = y[c];
+    }
+}
+
+// y of the rows below (fwd) or of the columns before the panel [t0, t1)
+__device__ __forceinline__ void rsolve_update_body(const DP& d, int bx_, int t0, int t1, bool fwd, const double* L) {
+  __shared__ double red[kThreads / 64][kNB];
+  const int n = d.nu, lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p0 = t0 * kNB, p1 = min(n, t1 * kNB);
+  if (fwd) {
+    const int row = p1 + bx_ * (kThreads / 64) + wv;
+    if (row >= n) return;
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < kRsTiles; ++q) {
+      const int c = p0 + q * kNB + lane;
+      if (c < p1) acc = fma(L[(long long)row * n + c], d.ry[c], acc);
+    }
+    acc = lanes_sum(acc);
+    if (lane == 0) d.ry[row] -= acc;
+  } else {
+    const int c = bx_ * kNB + lane;  // p0 is a multiple of the tile, so c < p0
+    double acc = 0.0;
+    for (int i = p0 + wv; i < p1; i += 16 * (kThreads / 64)) {
+      double v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int ii = i + u * (kThreads / 64);
+        v[u] = ii < p1 ? L[(long long)ii * n + c] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc = fma(v[u], d.ry[min(i + u * (kThreads / 64), n - 1)], acc);
+    }
+    red[wv][lane] = acc;
+    __syncthreads();
+    if (wv == 0) d.ry[c] -= (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_rsolve_prep(DP d, const double* r1u, const double* L) {
+  rsolve_prep_body(d, blockIdx.x, r1u, L);
+}
+__global__ __launch_bounds__(kRsThreads) void k_rsolve_panel(DP d, int t0, int t1, bool fwd, bool bwd,
+                                                             const double* L, double* pu) {
+  rsolve_panel_body(d, t0, t1, fwd, bwd, L, pu);
+}
+__global__ __launch_bounds__(kThreads) void k_rsolve_update(DP d, int t0, int t1, bool fwd, const double* L) {
+  rsolve_update_body(d, blockIdx.x, t0, t1, fwd, L);
+}
+
+// The launches of a reduced solve after k_rsolve_prep, in order: (first tile,
+// last tile, forward, backward, workgroups of the update or 0 for a panel).
+template <typename F>
+void rsolve_each(int n, F f) {
+  const int nt = chol_tiles(n), np = (nt + kRsTiles - 1) / kRsTiles, w = (nt + np - 1) / np;
+  if (np == 1) {
+    f(0, nt, true, true, 0);
+    return;
+  }
+  for (int p = 0; p < np; ++p) {
+    const int t0 = p * w, t1 = std::min(nt, t0 + w);
+    const bool last = t1 == nt;
+    f(t0, t1, true, last, 0);
+    if (!last) f(t0, t1, true, false, (n - t1 * kNB + kThreads / 64 - 1) / (kThreads / 64));
+    if (last) {
+      f(t0, t1, false, false, t0);
+      break;
+    }
+  }
+  for (int p = np - 1; p >= 0; --p) {
+    const int t0 = p * w, t1 = std::min(nt, t0 + w);
+    if (t0 >= nt || t1 == nt) continue;
+    f(t0, t1, false, true, 0);
+    if (t0 > 0) f(t0, t1, false, false, t0);
+  }
 }
 
 // Reduced solve with the factor stored by k_chol_small.  Every wavefront
@@ -1076,31 +1215,12 @@ static hipError_t allow_lds(const void* fn, int* cur, int need) {
 }
 
 hipError_t configure_dense_kernels(const DP& d) {
-  static int c1 = 0, c2 = 0, c3 = 0, c5 = 0;
+  static int c1 = 0, c5 = 0;
   hipError_t e = hipSuccess;
   if (d.nu <= kSmallN) e = allow_lds((const void*)k_chol_small, &c1, chol_small_lds_bytes(d.nu));
   if (e == hipSuccess && d.nu <= kSmallN)
     e = allow_lds((const void*)k_reduced_solve_blk, &c5, (int)rsolve_blk_lds_bytes(d.nu));
-  if (e == hipSuccess && d.nu > kSmallN) {
-    if (rsolve_lds(d.nu))
-      e = allow_lds((const void*)k_reduced_solve<true>, &c2, 8 * (d.nu * (d.nu + 1) + d.nu));
-    else
-      e = allow_lds((const void*)k_reduced_solve<false>, &c3, 8 * d.nu);
-  }
   return e;
-}
-
-__device__ __forceinline__ void copy_body(int bx_, int by_, int gx_, const double* a, double* b, long long n) {
-  long long t = (long long)bx_ * blockDim.x + threadIdx.x;
-  if (t < n) b[t] = a[t];
-}
-
-__global__ void k_copy(const double* a, double* b, long long n) {
-  copy_body((int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, a, b, n);
-}
-
-void launch_copy(const double* a, double* b, long long n, hipStream_t s) {
-  k_copy<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(a, b, n);
 }
 
 void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s) {
@@ -1139,18 +1259,9 @@ void launch_cholesky_from(const DP& d, const double* src, double* a, int* info, 
     k_chol_small<<<1, kCholSmallThreads, (size_t)chol_small_lds_bytes(n), s>>>(src, a, n, info);
     return;
   }
-  if (src != a) launch_copy(src, a, (long long)n * n, s);
-  k_set_int<<<1, 1, 0, s>>>(info, 0);
-  for (int jb = 0; jb < n; jb += kNB) {
-    k_chol_diag<<<1, kThreads, 0, s>>>(a, n, jb, info);
-    const int nb = n - jb < kNB ? n - jb : kNB;
-    const int rest = n - jb - nb;
-    if (rest <= 0) break;
-    k_chol_trsm<<<(rest + kWavesD * kTrsmRowsPerWave - 1) / (kWavesD * kTrsmRowsPerWave), kThreads, 0, s>>>(
-        a, n, jb, info);
-    const int nt = (rest + 63) / 64;
-    k_chol_update<<<dim3(nt, nt), kThreads, 0, s>>>(a, n, jb, info);
-  }
+  k_chol_first<<<src != a ? chol_first_blocks(n) : 1, kThreads, 0, s>>>(src, a, n, info, d.cw);
+  for (int k = 0; k < chol_tiles(n); ++k)
+    if (chol_step_blocks(n, k) > 0) k_chol_step<<<chol_step_blocks(n, k), kThreads, 0, s>>>(a, n, k, info, d.cw);
 }
 
 void launch_cholesky(const DP& d, double* a, int* info, hipStream_t s) {
@@ -1161,10 +1272,13 @@ void launch_reduced_solve(const DP& d, const double* r1u, const double* chol, do
                           hipStream_t s) {
   if (d.nu <= kSmallN)
     k_reduced_solve_blk<<<1, kIThreads, (size_t)rsolve_blk_lds_bytes(d.nu), s>>>(d, r1u, chol, pu);
-  else if (rsolve_lds(d.nu))
-    k_reduced_solve<true><<<1, kRThreads, 8 * ((size_t)d.nu * (d.nu + 1) + d.nu), s>>>(d, r1u, chol, pu);
-  else
-    k_reduced_solve<false><<<1, kRThreads, 8 * (size_t)d.nu, s>>>(d, r1u, chol, pu);
+  else {
+    k_rsolve_prep<<<chol_tiles(d.nu), kThreads, 0, s>>>(d, r1u, chol);
+    rsolve_each(d.nu, [&](int t0, int t1, bool fwd, bool bwd, int groups) {
+      if (groups > 0) k_rsolve_update<<<groups, kThreads, 0, s>>>(d, t0, t1, fwd, chol);
+      else k_rsolve_panel<<<1, kRsThreads, 0, s>>>(d, t0, t1, fwd, bwd, chol, pu);
+    });
+  }
 }
 
 // ---- several instances in one launch (block b is block (blk[b].bx, blk[b].by)
@@ -1191,31 +1305,26 @@ __global__ __launch_bounds__(kCholSmallThreads) void k_chol_small_m(RKKT_MULTI_A
   RKKT_MULTI_PROLOGUE
   chol_small_body(mb.bx, mb.by, mb.gx, it.khat, it.chol, d.nu, it.info);
 }
-__global__ void k_copy_chol_m(RKKT_MULTI_ARGS) {
+__global__ __launch_bounds__(kThreads) void k_chol_first_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
-  copy_body(mb.bx, mb.by, mb.gx, it.khat, it.chol, (long long)d.nu * d.nu);
+  chol_first_body(mb.bx, mb.gx, it.khat, it.chol, d.nu, it.info, d.cw);
 }
-__global__ void k_set_info_m(RKKT_MULTI_ARGS) {
+__global__ __launch_bounds__(kThreads) void k_chol_step_m(RKKT_MULTI_ARGS, int k) {
   RKKT_MULTI_PROLOGUE
-  (void)d;
-  if (threadIdx.x == 0) *it.info = 0;
+  chol_step_body(mb.bx, it.chol, d.nu, k, it.info, d.cw);
 }
-__global__ __launch_bounds__(kThreads) void k_chol_diag_m(RKKT_MULTI_ARGS, int jb) {
+__global__ __launch_bounds__(kThreads) void k_rsolve_prep_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
-  chol_diag_body(mb.bx, mb.by, mb.gx, it.chol, d.nu, jb, it.info);
+  rsolve_prep_body(d, mb.bx, it.r1u, it.chol);
 }
-__global__ __launch_bounds__(kThreads) void k_chol_trsm_m(RKKT_MULTI_ARGS, int jb) {
+__global__ __launch_bounds__(kRsThreads) void k_rsolve_panel_m(RKKT_MULTI_ARGS, int jb) {
   RKKT_MULTI_PROLOGUE
-  chol_trsm_body(mb.bx, mb.by, mb.gx, it.chol, d.nu, jb, it.info);
+  const int t1 = jb >> 14 & 0x3fff;
+  rsolve_panel_body(d, jb & 0x3fff, t1 ? t1 : (d.nu + kNB - 1) / kNB, jb >> 28 & 1, jb >> 29 & 1, it.chol, it.pu);
 }
-__global__ __launch_bounds__(kThreads) void k_chol_update_m(RKKT_MULTI_ARGS, int jb) {
+__global__ __launch_bounds__(kThreads) void k_rsolve_update_m(RKKT_MULTI_ARGS, int jb) {
   RKKT_MULTI_PROLOGUE
-  chol_update_body(mb.bx, mb.by, mb.gx, it.chol, d.nu, jb, it.info);
-}
-template <bool kLDS>
-__global__ __launch_bounds__(kRThreads) void k_reduced_solve_m(RKKT_MULTI_ARGS) {
-  RKKT_MULTI_PROLOGUE
-  reduced_solve_body<kLDS>(mb.bx, mb.by, mb.gx, d, it.r1u, it.chol, it.pu);
+  rsolve_update_body(d, mb.bx, jb & 0x3fff, jb >> 14 & 0x3fff, jb >> 28 & 1, it.chol);
 }
 __global__ __launch_bounds__(kIThreads) void k_reduced_solve_blk_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
@@ -1246,26 +1355,25 @@ void launches_dense(const DP& d, std::vector<Launch>& out) {
   if (n <= kSmallN) {
     out.push_back(Launch{F, kKCholSmall, 0, 1, 1, kCholSmallThreads, 0, chol_small_lds_bytes(n)});
   } else {
-    out.push_back(Launch{F, kKCopyChol, 0, (int)(((long long)n * n + kThreads - 1) / kThreads), 1, kThreads, 0, 0});
-    out.push_back(Launch{F + 1, kKSetInfo, 0, 1, 1, 1, 0, 0});
-    for (int jb = 0, q = 0; jb < n; jb += kNB, ++q) {
-      out.push_back(Launch{F + 2 + 3 * q, kKCholDiag, 0, 1, 1, kThreads, jb, 0});
-      const int nb = n - jb < kNB ? n - jb : kNB;
-      const int rest = n - jb - nb;
-      if (rest <= 0) break;
-      out.push_back(Launch{F + 3 + 3 * q, kKCholTrsm, 0,
-                           (rest + kWavesD * kTrsmRowsPerWave - 1) / (kWavesD * kTrsmRowsPerWave), 1, kThreads, jb,
-                           0});
-      const int nt = (rest + 63) / 64;
-      out.push_back(Launch{F + 4 + 3 * q, kKCholUpdate, 0, nt, nt, kThreads, jb, 0});
-    }
+    out.push_back(Launch{F, kKCholFirst, 0, chol_first_blocks(n), 1, kThreads, 0, 0});
+    for (int k = 0; k < chol_tiles(n); ++k)
+      if (chol_step_blocks(n, k) > 0)
+        out.push_back(Launch{F + 1 + k, kKCholStep, 0, chol_step_blocks(n, k), 1, kThreads, k, 0});
   }
   if (n <= kSmallN)
     out.push_back(Launch{kStRSolve * 4096, kKRSolveBlk, 0, 1, 1, kIThreads, 0, rsolve_blk_lds_bytes(n)});
-  else if (rsolve_lds(n))
-    out.push_back(Launch{kStRSolve * 4096, kKRSolve, 1, 1, 1, kRThreads, 0, 8LL * ((long long)n * (n + 1) + n)});
-  else
-    out.push_back(Launch{kStRSolve * 4096, kKRSolve, 0, 1, 1, kRThreads, 0, 8LL * n});
+  else {
+    int q = kStRSolve * 4096;
+    out.push_back(Launch{q++, kKRSolvePrep, 0, chol_tiles(n), 1, kThreads, 0, 0});
+    // jb: first tile, last tile << 14 (0: the last of the matrix, so that
+    // one-panel instances share a launch), forward << 28, backward << 29
+    rsolve_each(n, [&](int t0, int t1, bool fwd, bool bwd, int groups) {
+      const int last = t0 == 0 && t1 == chol_tiles(n) ? 0 : t1;
+      const int jb = t0 | last << 14 | (fwd ? 1 : 0) << 28 | (bwd ? 1 : 0) << 29;
+      if (groups > 0) out.push_back(Launch{q++, kKRSolveUpdate, 0, groups, 1, kThreads, jb, 0});
+      else out.push_back(Launch{q++, kKRSolvePanel, 0, 1, 1, kRsThreads, jb, 0});
+    });
+  }
 }
 
 hipError_t multi_dense(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
@@ -1291,19 +1399,13 @@ hipError_t multi_dense(const Launch& l, unsigned nblk, long long lds, const DP* 
       }
     case kKCholSmall:
       return go((const void*)k_chol_small_m, 0, [&] { k_chol_small_m<<<nblk, T, L, s>>>(dps, its, blk); });
-    case kKCopyChol: return go(nullptr, -1, [&] { k_copy_chol_m<<<nblk, T, 0, s>>>(dps, its, blk); });
-    case kKSetInfo: return go(nullptr, -1, [&] { k_set_info_m<<<nblk, T, 0, s>>>(dps, its, blk); });
-    case kKCholDiag: return go(nullptr, -1, [&] { k_chol_diag_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
-    case kKCholTrsm: return go(nullptr, -1, [&] { k_chol_trsm_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
-    case kKCholUpdate: return go(nullptr, -1, [&] { k_chol_update_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
+    case kKCholFirst: return go(nullptr, -1, [&] { k_chol_first_m<<<nblk, T, 0, s>>>(dps, its, blk); });
+    case kKCholStep: return go(nullptr, -1, [&] { k_chol_step_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
     case kKRSolveBlk:
       return go((const void*)k_reduced_solve_blk_m, 1, [&] { k_reduced_solve_blk_m<<<nblk, T, L, s>>>(dps, its, blk); });
-    case kKRSolve:
-      if (l.variant == 1)
-        return go((const void*)k_reduced_solve_m<true>, 2,
-                  [&] { k_reduced_solve_m<true><<<nblk, T, L, s>>>(dps, its, blk); });
-      return go((const void*)k_reduced_solve_m<false>, 3,
-                [&] { k_reduced_solve_m<false><<<nblk, T, L, s>>>(dps, its, blk); });
+    case kKRSolvePrep: return go(nullptr, -1, [&] { k_rsolve_prep_m<<<nblk, T, 0, s>>>(dps, its, blk); });
+    case kKRSolvePanel: return go(nullptr, -1, [&] { k_rsolve_panel_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
+    case kKRSolveUpdate: return go(nullptr, -1, [&] { k_rsolve_update_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
     default:
       *handled = false;
       return hipSuccess;
