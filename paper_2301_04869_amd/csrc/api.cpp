@@ -383,15 +383,19 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
       UP(pair_nodes, t.pair_nodes) UP(gstrip, t.gstrip) UP(rmap, t.rmap) UP(smap, t.smap)
       UP(cjobs, t.cjobs) UP(sn_ptr, t.sn_ptr) UP(sn, t.sn)
 #undef UP
-      r.npool = t.npool; r.nstrip = t.nstrip; r.T = t.T; r.ngroup = t.ngroup; r.parts = t.parts;
+      r.npool = t.npool; r.nstrip = t.nstrip; r.T = t.T; r.ngroup = t.ngroup; r.parts = t.parts; r.sparts = t.sparts;
       r.npair = (int)t.pair_g.size() / 2;
       r.nkuu = (int)t.kuu.size() / 3;
       r.stride = t.stride;
+      r.zero = t.zero;
       r.vstride = t.vstride;
       r.ncjob = (int)t.cjobs.size() / 2;
       r.nlev = (int)t.lev_ptr.size() - 1;
       const size_t ld = (size_t)t.ngroup * t.T * rkkt::kTreeB;
       if ((e = dalloc(p, &r.slab, (size_t)s.N * t.stride)) != hipSuccess) goto hip_error;
+      if ((e = hipMemset2D(r.slab + t.zero, sizeof(double) * t.stride, 0,
+                           sizeof(double) * rkkt::kTreeNB * rkkt::kTreeBlk, s.N)) != hipSuccess)
+        goto hip_error;
       if ((e = dalloc(p, &r.pool, (size_t)s.N * t.npool * rkkt::kTreeBlk)) != hipSuccess) goto hip_error;
       if ((e = dalloc(p, &r.vec, (size_t)s.N * t.vstride)) != hipSuccess) goto hip_error;
       if ((e = dalloc(p, &r.x, (size_t)s.N * s.nx)) != hipSuccess) goto hip_error;

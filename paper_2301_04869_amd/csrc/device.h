@@ -24,8 +24,8 @@ struct TreeDP {
   const int *cjobs, *sn_ptr, *sn;
   const short *rmap, *smap;
   int vstride, ncjob, nlev;
-  int npool, nstrip, T, ngroup, parts, npair, nkuu;
-  long long stride;
+  int npool, nstrip, T, ngroup, parts, sparts, npair, nkuu;
+  long long stride, zero;
   double *slab;  // [N][stride] fronts
   double *pool;  // [N][npool][256] blocks of original entries
   double *vec;   // [N][vstride] step vectors of the nodes

@@ -18,8 +18,8 @@
 // L_x per workgroup in device memory, every term of four triangular solves a
 // 512-byte gather), a front is read and written once and all its work is
 // 16 x 16 x 4 FP64 matrix products on registers: at 9241 buses, 16 scenarios
-// 105 GFLOP on 1.7 GB of fronts against 335 GB of panel traffic, 9.4 ms
-// (fronts 4.3, product 4.8, sum 0.1) against 90.7.
+// 105 GFLOP on 1.7 GB of fronts against 335 GB of panel traffic, 5.1 ms
+// (fronts 2.7, product 2.3, sum 0.1) against 90.7.
 #include "device.h"
 
 namespace rkkt {
@@ -530,57 +530,96 @@ __device__ __forceinline__ void tree_cols_body(const DP& d, int job, int k) {
 // part_p[a][b] = -sum over the part's (node, scenario) units of
 // V_a^T Y_b + Y_a^T V_b, one wavefront per (pair of groups of T strips, part);
 // every operand block is read straight from the slab in the matrix
-// instruction's own layout.
+// instruction's own layout, one step of four rows ahead of its use, strips
+// that a node does not hold from a block of zeros.  Bound by the matrix cores
+// once the operands come from L2 (64 x 64 outputs per wavefront: 8 flops per
+// byte; the probe of independent FP64 matrix instructions reaches 49 TFLOP/s):
+// 9241 buses x 16 scenarios 80 GFLOP in 2.28 ms, 35 TFLOP/s; without the loads
+// ahead and with every part on every die 4.68 ms.
+template <int T>
+struct ProdUnit {
+  const double* slab;
+  int va[T], ya[T], vb[T], yb[T], steps;
+};
+template <int T>
+struct ProdRegs {
+  double va[T], ya[T], vb[T], yb[T];
+};
+
+template <int T>
+__device__ __forceinline__ void prod_load(ProdRegs<T>& x, const ProdUnit<T>& u, int st, int lane) {
+  const double* p = u.slab + 64 * st;
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    x.va[i] = (p + u.va[i])[lane];
+    x.ya[i] = (p + u.ya[i])[lane];
+    x.vb[i] = (p + u.vb[i])[lane];
+    x.yb[i] = (p + u.yb[i])[lane];
+  }
+}
+
+template <int T>
+__device__ __forceinline__ void prod_mul(const ProdRegs<T>& x, v4d (&acc)[T][T]) {
+#pragma unroll
+  for (int i = 0; i < T; ++i)
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.va[i], x.yb[j], acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.ya[i], x.vb[j], acc[i][j], 0, 0, 0);
+    }
+}
+
 template <int T>
 __device__ __forceinline__ void tree_product_body(const DP& d, int bx, int part) {
   const int lane = threadIdx.x & 63, q = bx * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (q >= d.tr.npair) return;
+  if (q >= d.tr.npair || d.tr.pair_g[2 * q] < 0) return;
   const int a = d.tr.pair_g[2 * q], b = d.tr.pair_g[2 * q + 1];
   v4d acc[T][T];
 #pragma unroll
   for (int i = 0; i < T; ++i)
 #pragma unroll
     for (int j = 0; j < T; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-  const int l0 = d.tr.pair_ptr[q];
-  const long long units = (long long)(d.tr.pair_ptr[q + 1] - l0) * d.N;
-  const long long u0 = units * part / d.tr.parts, u1 = units * (part + 1) / d.tr.parts;
-  for (long long u = u0; u < u1;) {
-    const int li = (int)(u / d.N);
-    const int node = __builtin_amdgcn_readfirstlane(d.tr.pair_nodes[l0 + li]);
+  // the part's units: a range of scenarios, and of the pair's nodes
+  const int len = d.tr.pair_ptr[q + 1] - d.tr.pair_ptr[q], sp = d.tr.sparts, np = d.tr.parts / sp;
+  const int ps = part % sp, pn = part / sp;
+  const int s0 = (int)((long long)d.N * ps / sp), ns = (int)((long long)d.N * (ps + 1) / sp) - s0;
+  const int l0 = d.tr.pair_ptr[q] + len * pn / np, l1 = d.tr.pair_ptr[q] + len * (pn + 1) / np;
+  const int units = (l1 - l0) * ns;
+  const int zero = (int)d.tr.zero;
+  auto unit = [&](int u) {
+    ProdUnit<T> r;
+    const int li = u / ns, node = d.tr.pair_nodes[l0 + li];
     const TreeNode& n = d.tr.nodes[node];
-    const int nb = n.nb, ib = n.ib;
-    const int ga = __builtin_amdgcn_readfirstlane(d.tr.gstrip[(long long)node * d.tr.ngroup + a]);
-    const int gb = __builtin_amdgcn_readfirstlane(d.tr.gstrip[(long long)node * d.tr.ngroup + b]);
-    const int ma = ga >> 16, mb = gb >> 16;
-    long long oa[T], ob[T];
+    const int ga = d.tr.gstrip[node * d.tr.ngroup + a], gb = d.tr.gstrip[node * d.tr.ngroup + b];
+    const int bs = n.nb * kTreeBlk, v0 = (int)n.v + n.ib * bs, y0 = (int)n.y + n.ib * bs;
+    r.slab = d.tr.slab + (s0 + u - li * ns) * d.tr.stride;
+    r.steps = 4 * n.nb;
 #pragma unroll
     for (int i = 0; i < T; ++i) {
-      oa[i] = (long long)(ib + (ga & 0xffff) + __popc(ma & ((1 << i) - 1))) * nb * kTreeBlk;
-      ob[i] = (long long)(ib + (gb & 0xffff) + __popc(mb & ((1 << i) - 1))) * nb * kTreeBlk;
+      const int ma = ga >> 16, mb = gb >> 16;
+      const int ka = ((ga & 0xffff) + __popc(ma & ((1 << i) - 1))) * bs;
+      const int kb = ((gb & 0xffff) + __popc(mb & ((1 << i) - 1))) * bs;
+      r.va[i] = ma >> i & 1 ? v0 + ka : zero;
+      r.ya[i] = ma >> i & 1 ? y0 + ka : zero;
+      r.vb[i] = mb >> i & 1 ? v0 + kb : zero;
+      r.yb[i] = mb >> i & 1 ? y0 + kb : zero;
     }
-    const long long ue = min(u1, (long long)(li + 1) * d.N);
-    const long long nv = n.v, ny = n.y;
-    for (; u < ue; ++u) {
-      const double* slab = d.tr.slab + (u - (long long)li * d.N) * d.tr.stride;
-      const double *v = slab + nv, *y = slab + ny;
-      for (int st = 0; st < 4 * nb; ++st) {
-        const int o = 64 * st + lane;
-        double va[T], ya[T], vb[T], yb[T];
-#pragma unroll
-        for (int i = 0; i < T; ++i) {
-          va[i] = ma >> i & 1 ? v[oa[i] + o] : 0.0;
-          ya[i] = ma >> i & 1 ? y[oa[i] + o] : 0.0;
-          vb[i] = mb >> i & 1 ? v[ob[i] + o] : 0.0;
-          yb[i] = mb >> i & 1 ? y[ob[i] + o] : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < T; ++i)
-#pragma unroll
-          for (int j = 0; j < T; ++j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], yb[j], acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ya[i], vb[j], acc[i][j], 0, 0, 0);
-          }
+    return r;
+  };
+  if (units > 0) {
+    ProdRegs<T> x, z;
+    ProdUnit<T> cur = unit(0);
+    prod_load<T>(x, cur, 0, lane);
+    for (int u = 0; u < units; ++u) {
+      const ProdUnit<T> nxt = unit(u + 1 < units ? u + 1 : u);
+      for (int st = 0; st < cur.steps; st += 2) {
+        prod_load<T>(z, cur, st + 1, lane);
+        prod_mul<T>(x, acc);
+        if (st + 2 < cur.steps) prod_load<T>(x, cur, st + 2, lane);
+        else prod_load<T>(x, nxt, 0, lane);
+        prod_mul<T>(z, acc);
       }
+      cur = nxt;
     }
   }
   const int lm = lane & 15, lk = lane >> 4, ld = d.tr.ngroup * T * kTreeB;
@@ -1082,8 +1121,8 @@ __global__ __launch_bounds__(kTF) void k_tree_front(DP d, int first) {
 }
 __global__ __launch_bounds__(kTT) void k_tree_cols(DP d, int first) { tree_cols_body(d, first + blockIdx.x, blockIdx.y); }
 template <int T>
-__global__ __launch_bounds__(kTT, 1) void k_tree_product(DP d) {
-  tree_product_body<T>(d, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(kTT, 2) void k_tree_product(DP d) {
+  tree_product_body<T>(d, blockIdx.x / d.tr.parts, blockIdx.x % d.tr.parts);
 }
 __global__ __launch_bounds__(kTT) void k_tree_sum(DP d, const double* su, double dw, double* khat) {
   tree_sum_body(d, blockIdx.x, blockIdx.y, su, dw, khat);
@@ -1191,7 +1230,7 @@ void launch_tree_reduce(const DP& d, hipStream_t s) {
 }
 
 void launch_tree_product(const DP& d, hipStream_t s) {
-  const dim3 grid(cdiv(d.tr.npair, 4), d.tr.parts);
+  const unsigned grid = cdiv(d.tr.npair, 4) * d.tr.parts;
   if (d.tr.T == 4) k_tree_product<4><<<grid, kTT, 0, s>>>(d);
   else k_tree_product<2><<<grid, kTT, 0, s>>>(d);
 }
@@ -1260,6 +1299,7 @@ void launches_tree(const DP& d, std::vector<Launch>& out) {
 }
 
 bool tree_fits(const Tree& t) {
+  if (t.stride >= 1ll << 31) return false;
   for (size_t l = 0; l + 1 < t.lev_ptr.size(); ++l)
     if (front_lds(t, (int)l) > (size_t)kFrontLdsMax) return false;
   return true;

@@ -402,9 +402,11 @@ std::string build_tree(const Sym& s, Tree& t) {
         t.kuu.push_back(e);
       }
 
-  // product over the control columns: 64 x 64 outputs per wavefront when
-  // that still gives enough wavefronts, else 32 x 32
-  t.T = t.nstrip >= 32 ? 4 : 2;
+  // product over the control columns: 64 x 64 outputs per wavefront (half the
+  // operand traffic) from 100 strips, else 32 x 32 (four times the
+  // wavefronts): at 64 strips x 8 scenarios 2170 against 2056 us per pass, at
+  // 33 strips x 8 1104 against 1056
+  t.T = t.nstrip >= 100 ? 4 : 2;
   t.ngroup = (t.nstrip + t.T - 1) / t.T;
   t.gstrip.assign((size_t)nn * t.ngroup, 0);
   std::vector<std::vector<int>> lists((size_t)t.ngroup * (t.ngroup + 1) / 2);
@@ -423,20 +425,32 @@ std::string build_tree(const Sym& s, Tree& t) {
       for (size_t b = 0; b <= a; ++b) lists[(size_t)gs[a] * (gs[a] + 1) / 2 + gs[b]].push_back(q);
   }
   t.pair_ptr.push_back(0);
-  for (int a = 0; a < t.ngroup; ++a)
-    for (int b = 0; b <= a; ++b) {
-      t.pair_g.push_back(a);
-      t.pair_g.push_back(b);
-      const auto& l = lists[(size_t)a * (a + 1) / 2 + b];
-      t.pair_nodes.insert(t.pair_nodes.end(), l.begin(), l.end());
-      t.pair_ptr.push_back((int)t.pair_nodes.size());
-    }
-  // parts of the contraction: about 4096 wavefronts, parts of at least one
-  // (node, scenario) each for the longest list, at most 32
+  for (int a2 = 0; a2 < t.ngroup; a2 += 2)
+    for (int b2 = 0; b2 <= a2; b2 += 2)
+      for (int w = 0; w < 4; ++w) {
+        const int a = a2 + w / 2, b = b2 + w % 2;
+        const bool in = a < t.ngroup && b <= a;
+        t.pair_g.push_back(in ? a : -1);
+        t.pair_g.push_back(in ? b : -1);
+        if (in) {
+          const auto& l = lists[(size_t)a * (a + 1) / 2 + b];
+          t.pair_nodes.insert(t.pair_nodes.end(), l.begin(), l.end());
+        }
+        t.pair_ptr.push_back((int)t.pair_nodes.size());
+      }
+  // parts of the contraction: about 8192 wavefronts, at most 32.  They split
+  // the scenarios (by eights where there are as many: workgroups go to the
+  // chip's eight dies in turn, so a part stays on one die, whose L2 holds its
+  // scenarios' fronts), then the lists of nodes.
   const long long npair = (long long)t.pair_g.size() / 2;
   long long longest = 1;
   for (const auto& l : lists) longest = std::max(longest, (long long)l.size());
-  t.parts = (int)std::max(1LL, std::min({32LL, longest * s.N, (4096 + npair - 1) / npair}));
+  const long long want = std::max(1LL, std::min(32LL, (8192 + npair - 1) / npair));
+  t.sparts = (int)std::min<long long>(s.N, want);
+  if (want >= 6 && s.N >= 8) t.sparts = std::min(s.N / 8, (int)(want + 4) / 8) * 8;
+  t.parts = t.sparts * (int)std::min(longest, std::max(1LL, want / t.sparts));
+  t.zero = t.stride;
+  t.stride += kTreeNB * kTreeBlk;
   return "";
 }
 

@@ -88,10 +88,13 @@ struct Tree {
   // K_uu entries of the lower triangle (user order): (row u, column u, K index)
   std::vector<int> kuu;
   // product over the control columns: groups of T strips; pair q = (ga, gb),
-  // gb <= ga, with the nodes pair_nodes[pair_ptr[q] ..) that touch both;
-  // gstrip[node * ngroup + g] = first strip index | mask << 16 (mask 0: none)
-  int T = 0, ngroup = 0, parts = 1;
+  // gb <= ga (four pairs of a workgroup share two groups on either side where
+  // they can; ga -1: none), with the nodes pair_nodes[pair_ptr[q] ..) that
+  // touch both; gstrip[node * ngroup + g] = first strip index | mask << 16
+  // (mask 0: none); zero: offset of kTreeNB blocks of zeros in the slab
+  int T = 0, ngroup = 0, parts = 1, sparts = 1;  // sparts: parts that split the scenarios
   std::vector<int> pair_g, pair_ptr, pair_nodes, gstrip;
+  long long zero = 0;
 };
 
 // The pivot kernel keeps the maps of a node's children in LDS up to this many
