@@ -688,7 +688,7 @@ __device__ __forceinline__ void tree_kuu_body(const DP& d, int bx, double* khat)
 //     y_J = -G_JJ^-T (Y_b + K_JJ x_J / 2 + Y_I x_I + Y_U p_u + G_IJ^T y_I),
 // so a step is one sweep up and one down; the products with the control
 // columns need no order and run over the whole chip.
-constexpr int kTS = 64 * kTreeStepWaves;  // threads of the sweeps
+constexpr int kTS = 64 * kTreeNB * kTreeStepNodes;  // threads of the sweeps
 
 // value summed over the lanes of a row of 16, in every lane
 __device__ __forceinline__ double sum16(double v) {
@@ -757,135 +757,177 @@ __device__ __forceinline__ void tree_resid_body(const DP& d, int bx, int k, cons
   }
 }
 
-// V_b and Y_b of one node by one wavefront; b: 2 x 64 doubles of LDS of its own
+// A node's block substitutions by one wavefront on a vector v of 64 in LDS,
+// with the node's block LU in registers: v <- G_JJ^-1 v.
 template <int NB>
-__device__ __forceinline__ void up_pivot(const DP& d, const TreeNode& n, int k, double* b, int lane) {
+__device__ __forceinline__ void pivot_solve(const v4d (&lu)[kTreeNB * kTreeNB], double* v, int lane) {
   const int lm = lane & 15, lk = lane >> 4;
-  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
-  double* vec = d.tr.vec + (long long)k * d.tr.vstride;
-  v4d lu[NB * NB];
-#pragma unroll
-  for (int q = 0; q < NB * NB; ++q) lu[q] = load_blk(slab + n.lu + q * kTreeBlk, lane);
-  // lane: padded pivot row
-  double b3 = 0.0, b1 = 0.0;
-  if (lane < n.s) {
-    const long long at = (long long)k * d.nx + d.tr.rows[n.row0 + lane];
-    b3 = d.qbuf[at];
-    b1 = d.rhat1[at];
-  }
-  if (lane < NB * kTreeB)
-    for (int a = 0; a < n.nchild; ++a) {
-      const TreeChild ch = d.tr.children[n.child0 + a];
-      const TreeNode& c = d.tr.nodes[ch.node];
-      const int ci = d.tr.rmap[ch.rmap0 + lane];
-      if (ci >= 0) {
-        const double* cv = vec + c.vec + 2 * kTreeB * c.nb + ci;
-        b3 += cv[0];
-        b1 += cv[kTreeB * c.ib];
-      }
-    }
-  b[lane] = b3;
-  wave_sync();
 #pragma unroll
   for (int p = 1; p < NB; ++p) {
     double acc = 0.0;
 #pragma unroll
-    for (int j = 0; j < p; ++j) acc = dot_rows(lu[p * NB + j], b + j * kTreeB, lk, acc);
+    for (int j = 0; j < p; ++j) acc = dot_rows(lu[p * NB + j], v + j * kTreeB, lk, acc);
     acc = sum_rows(acc);
-    if (lk == 0) b[p * kTreeB + lm] -= acc;
+    if (lk == 0) v[p * kTreeB + lm] -= acc;
     wave_sync();
   }
 #pragma unroll
   for (int p = NB - 1; p >= 0; --p) {
-    double acc = 0.0;
+    if (p + 1 < NB) {
+      double acc = 0.0;
 #pragma unroll
-    for (int j = p + 1; j < NB; ++j) acc = dot_rows(lu[p * NB + j], b + j * kTreeB, lk, acc);
-    acc = sum_rows(acc);
-    if (lk == 0) b[p * kTreeB + lm] -= acc;
+      for (int j = p + 1; j < NB; ++j) acc = dot_rows(lu[p * NB + j], v + j * kTreeB, lk, acc);
+      acc = sum_rows(acc);
+      if (lk == 0) v[p * kTreeB + lm] -= acc;
+      wave_sync();
+    }
+    const double acc = sum_rows(dot_rows(lu[p * NB + p], v + p * kTreeB, lk, 0.0));
     wave_sync();
-    acc = sum_rows(dot_rows(lu[p * NB + p], b + p * kTreeB, lk, 0.0));
+    if (lk == 0) v[p * kTreeB + lm] = acc;
     wave_sync();
-    if (lk == 0) b[p * kTreeB + lm] = acc;
-    wave_sync();
-  }
-  double* y = b + 64;
-  y[lane] = b1;
-  wave_sync();
-#pragma unroll
-  for (int p = 0; p < NB; ++p) {
-    double acc = 0.0;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      acc = dot_rows(load_blk(slab + n.kjj + (j * NB + p) * kTreeBlk, lane), b + j * kTreeB, lk, acc);
-    acc = sum_rows(acc);
-    if (lk == 0) y[p * kTreeB + lm] = fma(-0.5, acc, y[p * kTreeB + lm]);
-  }
-  wave_sync();
-  if (lane < NB * kTreeB) {
-    vec[n.vec + lane] = b[lane];
-    vec[n.vec + NB * kTreeB + lane] = y[lane];
   }
 }
 
-// Sweep up over the levels [l0, l1): a node's V_b and Y_b by one wavefront,
-// then its interface strips, one wavefront each.  Workgroup bx of gx takes
-// every gx-th node of a level (gx > 1 for one level only).
+// v <- G_JJ^-T v; s: 16 doubles of LDS
+template <int NB>
+__device__ __forceinline__ void pivot_solve_t(const v4d (&lu)[kTreeNB * kTreeNB], double* v, double* s, int lane) {
+  const int lm = lane & 15;
+#pragma unroll
+  for (int p = 0; p < NB; ++p) {
+    if (p > 0) {
+      v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int j = 0; j < p; ++j) dot_cols(lu[j * NB + p], -v[j * kTreeB + lm], acc);
+      put_rows(acc, s, lane);
+      wave_sync();
+      if (lane < kTreeB) v[p * kTreeB + lane] += s[lane];
+      wave_sync();
+    }
+    v4d z = {0.0, 0.0, 0.0, 0.0};
+    dot_cols(lu[p * NB + p], v[p * kTreeB + lm], z);
+    wave_sync();
+    put_rows(z, v + p * kTreeB, lane);
+    wave_sync();
+  }
+#pragma unroll
+  for (int p = NB - 2; p >= 0; --p) {
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = p + 1; j < NB; ++j) dot_cols(lu[j * NB + p], -v[j * kTreeB + lm], acc);
+    put_rows(acc, s, lane);
+    wave_sync();
+    if (lane < kTreeB) v[p * kTreeB + lane] += s[lane];
+    wave_sync();
+  }
+}
+
+__device__ __forceinline__ void load_lu(v4d (&lu)[kTreeNB * kTreeNB], const double* p, int nbb, int lane) {
+#pragma unroll
+  for (int q = 0; q < kTreeNB * kTreeNB; ++q)
+    if (q < nbb) lu[q] = load_blk(p + q * kTreeBlk, lane);
+}
+
+// Sweep up over the levels [l0, l1): workgroup bx of gx takes kTreeStepNodes
+// nodes at a time, kTreeNB wavefronts each: right-hand sides by block rows,
+// V_b by the first wavefront (its LU loads issued first), Y_b by block rows,
+// the interface strips dealt to the wavefronts.  gx > 1 for one level only.
+// Bound by the latency of each step of the chain.
 __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k, int l0, int l1) {
-  __shared__ double sb[kTreeStepWaves][2 * 64];
+  __shared__ double s3[kTreeStepNodes][kTreeRows], s1[kTreeStepNodes][kTreeRows];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lm = lane & 15, lk = lane >> 4;
+  const int lm = lane & 15, lk = lane >> 4, grp = wv / kTreeNB, p = wv % kTreeNB;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
   double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  double *b3 = s3[grp], *b1 = s1[grp];
   for (int l = l0; l < l1; ++l) {
     const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
-    for (int q = q0 + bx + wv * gx; q < q1; q += kTreeStepWaves * gx) {
-      const TreeNode n = d.tr.nodes[d.tr.lev_nodes[q]];
-      switch (n.nb) {
-        case 1: up_pivot<1>(d, n, k, sb[wv], lane); break;
-        case 2: up_pivot<2>(d, n, k, sb[wv], lane); break;
-        case 3: up_pivot<3>(d, n, k, sb[wv], lane); break;
-        default: up_pivot<4>(d, n, k, sb[wv], lane); break;
-      }
-    }
-    __syncthreads();
-    int turn = wv;  // strips of the workgroup's nodes, dealt out in turn
-    for (int q = q0 + bx; q < q1; q += gx) {
-      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[q]];
+    for (int qq = q0 + bx * kTreeStepNodes; qq < q1; qq += gx * kTreeStepNodes) {
+      const bool act = qq + grp < q1;
+      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[min(qq + grp, q1 - 1)]];
       const int nb = n.nb, ib = n.ib;
-      int m = turn;
-      for (; m < ib; m += kTreeStepWaves) {
-        const double *vb = vec + n.vec, *yb = vb + nb * kTreeB;
+      const bool row = act && p < nb;
+      v4d lu[kTreeNB * kTreeNB], kr[kTreeNB];
+      if (act && p == 0) load_lu(lu, slab + n.lu, nb * nb, lane);
+      if (row)
+#pragma unroll
+        for (int j = 0; j < kTreeNB; ++j)
+          if (j < nb) kr[j] = load_blk(slab + n.kjj + (j * nb + p) * kTreeBlk, lane);
+      double* nv = vec + n.vec;
+      if (row && lane < kTreeB) {
+        const int r = p * kTreeB + lane;
         double a3 = 0.0, a1 = 0.0;
-        for (int p = 0; p < nb; ++p) {
-          const long long at = (long long)(m * nb + p) * kTreeBlk;
-          const v4d g = load_blk(slab + n.gijt + at, lane), v = load_blk(slab + n.v + at, lane),
-                    y = load_blk(slab + n.y + at, lane);
-          a3 = dot_rows(g, vb + p * kTreeB, lk, a3);
-          a1 = dot_rows(v, yb + p * kTreeB, lk, a1);
-          a1 = dot_rows(y, vb + p * kTreeB, lk, a1);
+        if (r < n.s) {
+          const long long at = (long long)k * d.nx + d.tr.rows[n.row0 + r];
+          a3 = d.qbuf[at];
+          a1 = d.rhat1[at];
         }
-        a3 = -sum_rows(a3);
-        a1 = -sum_rows(a1);
-        const int row = (nb + m) * kTreeB + lm;
         for (int a = 0; a < n.nchild; ++a) {
-          const TreeChild ch = d.tr.children[n.child0 + a];
-          const TreeNode& c = d.tr.nodes[ch.node];
-          const int ci = d.tr.rmap[ch.rmap0 + row];
+          const TreeChild& ch = d.tr.children[n.child0 + a];
+          const int ci = d.tr.rmap[n.rmap0 + a * kTreeB * (nb + ib) + r];
           if (ci >= 0) {
-            const double* cv = vec + c.vec + 2 * kTreeB * c.nb + ci;
+            const double* cv = vec + ch.vec + 2 * kTreeB * ch.nb + ci;
             a3 += cv[0];
-            a1 += cv[kTreeB * c.ib];
+            a1 += cv[kTreeB * ch.ib];
           }
         }
+        b3[r] = a3;
+        b1[r] = a1;
+      }
+      __syncthreads();
+      if (act && p == 0) {
+        switch (nb) {
+          case 1: pivot_solve<1>(lu, b3, lane); break;
+          case 2: pivot_solve<2>(lu, b3, lane); break;
+          case 3: pivot_solve<3>(lu, b3, lane); break;
+          default: pivot_solve<4>(lu, b3, lane); break;
+        }
+        if (lane < nb * kTreeB) nv[lane] = b3[lane];
+      }
+      __syncthreads();
+      if (row) {
+        double acc = 0.0;
+#pragma unroll
+        for (int j = 0; j < kTreeNB; ++j)
+          if (j < nb) acc = dot_rows(kr[j], b3 + j * kTreeB, lk, acc);
+        acc = sum_rows(acc);
         if (lk == 0) {
-          double* o = vec + n.vec + 2 * kTreeB * nb + m * kTreeB + lm;
-          o[0] = a3;
-          o[kTreeB * ib] = a1;
+          const double y = fma(-0.5, acc, b1[p * kTreeB + lm]);
+          b1[p * kTreeB + lm] = y;
+          nv[nb * kTreeB + p * kTreeB + lm] = y;
         }
       }
-      turn = m - ib;
+      __syncthreads();
+      if (act)
+        for (int m = p; m < ib; m += kTreeNB) {
+          double a3 = 0.0, a1 = 0.0;
+          for (int j = 0; j < nb; ++j) {
+            const long long at = (long long)(m * nb + j) * kTreeBlk;
+            const v4d g = load_blk(slab + n.gijt + at, lane), v = load_blk(slab + n.v + at, lane),
+                      y = load_blk(slab + n.y + at, lane);
+            a3 = dot_rows(g, b3 + j * kTreeB, lk, a3);
+            a1 = dot_rows(v, b1 + j * kTreeB, lk, a1);
+            a1 = dot_rows(y, b3 + j * kTreeB, lk, a1);
+          }
+          a3 = -sum_rows(a3);
+          a1 = -sum_rows(a1);
+          const int r = (nb + m) * kTreeB + lm;
+          for (int a = 0; a < n.nchild; ++a) {
+            const TreeChild& ch = d.tr.children[n.child0 + a];
+            const int ci = d.tr.rmap[n.rmap0 + a * kTreeB * (nb + ib) + r];
+            if (ci >= 0) {
+              const double* cv = vec + ch.vec + 2 * kTreeB * ch.nb + ci;
+              a3 += cv[0];
+              a1 += cv[kTreeB * ch.ib];
+            }
+          }
+          if (lk == 0) {
+            double* o = nv + 2 * kTreeB * nb + m * kTreeB + lm;
+            o[0] = a3;
+            o[kTreeB * ib] = a1;
+          }
+        }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -965,126 +1007,100 @@ __device__ __forceinline__ void tree_rec_u_body(const DP& d, int job, int k, con
   }
 }
 
-// y_J = -G_JJ^-T t of one node by one wavefront; t: 64 doubles of LDS
-template <int NB>
-__device__ __forceinline__ void down_pivot(const DP& d, const TreeNode& n, int k, double* t, double* py, int lane) {
-  const double* slab = d.tr.slab + (long long)k * d.tr.stride;
-  const int lm = lane & 15;
-  v4d lu[NB * NB];
-#pragma unroll
-  for (int q = 0; q < NB * NB; ++q) lu[q] = load_blk(slab + n.lu + q * kTreeBlk, lane);
-#pragma unroll
-  for (int p = 0; p < NB; ++p) {
-    v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int j = 0; j < p; ++j) dot_cols(lu[j * NB + p], -t[j * kTreeB + lm], acc);
-    if (p > 0) {
-      double* s = t + 64;
-      put_rows(acc, s, lane);
-      wave_sync();
-      if (lane < kTreeB) t[p * kTreeB + lane] += s[lane];
-      wave_sync();
-    }
-    v4d z = {0.0, 0.0, 0.0, 0.0};
-    dot_cols(lu[p * NB + p], t[p * kTreeB + lm], z);
-    wave_sync();
-    put_rows(z, t + p * kTreeB, lane);
-    wave_sync();
-  }
-#pragma unroll
-  for (int p = NB - 2; p >= 0; --p) {
-    v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int j = p + 1; j < NB; ++j) dot_cols(lu[j * NB + p], -t[j * kTreeB + lm], acc);
-    double* s = t + 64;
-    put_rows(acc, s, lane);
-    wave_sync();
-    if (lane < kTreeB) t[p * kTreeB + lane] += s[lane];
-    wave_sync();
-  }
-  if (lane < n.s) {
-    const int row = d.tr.rows[n.row0 + lane];
-    const double v = -t[lane];
-    d.tr.y[(long long)k * d.nx + row] = v;
-    py[(long long)k * d.nx + d.perm[row]] = v;
-  }
-}
-
-// Sweep down over the levels l1 - 1 .. l0, split over workgroups like the
-// sweep up: x_J, then the right-hand side of y_J (both by pivot block rows,
-// one wavefront each), then y_J by one wavefront.
+// Sweep down over the levels l1 - 1 .. l0, workgroups and wavefronts as in the
+// sweep up: x_J and the right-hand side of y_J by block rows, y_J by the
+// node's first wavefront.  Every load that does not wait for the node's own
+// x_J is issued before the first barrier.
 __device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int k, int l0, int l1, double* px,
                                                double* py) {
-  __shared__ double sb[kTreeStepWaves][80];
+  __shared__ double sx[kTreeStepNodes][kTreeRows], st[kTreeStepNodes][kTreeRows + kTreeB];
+  __shared__ double sr[kTreeStepNodes * kTreeNB][2 * kTreeB];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lm = lane & 15;
+  const int lm = lane & 15, grp = wv / kTreeNB, p = wv % kTreeNB;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
-  double* vec = d.tr.vec + (long long)k * d.tr.vstride;
+  const double* vec = d.tr.vec + (long long)k * d.tr.vstride;
   double* xk = d.tr.x + (long long)k * d.nx;
   double* yk = d.tr.y + (long long)k * d.nx;
-  const double* up = d.tr.upart + (long long)k * d.tr.ncjob * 2 * kTreeRows;
+  double *xs = sx[grp], *ts = st[grp], *red = sr[wv];
   for (int l = l1 - 1; l >= l0; --l) {
     const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
-    for (int ph = 0; ph < 2; ++ph) {
-      int turn = wv;
-      for (int q = q0 + bx; q < q1; q += gx) {
-        const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[q]];
-        const int nb = n.nb, ib = n.ib;
-        int p = turn;
-        for (; p < nb; p += kTreeStepWaves) {
-          v4d acc = {0.0, 0.0, 0.0, 0.0};
-          const double* blk = slab + (ph ? n.y : n.v);
-          for (int m = 0; m < ib; ++m) {
-            const int j = m * kTreeB + lm;
-            const int row = j < n.i ? d.tr.rows[n.row0 + n.s + j] : -1;
-            const double x = row >= 0 ? xk[row] : 0.0;
-            dot_cols(load_blk(blk + (long long)(m * nb + p) * kTreeBlk, lane), x, acc);
-            if (ph) {
-              const double y = row >= 0 ? yk[row] : 0.0;
-              dot_cols(load_blk(slab + n.gijt + (long long)(m * nb + p) * kTreeBlk, lane), y, acc);
-            }
+    for (int qq = q0 + bx * kTreeStepNodes; qq < q1; qq += gx * kTreeStepNodes) {
+      const bool act = qq + grp < q1;
+      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[min(qq + grp, q1 - 1)]];
+      const int nb = n.nb, ib = n.ib;
+      const bool row = act && p < nb;
+      v4d lu[kTreeNB * kTreeNB], kr[kTreeNB], t = {0.0, 0.0, 0.0, 0.0};
+      double base = 0.0;
+      if (row) {
+#pragma unroll
+        for (int j = 0; j < kTreeNB; ++j)
+          if (j < nb) kr[j] = load_blk(slab + n.kjj + (p * nb + j) * kTreeBlk, lane);
+        double bx0 = 0.0;
+        int at = 0;
+        if (lane < kTreeB) {
+          const double* up = d.tr.upart + ((long long)k * d.tr.ncjob + n.cjob0) * 2 * kTreeRows + p * kTreeB + lane;
+          bx0 = vec[n.vec + p * kTreeB + lane];
+          base = vec[n.vec + nb * kTreeB + p * kTreeB + lane];
+          for (int c = 0; c < n.ncjob; ++c) {
+            bx0 += up[c * 2 * kTreeRows];
+            base += up[(c * 2 + 1) * kTreeRows];
           }
-          if (ph)
-            for (int j = 0; j < nb; ++j) {
-              const int at = j * kTreeB + lm;
-              const double x = at < n.s ? 0.5 * xk[d.tr.rows[n.row0 + at]] : 0.0;
-              dot_cols(load_blk(slab + n.kjj + (long long)(p * nb + j) * kTreeBlk, lane), x, acc);
-            }
-          put_rows(acc, sb[wv], lane);
-          wave_sync();
-          if (lane < kTreeB) {
-            double v = sb[wv][lane];
-            double* o = vec + n.vec + ph * nb * kTreeB + p * kTreeB + lane;
-            v += *o;
-            for (int c = 0; c < n.ncjob; ++c) v += up[((long long)(n.cjob0 + c) * 2 + ph) * kTreeRows + p * kTreeB + lane];
-            const int at = p * kTreeB + lane;
-            if (ph) {
-              *o = v;  // Y_b becomes the right-hand side of y_J
-            } else if (at < n.s) {
-              const int row = d.tr.rows[n.row0 + at];
-              xk[row] = -v;
-              px[(long long)k * d.nx + d.perm[row]] = -v;
-            }
-          }
-          wave_sync();
+          at = p * kTreeB + lane < n.s ? d.tr.rows[n.row0 + p * kTreeB + lane] : -1;
         }
-        turn = p - nb;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+        for (int m = 0; m < ib; ++m) {
+          const int j = m * kTreeB + lm;
+          const long long o = (long long)(m * nb + p) * kTreeBlk;
+          const v4d bv = load_blk(slab + n.v + o, lane), by = load_blk(slab + n.y + o, lane),
+                    bg = load_blk(slab + n.gijt + o, lane);
+          double x = 0.0, y = 0.0;
+          if (j < n.i) {
+            const int r = d.tr.rows[n.row0 + n.s + j];
+            x = xk[r];
+            y = yk[r];
+          }
+          dot_cols(bv, x, acc);
+          dot_cols(by, x, t);
+          dot_cols(bg, y, t);
+        }
+        if (p == 0) load_lu(lu, slab + n.lu, nb * nb, lane);
+        put_rows(acc, red, lane);
+        wave_sync();
+        if (lane < kTreeB) {
+          const double x = at >= 0 ? -(bx0 + red[lane]) : 0.0;
+          xs[p * kTreeB + lane] = x;
+          if (at >= 0) {
+            xk[at] = x;
+            px[(long long)k * d.nx + d.perm[at]] = x;
+          }
+        }
+      }
+      __syncthreads();
+      if (row) {
+#pragma unroll
+        for (int j = 0; j < kTreeNB; ++j)
+          if (j < nb) dot_cols(kr[j], 0.5 * xs[j * kTreeB + lm], t);
+        put_rows(t, red, lane);
+        wave_sync();
+        if (lane < kTreeB) ts[p * kTreeB + lane] = base + red[lane];
+      }
+      __syncthreads();
+      if (act && p == 0) {
+        switch (nb) {
+          case 1: pivot_solve_t<1>(lu, ts, ts + kTreeRows, lane); break;
+          case 2: pivot_solve_t<2>(lu, ts, ts + kTreeRows, lane); break;
+          case 3: pivot_solve_t<3>(lu, ts, ts + kTreeRows, lane); break;
+          default: pivot_solve_t<4>(lu, ts, ts + kTreeRows, lane); break;
+        }
+        if (lane < n.s) {
+          const int r = d.tr.rows[n.row0 + lane];
+          const double v = -ts[lane];
+          yk[r] = v;
+          py[(long long)k * d.nx + d.perm[r]] = v;
+        }
       }
       __syncthreads();
     }
-    for (int q = q0 + bx + wv * gx; q < q1; q += kTreeStepWaves * gx) {
-      const TreeNode n = d.tr.nodes[d.tr.lev_nodes[q]];
-      if (lane < n.nb * kTreeB) sb[wv][lane] = vec[n.vec + n.nb * kTreeB + lane];
-      wave_sync();
-      switch (n.nb) {
-        case 1: down_pivot<1>(d, n, k, sb[wv], py, lane); break;
-        case 2: down_pivot<2>(d, n, k, sb[wv], py, lane); break;
-        case 3: down_pivot<3>(d, n, k, sb[wv], py, lane); break;
-        default: down_pivot<4>(d, n, k, sb[wv], py, lane); break;
-      }
-      wave_sync();
-    }
-    __syncthreads();
   }
 }
 
@@ -1241,7 +1257,7 @@ void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hip
 }
 
 // workgroups per scenario of a level's part of a sweep
-static int wide_groups(const Tree& t, int l) { return (int)cdiv(t.lev_ptr[l + 1] - t.lev_ptr[l], kTreeStepWaves); }
+static int wide_groups(const Tree& t, int l) { return (int)cdiv(t.lev_ptr[l + 1] - t.lev_ptr[l], kTreeStepNodes); }
 
 void launch_tree_rhs(const DP& d, const double* r1x, const double* r2, const double* r3, const double* r4,
                      const double* ss, hipStream_t s) {

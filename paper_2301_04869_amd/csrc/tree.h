@@ -106,8 +106,9 @@ std::string build_tree(const Sym& s, Tree& t);
 
 // Levels whose nodes are spread over several workgroups per scenario in the
 // step's sweeps (one launch each): the first levels, while they hold more
-// than kTreeWide nodes.  The rest run in one workgroup per scenario.
-constexpr int kTreeWide = 32, kTreeStepWaves = 8;
+// than kTreeWide nodes.  The rest run in one workgroup per scenario, which
+// takes kTreeStepNodes nodes at a time, kTreeNB wavefronts each.
+constexpr int kTreeWide = 4, kTreeStepNodes = 2;
 int tree_wide_levels(const Tree& t);
 
 }  // namespace rkkt
