@@ -120,60 +120,80 @@ __device__ __forceinline__ Kids kids_global(const DP& d, const TreeNode& n) {
               kTreeB * (n.nb + n.ib),   n.us};
 }
 
-// Adds the children's updates to the blocks of rows row0 .. of G_.U and K_.U
-// in control strip c.  Two children's loads are in flight together.
-__device__ __forceinline__ void add_ctrl(const Kids& kd, const double* slab, int row0, int c, int lane, v4d& g,
-                                         v4d& kk) {
+// whether child c maps rows into the parent's block row b
+__device__ __forceinline__ bool kid_has(const TreeChild& c, int b) {
+  const unsigned long long m = c.blocks >> min(b, 63);
+  return __builtin_amdgcn_readfirstlane((int)(m & 1)) != 0;
+}
+
+// Adds the children's updates to the NB blocks of rows from block row rb on of
+// G_.U and K_.U in control strip c.  Only children that hold the strip are
+// visited, and of those only the block rows that they map; all loads of a
+// child are in flight together.
+template <int NB>
+__device__ __forceinline__ void add_ctrl(const Kids& kd, const double* slab, int rb, int c, int lane, v4d* g,
+                                         v4d* kk) {
   const int lm = lane & 15, lk = lane >> 4;
-  for (int a0 = 0; a0 < kd.n; a0 += 2) {
-    v4d vg[2], vk[2];
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      const int a = min(a0 + w, kd.n - 1);
-      const int cst = a0 + w < kd.n ? kd.smap[a * kd.us + c] : -1;
-      const short* rm = kd.map + a * kd.len;
-      const int ib = kd.ch[a].ib;
+  for (int a0 = 0; a0 < kd.n; a0 += 64) {
+    const int cstv = a0 + lane < kd.n ? kd.smap[(a0 + lane) * kd.us + c] : -1;
+    for (unsigned long long m = __ballot(cstv >= 0); m; m &= m - 1) {
+      const int w = __ffsll((long long)m) - 1, a = a0 + w;
+      const TreeChild& ch = kd.ch[a];
+      const int cst = __builtin_amdgcn_readlane(cstv, w), ib = ch.ib;
+      const short* rm = kd.map + a * kd.len + rb * kTreeB;
       const long long so = (long long)(ib + cst) * ib * kTreeBlk + lm;
-      const long long gu = kd.ch[a].gu + so, ku = kd.ch[a].ku + so;
+      const double *gu = slab + ch.gu + so, *ku = slab + ch.ku + so;
+      v4d vg[NB], vk[NB];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int ci = rm[row0 + 4 * r + lk];
-        const bool in = ci >= 0 && cst >= 0;
-        vg[w][r] = in ? slab[gu + ci * kTreeB] : 0.0;
-        vk[w][r] = in ? slab[ku + ci * kTreeB] : 0.0;
+      for (int b = 0; b < NB; ++b) {
+        vg[b] = vk[b] = v4d{0.0, 0.0, 0.0, 0.0};
+        if (kid_has(ch, rb + b))
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int ci = rm[b * kTreeB + 4 * r + lk];
+            vg[b][r] = ci >= 0 ? gu[ci * kTreeB] : 0.0;
+            vk[b][r] = ci >= 0 ? ku[ci * kTreeB] : 0.0;
+          }
       }
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          g[b][r] += vg[b][r];
+          kk[b][r] += vk[b][r];
+        }
     }
-#pragma unroll
-    for (int w = 0; w < 2; ++w)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        g[r] += vg[w][r];
-        kk[r] += vk[w][r];
-      }
   }
 }
 
 // Adds the children's updates to one block whose rows and columns are both
-// interface-mapped: element (row, col) of the parent (padded places row0 +
-// 4 r + lane/16, col0 + lane%16).  kG / kK: to g from G_IC, to kk from K_IC;
+// interface-mapped: element (row, col) of the parent, rows of block row rb,
+// columns those of block row cb.  kG / kK: to g from G_IC, to kk from K_IC;
 // kT: the block holds the transpose, element (row, col) taken from the
-// child's (col, row).  Two children's loads are in flight together.
+// child's (col, row).  Children that map nothing into the block are skipped;
+// the loads of two children are in flight together.
 template <bool kT, bool kG, bool kK>
-__device__ __forceinline__ void add_mapped(const Kids& kd, const double* slab, int row0, int col0, int lane, v4d& g,
+__device__ __forceinline__ void add_mapped(const Kids& kd, const double* slab, int rb, int cb, int lane, v4d& g,
                                            v4d& kk) {
   const int lm = lane & 15, lk = lane >> 4;
-  for (int a0 = 0; a0 < kd.n; a0 += 2) {
+  auto next = [&](int a) {
+    while (a < kd.n && !(kid_has(kd.ch[a], rb) && kid_has(kd.ch[a], cb))) ++a;
+    return a;
+  };
+  for (int a0 = next(0); a0 < kd.n;) {
+    int a1 = next(a0 + 1);
     v4d vg[2], vk[2];
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
-      const int a = min(a0 + w, kd.n - 1);
+      const int a = w == 0 ? a0 : min(a1, kd.n - 1);
+      const TreeChild& ch = kd.ch[a];
       const short* rm = kd.map + a * kd.len;
-      const int cj = a0 + w < kd.n ? rm[col0 + lm] : -1;
-      const long long gu = kd.ch[a].gu, ku = kd.ch[a].ku;
-      const int pitch = kd.ch[a].ib * kTreeBlk;
+      const int cj = w == 0 || a1 < kd.n ? rm[cb * kTreeB + lm] : -1;
+      const long long gu = ch.gu, ku = ch.ku;
+      const int pitch = ch.ib * kTreeBlk;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int ci = rm[row0 + 4 * r + lk];
+        const int ci = rm[rb * kTreeB + 4 * r + lk];
         const bool in = ci >= 0 && cj >= 0;
         const int rr = kT ? cj : ci, cc = kT ? ci : cj;
         const long long at = in ? (long long)(cc >> 4) * pitch + rr * kTreeB + (cc & 15) : 0;
@@ -188,6 +208,7 @@ __device__ __forceinline__ void add_mapped(const Kids& kd, const double* slab, i
         if (kG) g[r] += vg[w][r];
         if (kK) kk[r] += vk[w][r];
       }
+    a0 = a1 < kd.n ? next(a1 + 1) : kd.n;
   }
 }
 
@@ -328,9 +349,8 @@ __device__ __forceinline__ void update_block(const TreeNode& n, const Kids& kd, 
                                              int lane) {
   const int nb = n.nb;
   v4d ga = {0.0, 0.0, 0.0, 0.0}, ka = {0.0, 0.0, 0.0, 0.0};
-  const int row0 = (nb + m) * kTreeB;
-  if (strip >= n.ib) add_ctrl(kd, slab, row0, strip - n.ib, lane, ga, ka);
-  else add_mapped<false, true, true>(kd, slab, row0, (nb + strip) * kTreeB, lane, ga, ka);
+  if (strip >= n.ib) add_ctrl<1>(kd, slab, nb + m, strip - n.ib, lane, &ga, &ka);
+  else add_mapped<false, true, true>(kd, slab, nb + m, nb + strip, lane, ga, ka);
   const double *gt = slab + n.gijt + (long long)m * nb * kTreeBlk, *vm = slab + n.v + (long long)m * nb * kTreeBlk,
                *ym = slab + n.y + (long long)m * nb * kTreeBlk, *vs = slab + n.v + (long long)strip * nb * kTreeBlk,
                *ys = slab + n.y + (long long)strip * nb * kTreeBlk;
@@ -396,7 +416,7 @@ __device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
   for (int b = wv; b < nbb; b += kW) {
     const int rb = b / nb, cb = b % nb;
     v4d g = pool_blk(pool, so[b], lane), kk = pool_blk(pool, so[nbb + b], lane);
-    add_mapped<false, true, true>(kd, slab, rb * kTreeB, cb * kTreeB, lane, g, kk);
+    add_mapped<false, true, true>(kd, slab, rb, cb, lane, g, kk);
     store_blk(slab + n.kjj + b * kTreeBlk, kk, lane);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -413,13 +433,13 @@ __device__ __forceinline__ void tree_front_body(const DP& d, int node, int k) {
       v4d g = pool_blk(pool, so[2 * nbb + b], lane), kk = {0.0, 0.0, 0.0, 0.0};
       if (b < ib * nb) {
         const int ist = b / nb, kb = b % nb;
-        add_mapped<true, true, false>(kd, slab, kb * kTreeB, (nb + ist) * kTreeB, lane, g, kk);
+        add_mapped<true, true, false>(kd, slab, kb, nb + ist, lane, g, kk);
         store_blk(slab + n.gijt + b * kTreeBlk, g, lane);
       } else {
         const int q = b - ib * nb, ist = q / nb, kb = q % nb;
         kk = pool_blk(pool, so[nfix + nst + q], lane);
-        if (kAll && ist >= ib) add_ctrl(kd, slab, kb * kTreeB, ist - ib, lane, g, kk);
-        else add_mapped<false, true, true>(kd, slab, kb * kTreeB, (nb + ist) * kTreeB, lane, g, kk);
+        if (kAll && ist >= ib) add_ctrl<1>(kd, slab, kb, ist - ib, lane, &g, &kk);
+        else add_mapped<false, true, true>(kd, slab, kb, nb + ist, lane, g, kk);
         store_blk(slab + n.v + q * kTreeBlk, g, lane);
         store_blk(slab + n.y + q * kTreeBlk, kk, lane);
       }
@@ -476,8 +496,7 @@ __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, doubl
       g[k] = pool_blk(pool, d.tr.orig[v0 + k], lane);
       kj[k] = pool_blk(pool, d.tr.orig[v0 + n.cs * NB + k], lane);
     }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) add_ctrl(kd, slab, k * kTreeB, strip - n.ib, lane, g[k], kj[k]);
+    add_ctrl<NB>(kd, slab, 0, strip - n.ib, lane, g, kj);
     const double* lu = slab + n.lu;
     strip_solve<NB>(
         n, slab, [&](int r, int c) { return load_blk(lu + (r * NB + c) * kTreeBlk, lane); }, lane, g, kj);
@@ -494,16 +513,21 @@ __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, doubl
     }
   }
   for (int m = 0; m < n.ib; ++m) {
-    v4d ga = {0.0, 0.0, 0.0, 0.0}, ka = {0.0, 0.0, 0.0, 0.0};
-    const int row0 = (NB + m) * kTreeB;
-    if (ctrl) add_ctrl(kd, slab, row0, strip - n.ib, lane, ga, ka);
-    else add_mapped<false, true, true>(kd, slab, row0, (NB + strip) * kTreeB, lane, ga, ka);
+    v4d ga = {0.0, 0.0, 0.0, 0.0}, ka = {0.0, 0.0, 0.0, 0.0}, bg[NB], bv[NB], by[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const long long at = (long long)(m * NB + k) * kTreeBlk;
-      ga = mul_sub(load_blk(slab + n.gijt + at, lane), g[k], ga);
-      ka = mul_sub(load_blk(slab + n.v + at, lane), kj[k], ka);
-      ka = mul_sub(load_blk(slab + n.y + at, lane), g[k], ka);
+      bg[k] = load_blk(slab + n.gijt + at, lane);
+      bv[k] = load_blk(slab + n.v + at, lane);
+      by[k] = load_blk(slab + n.y + at, lane);
+    }
+    if (ctrl) add_ctrl<1>(kd, slab, NB + m, strip - n.ib, lane, &ga, &ka);
+    else add_mapped<false, true, true>(kd, slab, NB + m, NB + strip, lane, ga, ka);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      ga = mul_sub(bg[k], g[k], ga);
+      ka = mul_sub(bv[k], kj[k], ka);
+      ka = mul_sub(by[k], g[k], ka);
     }
     const long long o = ((long long)strip * n.ib + m) * kTreeBlk;
     store_blk(slab + n.gu + o, ga, lane);
@@ -513,7 +537,7 @@ __device__ __forceinline__ void tree_strip(const DP& d, const TreeNode& n, doubl
 
 __device__ __forceinline__ void tree_cols_body(const DP& d, int job, int k) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const TreeNode n = d.tr.nodes[d.tr.jobs[2 * job]];
+  const TreeNode& n = d.tr.nodes[d.tr.jobs[2 * job]];
   const int strip = d.tr.jobs[2 * job + 1] + wv;
   if (strip >= n.cs) return;
   double* slab = d.tr.slab + (long long)k * d.tr.stride;

@@ -230,7 +230,7 @@ std::string build_tree(const Sym& s, Tree& t) {
     for (int u : own[q]) hit[t.upos[u] / kTreeB] = 1;
     for (int c0 : kids[post[q]]) {
       const int c = where[c0];
-      t.children.push_back({c, 0, 0, t.nodes[c].ib, t.nodes[c].nb, t.nodes[c].vec, t.nodes[c].gu, t.nodes[c].ku});
+      t.children.push_back({c, 0, 0, t.nodes[c].ib, t.nodes[c].nb, t.nodes[c].vec, t.nodes[c].gu, t.nodes[c].ku, 0});
       n.level = std::max(n.level, t.nodes[c].level + 1);
       for (int z : strips[c]) hit[z] = 1;
     }
@@ -284,6 +284,7 @@ std::string build_tree(const Sym& s, Tree& t) {
         const int r = place(n, erows[c.row0 + c.s + j]);
         if (r < 0) return "internal: interface row of a front missing from its parent";
         t.rmap[ch.rmap0 + r] = (short)j;
+        ch.blocks |= 1ull << std::min(63, r / kTreeB);
       }
       ch.smap0 = (int)t.smap.size();
       for (int z : strips[q]) {

@@ -54,11 +54,13 @@ struct TreeNode {
 // index of the parent's padded row r (pivot block rows, then interface block
 // rows) or -1; smap[smap0 + t] the child's control strip of the parent's
 // control strip t or -1.  The children of a node have their maps one after the
-// other.  ib, nb, vec, gu, ku: the child's own.
+// other.  blocks: bit b (63 for all beyond) set where a row of the
+// parent's padded block row b is mapped.  ib, nb, vec, gu, ku: the child's own.
 struct TreeChild {
   int node, rmap0, smap0;
   int ib, nb, vec;
   long long gu, ku;
+  unsigned long long blocks;
 };
 
 struct Tree {
