@@ -115,20 +115,6 @@ hipError_t upload_sched(rkkt_problem* p, const rkkt::Sched& sc, bool packed, con
   return e;
 }
 
-// Runs `launch` between two events on `stream` when profiling is on.
-template <typename F>
-void stage(rkkt_problem* p, int id, hipStream_t stream, F&& launch) {
-  if (!p->prof || 2 * (p->rec_used + 1) > p->events.size()) {
-    launch();
-    return;
-  }
-  size_t r = p->rec_used++;
-  (void)hipEventRecord(p->events[2 * r], stream);
-  launch();
-  (void)hipEventRecord(p->events[2 * r + 1], stream);
-  p->rec_stage[r] = id;
-}
-
 int check_launch(rkkt_problem* p, const char* where) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(p, e, where);
@@ -1127,6 +1113,7 @@ int rkkt_destroy(rkkt_problem* p) {
   for (hipEvent_t ev : {p->fork_ev[0], p->fork_ev[1], p->join_ev[0], p->join_ev[1]})
     if (ev) (void)hipEventDestroy(ev);
   for (void* q : p->ipm_allocs) (void)hipFree(q);
+  if (p->ipm_host) (void)hipHostFree(p->ipm_host);
   for (void* q : p->allocs) (void)hipFree(q);
   delete p;
   return RKKT_OK;

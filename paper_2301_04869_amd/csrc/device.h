@@ -206,11 +206,16 @@ void launch_condense_values(const DP& d, const double* sx, const double* ss, dou
 // dynamic LDS limit of the fused line / gather kernel (never lowered)
 hipError_t configure_eval_kernels(const DP& d);
 // the two halves of launch_evaluate: line values and EV (all that the
-// refactorisation needs), then g, h, f, its gradients and W
+// refactorisation needs), then g, h, f, its gradients (launch_assemble) and W
+// (launch_hessian)
 void launch_evaluate_values(const DP& d, const double* x, const double* u, hipStream_t s);
 void launch_evaluate_rest(const DP& d, const double* x, const double* u, const double* y,
                           const double* z, double w, double* f, double* gx, double* gu, double* g,
                           double* h, hipStream_t s);
+void launch_assemble(const DP& d, const double* u, double w, double* f, double* gx, double* gu, double* g,
+                     double* h, hipStream_t s);
+void launch_hessian(const DP& d, const double* x, const double* u, const double* y, const double* z, double w,
+                    hipStream_t s);
 // (k_lu.hip)
 void launch_refactor(const DP& d, hipStream_t s);
 void launch_identity_rows(const DP& d, hipStream_t s);

@@ -29,11 +29,27 @@ struct rkkt_problem {
   bool ipm_ready = false;
   rkkt::IpmDev ipm{};
   std::vector<void*> ipm_allocs;
+  double* ipm_host = nullptr;  // pinned; ipm.hs is its device address
   // captured hot-path pass
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
-  // second stream of rkkt_iterate and its two fork / join event pairs
+  // second stream of rkkt_iterate and rkkt_solve and its two fork / join event
+  // pairs
   hipStream_t side_stream = nullptr;
   hipEvent_t fork_ev[2] = {nullptr, nullptr}, join_ev[2] = {nullptr, nullptr};
 };
+
+// Runs `launch` between two events on `stream` when profiling is on.
+template <typename F>
+inline void stage(rkkt_problem* p, int id, hipStream_t stream, F&& launch) {
+  if (!p->prof || 2 * (p->rec_used + 1) > p->events.size()) {
+    launch();
+    return;
+  }
+  size_t r = p->rec_used++;
+  (void)hipEventRecord(p->events[2 * r], stream);
+  launch();
+  (void)hipEventRecord(p->events[2 * r + 1], stream);
+  p->rec_stage[r] = id;
+}

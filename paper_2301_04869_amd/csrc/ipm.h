@@ -21,14 +21,16 @@ struct IpmDev {
   double *pzlx, *pzux, *pzlu, *pzuu, *pzls, *pzus; // bound-multiplier steps
   double *khat, *chol;
   int* info;
-  double* scal;                                    // device scalars [32]
+  double* part;                                    // workgroups' parts of a reduction
+  double* hs;                                      // scalars for the host [32], in its pinned memory
 };
 
-void ipm_resid(const DP& d, const IpmDev& s, double mu, hipStream_t st);
-void ipm_kkt_scalars(const DP& d, const IpmDev& s, double mu, double* out, hipStream_t st);
+long long ipm_part_doubles(const DP& d);  // size of IpmDev::part
+// residuals, Sigmas and the scaled KKT error's parts (out [6])
+void ipm_resid(const DP& d, const IpmDev& s, double mu, double* out, hipStream_t st);
 void ipm_merit(const DP& d, const IpmDev& s, bool trial, double* out, hipStream_t st);
-void ipm_step_scalars(const DP& d, const IpmDev& s, double mu, double tau, double* out,
-                      hipStream_t st);
+// step lengths, and the trial point of the largest primal step (out [6])
+void ipm_step_trial(const DP& d, const IpmDev& s, double mu, double tau, double* out, hipStream_t st);
 void ipm_trial(const DP& d, const IpmDev& s, double alpha, hipStream_t st);
 void ipm_accept(const DP& d, const IpmDev& s, double alpha, double alpha_z, double mu, double ks,
                 hipStream_t st);

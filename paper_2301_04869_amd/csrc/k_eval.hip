@@ -555,14 +555,24 @@ void launch_evaluate_values(const DP& d, const double* x, const double* u, hipSt
   k_gather_ev<<<grid_for(ne), kBlock, 0, s>>>(d);
 }
 
-void launch_evaluate_rest(const DP& d, const double* x, const double* u, const double* y,
-                          const double* z, double w, double* f, double* gx, double* gu, double* g,
-                          double* h, hipStream_t s) {
+void launch_assemble(const DP& d, const double* u, double w, double* f, double* gx, double* gu, double* g,
+                     double* h, hipStream_t s) {
   k_assemble<<<grid_for(assemble_threads(d)), kBlock, 0, s>>>(d, u, w, f, gx, gu, g, h);
+}
+
+void launch_hessian(const DP& d, const double* x, const double* u, const double* y, const double* z, double w,
+                    hipStream_t s) {
   long long nl = (long long)d.N * d.nl;
   k_line_hess<<<grid_for(nl), kBlock, 0, s>>>(d, x, u, y, z, w);
   long long nk = (long long)d.N * d.nnz_k;
   k_w_gather<<<grid_for(nk), kBlock, 0, s>>>(d, w);
+}
+
+void launch_evaluate_rest(const DP& d, const double* x, const double* u, const double* y,
+                          const double* z, double w, double* f, double* gx, double* gu, double* g,
+                          double* h, hipStream_t s) {
+  launch_assemble(d, u, w, f, gx, gu, g, h, s);
+  launch_hessian(d, x, u, y, z, w, s);
 }
 
 void launch_evaluate(const DP& d, const double* x, const double* u, const double* y,

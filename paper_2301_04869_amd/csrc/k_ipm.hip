@@ -2,9 +2,20 @@
 // augmented system (paper: KKT conditions with barrier homotopy, residuals
 // r1..r4), the scaled KKT error, the barrier objective and constraint
 // violation of the filter line search, fraction-to-boundary step lengths and
-// the iterate update.  Reductions run in one workgroup with a fixed tree, so
-// every scalar is reproducible run to run.
+// the iterate update.  Reductions meet in a fixed tree (lanes, wavefronts,
+// workgroups in order), so every scalar is reproducible run to run; what the
+// host decides on goes straight into its own pinned memory (IpmDev::hs).
+//
+// At one scenario every kernel here is a handful of dependent loads on a few
+// hundred elements, so what counts is how many launches and how many
+// dependent rounds a pass over the iterate takes.  118-bus grid, one
+// scenario, per iteration: residuals (17 us, one dependent chain of loads per
+// term) + their u part (4) + KKT scalars (10, 60 barriers) became two
+// launches of 13 and 8 us, bound-multiplier steps + step scalars +
+// trial point (5 + 9 + 3) two of 5 us, the merit 5 us instead of 7.
 #include "ipm.h"
+
+#include <algorithm>
 
 namespace rkkt {
 
@@ -28,152 +39,201 @@ __device__ inline void box_terms(double v, double lo, double hi, double zl, doub
   *bdual = bd;
 }
 
-// r1x, dx, Sigma_x (x part); per-scenario u gradient of the Lagrangian (u part);
-// r2, ds, r4, Sigma_s (s part)
-__global__ void k_resid(DP d, IpmDev s, double mu) {
-  const long long per = (long long)d.nx + d.nu + d.m;
-  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (long long)d.N * per) return;
-  const int k = (int)(t / per);
-  int i = (int)(t % per);
-  const double* ev = d.EV + (long long)k * d.n_ev;
-  const double* hv = ev + d.off_h;
-  const double* yk = s.y + (long long)k * d.nx;
-  const double* zk = s.z + (long long)k * d.m;
-  if (i < d.nx) {
-    const int ih = d.pinv[i];
-    double acc = s.gx[(long long)k * d.nx + i];
-    for (int j = d.gxc_ptr[ih]; j < d.gxc_ptr[ih + 1]; ++j)
-      acc += ev[d.off_gx + d.gxc_pos[j]] * yk[d.perm[d.gxc_row[j]]];
-    for (int j = d.ht_ptr[ih]; j < d.ht_ptr[ih + 1]; ++j) acc += hv[d.ht_pos[j]] * zk[d.ht_row[j]];
-    const long long q = (long long)k * d.nx + i;
-    double sg, bg, bd;
-    box_terms(s.x[q], s.xl[i], s.xu[i], s.zlx[q], s.zux[q], mu, &sg, &bg, &bd);
-    s.sx[q] = sg;
-    s.r1x[q] = acc + bg;
-    s.dx[q] = acc + bd;
-    s.r3[q] = s.g[q];
-    return;
-  }
-  i -= d.nx;
-  if (i < d.nu) {
-    double acc = s.gu[(long long)k * d.nu + i];
-    for (int j = d.guc_ptr[i]; j < d.guc_ptr[i + 1]; ++j)
-      acc += ev[d.off_gu + d.guc_pos[j]] * yk[d.perm[d.guc_row[j]]];
-    const int v = d.nx + i;
-    for (int j = d.ht_ptr[v]; j < d.ht_ptr[v + 1]; ++j) acc += hv[d.ht_pos[j]] * zk[d.ht_row[j]];
-    s.cu[(long long)k * d.nu + i] = acc;
-    return;
-  }
-  i -= d.nu;
-  const long long q = (long long)k * d.m + i;
-  double sg, bg, bd;
-  box_terms(s.s[q], s.sl[i], s.su[i], s.zls[q], s.zus[q], mu, &sg, &bg, &bd);
-  s.ss[q] = sg;
-  s.r2[q] = zk[i] + bg;
-  s.ds[q] = zk[i] + bd;
-  s.r4[q] = s.h[q] + s.s[q];
+// ---- reductions: the kinds of the values that a kernel reduces together
+enum Red { kSum, kMax, kMin };
+
+template <Red kR>
+__device__ __forceinline__ double red2(double a, double b) {
+  return kR == kSum ? a + b : kR == kMax ? fmax(a, b) : fmin(a, b);
 }
 
-__global__ void k_resid_u(DP d, IpmDev s, double mu) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= d.nu) return;
-  double acc = 0.0;
-  for (int k = 0; k < d.N; ++k) acc += s.cu[(long long)k * d.nu + c];
-  double sg, bg, bd;
-  box_terms(s.u[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], mu, &sg, &bg, &bd);
-  s.sgu[c] = sg;
-  s.r1u[c] = acc + bg;
-  s.du[c] = acc + bd;
-}
-
-// block reductions in one workgroup (fixed tree)
-__device__ double block_sum(double v, double* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
+// v[q] over the workgroup, every value at once: the lanes of a wavefront by a
+// butterfly (the values' chains interleave), then the wavefronts in order
+// through LDS; the result is in every thread
+template <int kWaves, Red... kRs>
+__device__ __forceinline__ void block_reduce(double (&v)[sizeof...(kRs)]) {
+  constexpr int n = sizeof...(kRs);
+  __shared__ double sh[kWaves][n];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    int q = 0;
+    ((v[q] = red2<kRs>(v[q], __shfl_xor(v[q], o, 64)), ++q), ...);
   }
-  double r = sh[0];
+  const int wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < n; ++q) sh[wv][q] = v[q];
   __syncthreads();
-  return r;
-}
-
-__device__ double block_max(double v, double* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
-    __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    int q = 0;
+    ((v[q] = w == 0 ? sh[0][q] : red2<kRs>(v[q], sh[w][q]), ++q), ...);
   }
-  double r = sh[0];
-  __syncthreads();
-  return r;
 }
 
-__device__ double block_min(double v, double* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + w]);
-    __syncthreads();
+// value [r][n] of workgroup r's part, r over the workgroups, in every thread
+template <int kWaves, Red... kRs>
+__device__ __forceinline__ void parts_reduce(const double* part, int nparts, const double (&init)[sizeof...(kRs)],
+                                             double (&v)[sizeof...(kRs)]) {
+  constexpr int n = sizeof...(kRs);
+#pragma unroll
+  for (int q = 0; q < n; ++q) v[q] = init[q];
+  for (int r = threadIdx.x; r < nparts; r += 64 * kWaves) {
+    int q = 0;
+    ((v[q] = red2<kRs>(v[q], part[(long long)r * n + q]), ++q), ...);
   }
-  double r = sh[0];
-  __syncthreads();
-  return r;
+  block_reduce<kWaves, kRs...>(v);
 }
 
-// complementarity of one boxed variable
-__device__ inline void comp_terms(double v, double lo, double hi, double zl, double zu, double mu,
-                                  double* cm, double* c0, double* zs) {
+// acc + sum of a(j) b(j), j in [j0, j1) in order; the loads of kTb terms (the
+// indices, then the values they name) are issued together, so a column costs
+// one round of dependent loads per kTb entries
+constexpr int kTb = 8;
+template <typename A, typename B>
+__device__ __forceinline__ double dot_terms(double acc, int j0, int j1, A a, B b) {
+  for (int j = j0; j < j1; j += kTb) {
+    double va[kTb], vb[kTb];
+#pragma unroll
+    for (int q = 0; q < kTb; ++q) {
+      const int jj = min(j + q, j1 - 1);
+      va[q] = a(jj);
+      vb[q] = b(jj);
+    }
+#pragma unroll
+    for (int q = 0; q < kTb; ++q)
+      if (j + q < j1) acc += va[q] * vb[q];
+  }
+  return acc;
+}
+
+// complementarity of one boxed variable: the smallest and the largest
+// (v - bound) z (every |comp - mu| follows from them, whatever mu is) and the
+// sum of the bound multipliers
+__device__ inline void comp_terms(double v, double lo, double hi, double zl, double zu, double* cmin,
+                                  double* cmax, double* zs) {
   if (fin(lo)) {
-    double a = (v - lo) * zl;
-    *cm = fmax(*cm, fabs(a - mu));
-    *c0 = fmax(*c0, fabs(a));
+    const double a = (v - lo) * zl;
+    *cmin = fmin(*cmin, a);
+    *cmax = fmax(*cmax, a);
     *zs += fabs(zl);
   }
   if (fin(hi)) {
-    double a = (hi - v) * zu;
-    *cm = fmax(*cm, fabs(a - mu));
-    *c0 = fmax(*c0, fabs(a));
+    const double a = (hi - v) * zu;
+    *cmin = fmin(*cmin, a);
+    *cmax = fmax(*cmax, a);
     *zs += fabs(zu);
   }
 }
 
-// out: [0] max dual, [1] max primal, [2] max |comp - mu|, [3] max |comp|,
-//      [4] sum |y| + |z|, [5] sum |bound duals|
-__global__ __launch_bounds__(kRed) void k_kkt_scalars(DP d, IpmDev s, double mu, double* out) {
-  __shared__ double sh[kRed];
-  const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
-  double dmax = 0.0, pmax = 0.0, cm = 0.0, c0 = 0.0, ysum = 0.0, zs = 0.0;
-  for (long long q = threadIdx.x; q < nxN; q += kRed) {
-    const int i = (int)(q % d.nx);
-    dmax = fmax(dmax, fabs(s.dx[q]));
-    pmax = fmax(pmax, fabs(s.g[q]));
-    ysum += fabs(s.y[q]);
-    comp_terms(s.x[q], s.xl[i], s.xu[i], s.zlx[q], s.zux[q], mu, &cm, &c0, &zs);
+// r1x, dx, Sigma_x (x part); per-scenario u gradient of the Lagrangian (u part);
+// r2, ds, r4, Sigma_s (s part); the workgroup's share of the KKT scalars
+__global__ __launch_bounds__(kBlock) void k_resid(DP d, IpmDev s, double mu) {
+  const long long per = (long long)d.nx + d.nu + d.m;
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  double dmax = 0.0, pmax = 0.0, cmin = INFINITY, cmax = -INFINITY, ysum = 0.0, zs = 0.0;
+  if (t < (long long)d.N * per) {
+    const int k = (int)(t / per);
+    int i = (int)(t % per);
+    const double* ev = d.EV + (long long)k * d.n_ev;
+    const double* hv = ev + d.off_h;
+    const double* yk = s.y + (long long)k * d.nx;
+    const double* zk = s.z + (long long)k * d.m;
+    auto ht = [&](double acc, int v) {
+      return dot_terms(acc, d.ht_ptr[v], d.ht_ptr[v + 1], [&](int j) { return hv[d.ht_pos[j]]; },
+                       [&](int j) { return zk[d.ht_row[j]]; });
+    };
+    if (i < d.nx) {
+      const int ih = d.pinv[i];
+      const long long q = (long long)k * d.nx + i;
+      double acc = dot_terms(s.gx[q], d.gxc_ptr[ih], d.gxc_ptr[ih + 1],
+                             [&](int j) { return ev[d.off_gx + d.gxc_pos[j]]; },
+                             [&](int j) { return yk[d.perm[d.gxc_row[j]]]; });
+      acc = ht(acc, ih);
+      double sg, bg, bd;
+      box_terms(s.x[q], s.xl[i], s.xu[i], s.zlx[q], s.zux[q], mu, &sg, &bg, &bd);
+      const double dx = acc + bd, gq = s.g[q];
+      s.sx[q] = sg;
+      s.r1x[q] = acc + bg;
+      s.dx[q] = dx;
+      s.r3[q] = gq;
+      dmax = fabs(dx);
+      pmax = fabs(gq);
+      ysum = fabs(yk[i]);
+      comp_terms(s.x[q], s.xl[i], s.xu[i], s.zlx[q], s.zux[q], &cmin, &cmax, &zs);
+    } else if (i < d.nx + d.nu) {
+      i -= d.nx;
+      const double acc = dot_terms(s.gu[(long long)k * d.nu + i], d.guc_ptr[i], d.guc_ptr[i + 1],
+                                   [&](int j) { return ev[d.off_gu + d.guc_pos[j]]; },
+                                   [&](int j) { return yk[d.perm[d.guc_row[j]]]; });
+      s.cu[(long long)k * d.nu + i] = ht(acc, d.nx + i);
+    } else {
+      i -= d.nx + d.nu;
+      const long long q = (long long)k * d.m + i;
+      double sg, bg, bd;
+      box_terms(s.s[q], s.sl[i], s.su[i], s.zls[q], s.zus[q], mu, &sg, &bg, &bd);
+      const double ds = zk[i] + bd, r4 = s.h[q] + s.s[q];
+      s.ss[q] = sg;
+      s.r2[q] = zk[i] + bg;
+      s.ds[q] = ds;
+      s.r4[q] = r4;
+      dmax = fabs(ds);
+      pmax = fabs(r4);
+      ysum = fabs(zk[i]);
+      comp_terms(s.s[q], s.sl[i], s.su[i], s.zls[q], s.zus[q], &cmin, &cmax, &zs);
+    }
   }
-  for (long long q = threadIdx.x; q < nmN; q += kRed) {
-    const int i = (int)(q % d.m);
-    dmax = fmax(dmax, fabs(s.ds[q]));
-    pmax = fmax(pmax, fabs(s.h[q] + s.s[q]));
-    ysum += fabs(s.z[q]);
-    comp_terms(s.s[q], s.sl[i], s.su[i], s.zls[q], s.zus[q], mu, &cm, &c0, &zs);
+  double v[6] = {dmax, pmax, cmin, cmax, ysum, zs};
+  block_reduce<kBlock / 64, kMax, kMax, kMin, kMax, kSum, kSum>(v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) s.part[6LL * blockIdx.x + q] = v[q];
+}
+
+// the u part of the residuals and the KKT scalars: out [0] max dual, [1] max
+// primal, [2] min comp, [3] max comp, [4] sum |y| + |z|, [5] sum |bound
+// duals|.  One workgroup: lane c of a wavefront adds its column's scenario
+// gradients over the wavefront's share of the scenarios, the shares meet in
+// wavefront order.
+__global__ __launch_bounds__(kRed) void k_resid_fin(DP d, IpmDev s, double mu, int nparts, double* out) {
+  constexpr int kW = kRed / 64;
+  __shared__ double sh[kW][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int per = (d.N + kW - 1) / kW, k0 = min(d.N, wv * per), k1 = min(d.N, k0 + per);
+  double dmax = 0.0, cmin = INFINITY, cmax = -INFINITY, zs = 0.0;
+  for (int c0 = 0; c0 < d.nu; c0 += 64) {
+    const int c = c0 + lane;
+    double acc = 0.0;
+    if (c < d.nu)
+      for (int k = k0; k < k1; k += kTb) {
+        double v[kTb];
+#pragma unroll
+        for (int q = 0; q < kTb; ++q) v[q] = s.cu[(long long)min(k + q, k1 - 1) * d.nu + c];
+#pragma unroll
+        for (int q = 0; q < kTb; ++q)
+          if (k + q < k1) acc += v[q];
+      }
+    sh[wv][lane] = acc;
+    __syncthreads();
+    if (wv == 0 && c < d.nu) {
+      acc = sh[0][lane];
+      for (int w = 1; w < kW; ++w) acc += sh[w][lane];
+      double sg, bg, bd;
+      box_terms(s.u[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], mu, &sg, &bg, &bd);
+      const double du = acc + bd;
+      s.sgu[c] = sg;
+      s.r1u[c] = acc + bg;
+      s.du[c] = du;
+      dmax = fmax(dmax, fabs(du));
+      comp_terms(s.u[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], &cmin, &cmax, &zs);
+    }
+    __syncthreads();
   }
-  for (int c = threadIdx.x; c < d.nu; c += kRed) {
-    dmax = fmax(dmax, fabs(s.du[c]));
-    comp_terms(s.u[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], mu, &cm, &c0, &zs);
-  }
-  dmax = block_max(dmax, sh);
-  pmax = block_max(pmax, sh);
-  cm = block_max(cm, sh);
-  c0 = block_max(c0, sh);
-  ysum = block_sum(ysum, sh);
-  zs = block_sum(zs, sh);
-  if (threadIdx.x == 0) {
-    out[0] = dmax; out[1] = pmax; out[2] = cm; out[3] = c0; out[4] = ysum; out[5] = zs;
-  }
+  const double init[6] = {dmax, 0.0, cmin, cmax, 0.0, zs};
+  double v[6];
+  parts_reduce<kW, kMax, kMax, kMin, kMax, kSum, kSum>(s.part, nparts, init, v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) out[q] = v[q];
 }
 
 __device__ inline double logbox(double v, double lo, double hi, int* bad) {
@@ -185,31 +245,52 @@ __device__ inline double logbox(double v, double lo, double hi, int* bad) {
 
 // merit of a primal point (x, u, s) with its f, g, h:
 // out: [0] sum f, [1] theta = |g|_1 + |h + s|_1, [2] log-barrier sum, [3] bad (1 if outside)
+// One workgroup up to kMeritPer elements per thread (the result goes to out
+// itself), more workgroups above that and their parts to k_merit_fin.
+constexpr int kMeritPer = 4, kMeritBlocks = 256;
+
+inline unsigned merit_blocks(const DP& d) {
+  const long long n = (long long)d.N * (d.nx + d.m) + d.nu, per = (long long)kMeritPer * kRed;
+  return (unsigned)std::min<long long>(kMeritBlocks, (n + per - 1) / per);
+}
+
 __global__ __launch_bounds__(kRed) void k_merit(DP d, IpmDev s, const double* x, const double* u,
                                                 const double* sv, const double* f, const double* g,
                                                 const double* h, double* out) {
-  __shared__ double sh[kRed];
-  __shared__ int sbad;
-  if (threadIdx.x == 0) sbad = 0;
-  __syncthreads();
   int bad = 0;
   double fs = 0.0, th = 0.0, lg = 0.0;
   const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
-  for (long long q = threadIdx.x; q < nxN; q += kRed) {
-    th += fabs(g[q]);
-    lg += logbox(x[q], s.xl[q % d.nx], s.xu[q % d.nx], &bad);
+  const long long t0 = (long long)blockIdx.x * kRed + threadIdx.x, dt = (long long)gridDim.x * kRed;
+  for (long long t = t0; t < nxN + nmN + d.nu; t += dt) {
+    if (t < nxN) {
+      const int i = (int)(t % d.nx);
+      th += fabs(g[t]);
+      lg += logbox(x[t], s.xl[i], s.xu[i], &bad);
+    } else if (t < nxN + nmN) {
+      const long long q = t - nxN;
+      const int i = (int)(q % d.m);
+      th += fabs(h[q] + sv[q]);
+      lg += logbox(sv[q], s.sl[i], s.su[i], &bad);
+    } else {
+      const int c = (int)(t - nxN - nmN);
+      lg += logbox(u[c], s.ul[c], s.uu[c], &bad);
+    }
   }
-  for (long long q = threadIdx.x; q < nmN; q += kRed) {
-    th += fabs(h[q] + sv[q]);
-    lg += logbox(sv[q], s.sl[q % d.m], s.su[q % d.m], &bad);
-  }
-  for (int c = threadIdx.x; c < d.nu; c += kRed) lg += logbox(u[c], s.ul[c], s.uu[c], &bad);
-  for (int k = threadIdx.x; k < d.N; k += kRed) fs += f[k];
-  if (bad) atomicOr(&sbad, 1);
-  fs = block_sum(fs, sh);
-  th = block_sum(th, sh);
-  lg = block_sum(lg, sh);
-  if (threadIdx.x == 0) { out[0] = fs; out[1] = th; out[2] = lg; out[3] = sbad ? 1.0 : 0.0; }
+  for (long long k = t0; k < d.N; k += dt) fs += f[k];
+  double v[4] = {fs, th, lg, bad ? 1.0 : 0.0};
+  block_reduce<kRed / 64, kSum, kSum, kSum, kMax>(v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[4LL * blockIdx.x + q] = v[q];
+}
+
+__global__ __launch_bounds__(kMeritBlocks) void k_merit_fin(IpmDev s, int nparts, double* out) {
+  const double init[4] = {0.0, 0.0, 0.0, 0.0};
+  double v[4];
+  parts_reduce<kMeritBlocks / 64, kSum, kSum, kSum, kMax>(s.part, nparts, init, v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = v[q];
 }
 
 // bound-dual steps: p_zL = mu/(v-l) - zL - zL/(v-l) p, p_zU = mu/(u-v) - zU + zU/(u-v) p
@@ -219,27 +300,6 @@ __device__ inline void dual_step(double v, double p, double lo, double hi, doubl
   *pu = 0.0;
   if (fin(lo)) { double a = v - lo; *pl = mu / a - zl - zl / a * p; }
   if (fin(hi)) { double b = hi - v; *pu = mu / b - zu + zu / b * p; }
-}
-
-__global__ void k_dual_steps(DP d, IpmDev s, double mu) {
-  const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
-  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nxN) {
-    const int i = (int)(t % d.nx);
-    dual_step(s.x[t], s.px[t], s.xl[i], s.xu[i], s.zlx[t], s.zux[t], mu, &s.pzlx[t], &s.pzux[t]);
-    return;
-  }
-  t -= nxN;
-  if (t < nmN) {
-    const int i = (int)(t % d.m);
-    dual_step(s.s[t], s.ps[t], s.sl[i], s.su[i], s.zls[t], s.zus[t], mu, &s.pzls[t], &s.pzus[t]);
-    return;
-  }
-  t -= nmN;
-  if (t < d.nu) {
-    const int c = (int)t;
-    dual_step(s.u[c], s.pu[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], mu, &s.pzlu[c], &s.pzuu[c]);
-  }
 }
 
 __device__ inline double primal_ratio(double v, double p, double lo, double hi, double tau) {
@@ -253,46 +313,72 @@ __device__ inline double dual_ratio(double z, double p, double tau) {
   return p < 0.0 ? fmin(1.0, -tau * z / p) : 1.0;
 }
 
-// out: [0] alpha_max primal, [1] alpha_z, [2] grad(phi)^T d
-__global__ __launch_bounds__(kRed) void k_step_scalars(DP d, IpmDev s, double mu, double tau,
-                                                       double* out) {
-  __shared__ double sh[kRed];
-  double ap = 1.0, az = 1.0, dphi = 0.0;
-  const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
-  for (long long q = threadIdx.x; q < nxN; q += kRed) {
-    const int i = (int)(q % d.nx);
-    ap = fmin(ap, primal_ratio(s.x[q], s.px[q], s.xl[i], s.xu[i], tau));
-    az = fmin(az, fmin(dual_ratio(s.zlx[q], s.pzlx[q], tau), dual_ratio(s.zux[q], s.pzux[q], tau)));
-    double sg, bg, bd;
-    box_terms(s.x[q], s.xl[i], s.xu[i], 0.0, 0.0, mu, &sg, &bg, &bd);
-    dphi += (s.gx[q] + bg) * s.px[q];
-  }
-  for (long long q = threadIdx.x; q < nmN; q += kRed) {
-    const int i = (int)(q % d.m);
-    ap = fmin(ap, primal_ratio(s.s[q], s.ps[q], s.sl[i], s.su[i], tau));
-    az = fmin(az, fmin(dual_ratio(s.zls[q], s.pzls[q], tau), dual_ratio(s.zus[q], s.pzus[q], tau)));
-    double sg, bg, bd;
-    box_terms(s.s[q], s.sl[i], s.su[i], 0.0, 0.0, mu, &sg, &bg, &bd);
-    dphi += bg * s.ps[q];
-  }
-  for (int c = threadIdx.x; c < d.nu; c += kRed) {
-    ap = fmin(ap, primal_ratio(s.u[c], s.pu[c], s.ul[c], s.uu[c], tau));
-    az = fmin(az, fmin(dual_ratio(s.zlu[c], s.pzlu[c], tau), dual_ratio(s.zuu[c], s.pzuu[c], tau)));
-    double gsum = 0.0;
-    for (int k = 0; k < d.N; ++k) gsum += s.gu[(long long)k * d.nu + c];
-    double sg, bg, bd;
-    box_terms(s.u[c], s.ul[c], s.uu[c], 0.0, 0.0, mu, &sg, &bg, &bd);
-    dphi += (gsum + bg) * s.pu[c];
-  }
-  ap = block_min(ap, sh);
-  az = block_min(az, sh);
-  dphi = block_sum(dphi, sh);
-  if (threadIdx.x == 0) { out[0] = ap; out[1] = az; out[2] = dphi; }
-}
-
-__global__ void k_trial(DP d, IpmDev s, double alpha) {
+// bound-multiplier steps and, per workgroup, the largest step lengths (primal
+// and bound multipliers) and grad(phi)^T d
+__global__ __launch_bounds__(kBlock) void k_step_scalars(DP d, IpmDev s, double mu, double tau) {
   const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
   long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  double ap = 1.0, az = 1.0, dphi = 0.0;
+  auto one = [&](double v, double p, double lo, double hi, double zl, double zu, double grad, double* pzl,
+                 double* pzu) {
+    double pl, pu, sg, bg, bd;
+    dual_step(v, p, lo, hi, zl, zu, mu, &pl, &pu);
+    *pzl = pl;
+    *pzu = pu;
+    ap = primal_ratio(v, p, lo, hi, tau);
+    az = fmin(dual_ratio(zl, pl, tau), dual_ratio(zu, pu, tau));
+    box_terms(v, lo, hi, 0.0, 0.0, mu, &sg, &bg, &bd);
+    dphi = (grad + bg) * p;
+  };
+  if (t < nxN) {
+    const int i = (int)(t % d.nx);
+    one(s.x[t], s.px[t], s.xl[i], s.xu[i], s.zlx[t], s.zux[t], s.gx[t], &s.pzlx[t], &s.pzux[t]);
+  } else if ((t -= nxN) < nmN) {
+    const int i = (int)(t % d.m);
+    one(s.s[t], s.ps[t], s.sl[i], s.su[i], s.zls[t], s.zus[t], 0.0, &s.pzls[t], &s.pzus[t]);
+  } else if ((t -= nmN) < d.nu) {
+    const int c = (int)t;
+    double gsum = 0.0;
+    for (int k = 0; k < d.N; k += kTb) {
+      double v[kTb];
+#pragma unroll
+      for (int q = 0; q < kTb; ++q) v[q] = s.gu[(long long)min(k + q, d.N - 1) * d.nu + c];
+#pragma unroll
+      for (int q = 0; q < kTb; ++q)
+        if (k + q < d.N) gsum += v[q];
+    }
+    one(s.u[c], s.pu[c], s.ul[c], s.uu[c], s.zlu[c], s.zuu[c], gsum, &s.pzlu[c], &s.pzuu[c]);
+  }
+  double v[3] = {ap, az, dphi};
+  block_reduce<kBlock / 64, kMin, kMin, kSum>(v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.part[3LL * blockIdx.x + q] = v[q];
+}
+
+// trial point x + alpha p.  With nparts > 0, alpha is the largest primal step
+// of k_step_scalars' parts, which every workgroup reduces for itself; the
+// first also reports them to the host: out [0] alpha_max primal, [1] alpha_z,
+// [2] grad(phi)^T d, [3] info of the factorisation, [4], [5] device status
+// (which is cleared).
+__global__ __launch_bounds__(kBlock) void k_trial(DP d, IpmDev s, double alpha, int nparts, double* out) {
+  const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
+  long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (nparts > 0) {
+    const double init[3] = {1.0, 1.0, 0.0};
+    double v[3];
+    parts_reduce<kBlock / 64, kMin, kMin, kSum>(s.part, nparts, init, v);
+    alpha = v[0];
+    if (t == 0) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) out[q] = v[q];
+      out[3] = *s.info;
+      out[4] = d.status[0];
+      out[5] = d.status[1];
+      d.status[0] = 0;
+      d.status[1] = 0;
+    }
+  }
   if (t < nxN) { s.xt[t] = s.x[t] + alpha * s.px[t]; return; }
   t -= nxN;
   if (t < nmN) { s.st[t] = s.s[t] + alpha * s.ps[t]; return; }
@@ -306,12 +392,14 @@ __device__ inline void safeguard(double v, double lo, double hi, double mu, doub
   if (fin(hi)) { double b = hi - v; *zu = fmax(fmin(*zu, ks * mu / b), mu / (ks * b)); } else *zu = 0.0;
 }
 
+// the accepted trial point becomes the iterate; y, z and the bound
+// multipliers take their steps
 __global__ void k_accept(DP d, IpmDev s, double alpha, double alpha_z, double mu, double ks) {
   const long long nxN = (long long)d.N * d.nx, nmN = (long long)d.N * d.m;
   long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < nxN) {
     const int i = (int)(t % d.nx);
-    s.x[t] += alpha * s.px[t];
+    s.x[t] = s.xt[t];
     s.y[t] += alpha * s.py[t];
     double zl = s.zlx[t] + alpha_z * s.pzlx[t], zu = s.zux[t] + alpha_z * s.pzux[t];
     safeguard(s.x[t], s.xl[i], s.xu[i], mu, ks, &zl, &zu);
@@ -322,7 +410,7 @@ __global__ void k_accept(DP d, IpmDev s, double alpha, double alpha_z, double mu
   t -= nxN;
   if (t < nmN) {
     const int i = (int)(t % d.m);
-    s.s[t] += alpha * s.ps[t];
+    s.s[t] = s.st[t];
     s.z[t] += alpha * s.pz[t];
     double zl = s.zls[t] + alpha_z * s.pzls[t], zu = s.zus[t] + alpha_z * s.pzus[t];
     safeguard(s.s[t], s.sl[i], s.su[i], mu, ks, &zl, &zu);
@@ -333,7 +421,7 @@ __global__ void k_accept(DP d, IpmDev s, double alpha, double alpha_z, double mu
   t -= nmN;
   if (t < d.nu) {
     const int c = (int)t;
-    s.u[c] += alpha * s.pu[c];
+    s.u[c] = s.ut[c];
     double zl = s.zlu[c] + alpha_z * s.pzlu[c], zu = s.zuu[c] + alpha_z * s.pzuu[c];
     safeguard(s.u[c], s.ul[c], s.uu[c], mu, ks, &zl, &zu);
     s.zlu[c] = zl;
@@ -468,46 +556,50 @@ __global__ void k_warm_implied(DP d, IpmDev s, double mu0) {
 
 // out[0] = max(max |grad_x f_i|, max |sum_i grad_u f_i|)
 __global__ __launch_bounds__(kRed) void k_grad_max(DP d, IpmDev s, double* out) {
-  __shared__ double sh[kRed];
-  double mx = 0.0;
+  double v[1] = {0.0};
   const long long nxN = (long long)d.N * d.nx;
-  for (long long q = threadIdx.x; q < nxN; q += kRed) mx = fmax(mx, fabs(s.gx[q]));
+  for (long long q = threadIdx.x; q < nxN; q += kRed) v[0] = fmax(v[0], fabs(s.gx[q]));
   for (int c = threadIdx.x; c < d.nu; c += kRed) {
     double acc = 0.0;
     for (int k = 0; k < d.N; ++k) acc += s.gu[(long long)k * d.nu + c];
-    mx = fmax(mx, fabs(acc));
+    v[0] = fmax(v[0], fabs(acc));
   }
-  mx = block_max(mx, sh);
-  if (threadIdx.x == 0) out[0] = mx;
+  block_reduce<kRed / 64, kMax>(v);
+  if (threadIdx.x == 0) out[0] = v[0];
 }
 
 }  // namespace
 
-void ipm_resid(const DP& d, const IpmDev& s, double mu, hipStream_t st) {
-  const long long n = (long long)d.N * (d.nx + d.nu + d.m);
-  k_resid<<<grid_for(n), kBlock, 0, st>>>(d, s, mu);
-  k_resid_u<<<grid_for(d.nu), kBlock, 0, st>>>(d, s, mu);
+// parts of the reductions: the largest of the workgroups' counts of k_resid
+// (6 values each), k_step_scalars (3) and k_merit (4)
+long long ipm_part_doubles(const DP& d) {
+  const long long n = (long long)d.N * (d.nx + d.nu + d.m), n1 = (long long)d.N * (d.nx + d.m) + d.nu;
+  return std::max<long long>({6LL * grid_for(n), 3LL * grid_for(n1), 4LL * kMeritBlocks});
 }
 
-void ipm_kkt_scalars(const DP& d, const IpmDev& s, double mu, double* out, hipStream_t st) {
-  k_kkt_scalars<<<1, kRed, 0, st>>>(d, s, mu, out);
+void ipm_resid(const DP& d, const IpmDev& s, double mu, double* out, hipStream_t st) {
+  const unsigned nb = grid_for((long long)d.N * (d.nx + d.nu + d.m));
+  k_resid<<<nb, kBlock, 0, st>>>(d, s, mu);
+  k_resid_fin<<<1, kRed, 0, st>>>(d, s, mu, (int)nb, out);
 }
 
 void ipm_merit(const DP& d, const IpmDev& s, bool trial, double* out, hipStream_t st) {
-  if (trial) k_merit<<<1, kRed, 0, st>>>(d, s, s.xt, s.ut, s.st, s.ft, s.gt, s.ht, out);
-  else k_merit<<<1, kRed, 0, st>>>(d, s, s.x, s.u, s.s, s.f, s.g, s.h, out);
+  const unsigned nb = merit_blocks(d);
+  double* o = nb > 1 ? s.part : out;
+  if (trial) k_merit<<<nb, kRed, 0, st>>>(d, s, s.xt, s.ut, s.st, s.ft, s.gt, s.ht, o);
+  else k_merit<<<nb, kRed, 0, st>>>(d, s, s.x, s.u, s.s, s.f, s.g, s.h, o);
+  if (nb > 1) k_merit_fin<<<1, kMeritBlocks, 0, st>>>(s, (int)nb, out);
 }
 
-void ipm_step_scalars(const DP& d, const IpmDev& s, double mu, double tau, double* out,
-                      hipStream_t st) {
-  const long long n = (long long)d.N * (d.nx + d.m) + d.nu;
-  k_dual_steps<<<grid_for(n), kBlock, 0, st>>>(d, s, mu);
-  k_step_scalars<<<1, kRed, 0, st>>>(d, s, mu, tau, out);
+void ipm_step_trial(const DP& d, const IpmDev& s, double mu, double tau, double* out, hipStream_t st) {
+  const unsigned nb = grid_for((long long)d.N * (d.nx + d.m) + d.nu);
+  k_step_scalars<<<nb, kBlock, 0, st>>>(d, s, mu, tau);
+  k_trial<<<nb, kBlock, 0, st>>>(d, s, 0.0, (int)nb, out);
 }
 
 void ipm_trial(const DP& d, const IpmDev& s, double alpha, hipStream_t st) {
   const long long n = (long long)d.N * (d.nx + d.m) + d.nu;
-  k_trial<<<grid_for(n), kBlock, 0, st>>>(d, s, alpha);
+  k_trial<<<grid_for(n), kBlock, 0, st>>>(d, s, alpha, 0, nullptr);
 }
 
 void ipm_accept(const DP& d, const IpmDev& s, double alpha, double alpha_z, double mu, double ks,
