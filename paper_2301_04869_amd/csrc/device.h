@@ -150,6 +150,14 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// 1/d: the hardware reciprocal estimate refined by two Newton-Raphson steps
+// r <- r (2 - d r).
+__device__ __forceinline__ double rcp_nr(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return fma(r, fma(-d, r, 1.0), r);
+}
+
 // value of v in lane Q of the caller's row of 16 lanes (DPP row_newbcast)
 template <int Q>
 __device__ __forceinline__ double row_bcast(double v) {

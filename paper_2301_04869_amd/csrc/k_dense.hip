@@ -302,14 +302,6 @@ __device__ __forceinline__ double rsqrt_nr(double d) {
   return fma(0.5 * r, e, r);
 }
 
-// 1/d: the hardware reciprocal estimate refined by two Newton-Raphson steps
-// r <- r (2 - d r).
-__device__ __forceinline__ double rcp_nr(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  r = fma(r, fma(-d, r, 1.0), r);
-  return fma(r, fma(-d, r, 1.0), r);
-}
-
 constexpr int kPB = 16;
 
 // Factor of an n x n matrix (n <= kSmallN) in one workgroup of 8 wavefronts,

@@ -187,27 +187,31 @@ __device__ __forceinline__ void sweep_w(const int* ptr, const uint2* ent, const 
   auto pos = [](uint2 v) { return (int)(kTrans ? v.y >> 16 : v.y & 0xffffu); };
   auto dst = [](uint2 v) { return (int)(v.x & 0xffffu); };
   auto src = [](uint2 v) { return (int)(v.x >> 16); };
-  // phase q: extent (e0, n), first entry t, slot maximum m; phase q + 1: the
-  // extent's ends (e1, b1) as read
-  int e0 = 0, n = 0, m = 0, e1 = 0, b1 = 0;
-  uint2 t = make_uint2(0u, 0u);
-  if (nphase > 0) {
-    e0 = ptr[slot];
-    n = ptr[slot + 1] - e0;
-    t = ent[n > 0 ? e0 : 0];
-    m = phmax[0];
-    // reads past the last phase take the last phase's (valid) data, unused
-    const int q1 = min(1, nphase - 1);
-    e1 = ptr[q1 * kGroupLds + slot];
-    b1 = ptr[q1 * kGroupLds + slot + 1];
-  }
-  for (int q = 0; q < nphase; ++q) {
-    const int mq = __builtin_amdgcn_readfirstlane(m);
+  // phase q: extent (e, b), first entry t, slot maximum m, in a ring of three
+  // registers each with the phases unrolled over it (rotating them with moves
+  // made every phase wait for the reads it had just issued)
+  if (nphase == 0) return;
+  int eb[3], bb[3], mx[3];
+  uint2 tt[3];
+  eb[0] = ptr[slot];
+  bb[0] = ptr[slot + 1];
+  tt[0] = ent[bb[0] > eb[0] ? eb[0] : 0];
+  mx[0] = phmax[0];
+  // reads past the last phase take the last phase's (valid) data, unused
+  const int q1 = min(1, nphase - 1);
+  eb[1] = ptr[q1 * kGroupLds + slot];
+  bb[1] = ptr[q1 * kGroupLds + slot + 1];
+  auto phase = [&](int q, auto jc) {
+    constexpr int j = decltype(jc)::value, j1 = (j + 1) % 3, j2 = (j + 2) % 3;
+    const int mq = __builtin_amdgcn_readfirstlane(mx[j]);
+    const uint2 t = tt[j];
+    const int e0 = eb[j], n = bb[j] - e0;
     const double a = lu[pos(t)], xs = X[src(t)], xd = X[dst(t)];
-    const int n1 = b1 - e1, q1 = min(q + 1, nphase - 1), q2 = min(q + 2, nphase - 1);
-    const uint2 t1 = ent[n1 > 0 ? e1 : 0];
-    const int m1 = phmax[q1];
-    const int e2 = ptr[q2 * kGroupLds + slot], b2 = ptr[q2 * kGroupLds + slot + 1];
+    const int qn = min(q + 1, nphase - 1), qm = min(q + 2, nphase - 1);
+    tt[j1] = ent[bb[j1] > eb[j1] ? eb[j1] : 0];
+    mx[j1] = phmax[qn];
+    eb[j2] = ptr[qm * kGroupLds + slot];
+    bb[j2] = ptr[qm * kGroupLds + slot + 1];
     if (n > 0) {
       if (mq <= 1) {
         X[dst(t)] = fma(-a, xs, xd);
@@ -227,12 +231,11 @@ __device__ __forceinline__ void sweep_w(const int* ptr, const uint2* ent, const 
       }
     }
     sync();
-    e0 = e1;
-    n = n1;
-    t = t1;
-    m = m1;
-    e1 = e2;
-    b1 = b2;
+  };
+  for (int q = 0; q < nphase; q += 3) {
+    phase(q, std::integral_constant<int, 0>{});
+    if (q + 1 < nphase) phase(q + 1, std::integral_constant<int, 1>{});
+    if (q + 2 < nphase) phase(q + 2, std::integral_constant<int, 2>{});
   }
 }
 
@@ -309,127 +312,113 @@ __device__ __forceinline__ void chain_solve1(const DP& d, const double* lu, cons
   if (own) X[c0 + lane] = x;
 }
 
-// Many columns: the calling thread solves its own column c of X (leading
-// dimension ld) over the chain rows.  cv[a t + b] holds the chain block's
-// values (zero where the pattern has no entry), staged in LDS once per
-// workgroup, so every coefficient is one broadcast read.
-template <bool kUp, bool kTrans>
-__device__ __forceinline__ void chain_solveW(const DP& d, const double* cv, double* X, int ld, int c) {
-  const int t = d.chain_t, c0 = d.chain_c0;
-  double x[kChainMax];
-#pragma unroll
-  for (int a = 0; a < kChainMax; ++a) x[a] = a < t ? X[(long long)(c0 + a) * ld + c] : 0.0;
-  // column order: once x_b is final, every later row subtracts its term; the
-  // updates of one step are independent, and each row still subtracts its
-  // terms in the order of b
-  if (kUp) {
-#pragma unroll
-    for (int b = 0; b < kChainMax - 1; ++b)
-      if (b + 1 < t) {
-#pragma unroll
-        for (int a = b + 1; a < kChainMax; ++a)
-          if (a < t) x[a] = fma(-(kTrans ? cv[b * t + a] : cv[a * t + b]), x[b], x[a]);
-      }
-  } else {
-#pragma unroll
-    for (int b = kChainMax - 1; b >= 1; --b)
-      if (b < t) {
-#pragma unroll
-        for (int a = 0; a < b; ++a) x[a] = fma(-(kTrans ? cv[b * t + a] : cv[a * t + b]), x[b], x[a]);
-      }
-  }
-#pragma unroll
-  for (int a = 0; a < kChainMax; ++a)
-    if (a < t) X[(long long)(c0 + a) * ld + c] = x[a];
-}
-
-// Many columns, all wavefronts: wavefront w takes columns 4 w .. 4 w + 3 of
-// X, lanes 0..31 holding the chain rows of columns 4 w and 4 w + 2, lanes
-// 32..63 those of 4 w + 1 and 4 w + 3; x_b is broadcast with readlane.  The up solve
-// and then the down solve, each row subtracting its terms in the same order
-// as chain_solveW (so the results are the same).  64 columns = 16
-// wavefronts.
 // f(integral_constant<int, B>) for B in order
 template <typename F, int... B>
 __device__ __forceinline__ void for_each_const(F&& f, std::integer_sequence<int, B...>) {
   (f(std::integral_constant<int, B>{}), ...);
 }
 
+// Many columns, all wavefronts: wavefront w takes columns 4 w .. 4 w + 3 of
+// X (those below ncol), lanes 0..31 holding the chain rows of columns 4 w and
+// 4 w + 2, lanes 32..63 those of 4 w + 1 and 4 w + 3; x_b is broadcast with
+// readlane.  The up solve and then the down solve, each row subtracting its
+// terms in the order of the steps.  cv[a t + b] holds the chain block's values
+// (zero where the pattern has no entry), staged in LDS once per workgroup.  64
+// columns = 16 wavefronts.  The 2 t dependent steps are all that bounds it: a
+// row's coefficients come from LDS into registers before the first of them.
+// The narrow tiles' 29 rows and 11 columns of the 30-bus grid: their whole
+// reduction 39 us with one thread per column on one wavefront, 19 us so.
 template <bool kTrans>
-__device__ __forceinline__ void chain_solveR(const DP& d, const double* cv, double* X, int ld, int wv) {
+__device__ __forceinline__ void chain_solveR(const DP& d, const double* cv, double* X, int ld, int wv, int ncol) {
   const int t = d.chain_t, c0 = d.chain_c0;
   const int lane = threadIdx.x & 63, a = lane & 31, half = lane >> 5;
+  if (4 * wv >= ncol) return;
   const bool own = a < t;
   // both column pairs of the wavefront at once (independent chains)
   const int col0 = 4 * wv + half, col1 = col0 + 2;
-  double x = own ? X[(long long)(c0 + a) * ld + col0] : 0.0;
-  double y = own ? X[(long long)(c0 + a) * ld + col1] : 0.0;
-  if (t <= 16) {
-    // rows in lanes 0..15 (and 32..47 for the other column of the pair):
-    // x_b is lane b of each row of 16 lanes, a DPP broadcast
-    auto up = [&](auto bc) {
+  const bool has0 = own && col0 < ncol, has1 = own && col1 < ncol;
+  double x = has0 ? X[(long long)(c0 + a) * ld + col0] : 0.0;
+  double y = has1 ? X[(long long)(c0 + a) * ld + col1] : 0.0;
+  // coefficients of row a: those before a for the up solve, after a for the
+  // down solve
+  auto solve = [&](auto rows) {
+    constexpr int kT = decltype(rows)::value;
+    double cf[kT];
+#pragma unroll
+    for (int b = 0; b < kT; ++b) cf[b] = own && b < t ? (kTrans ? cv[b * t + a] : cv[a * t + b]) : 0.0;
+    auto step = [&](auto bc, bool below) {
       constexpr int b = decltype(bc)::value;
-      if (b < t) {
-        const double cf = own ? (kTrans ? cv[b * t + a] : cv[a * t + b]) : 0.0;
-        const double xb = row_bcast<b>(x), yb = row_bcast<b>(y);
-        if (a > b) {
-          x = fma(-cf, xb, x);
-          y = fma(-cf, yb, y);
-        }
+      double xb, yb;
+      if constexpr (kT <= 16) {
+        // rows in lanes 0..15 (and 32..47 for the other column of the pair):
+        // x_b is lane b of each row of 16 lanes, a DPP broadcast
+        xb = row_bcast<b>(x);
+        yb = row_bcast<b>(y);
+      } else {
+        const double x0 = readlane_d(x, b), x1 = readlane_d(x, 32 + b);
+        const double y0 = readlane_d(y, b), y1 = readlane_d(y, 32 + b);
+        xb = half ? x1 : x0;
+        yb = half ? y1 : y0;
+      }
+      if (below ? a > b : a < b) {
+        x = fma(-cf[b], xb, x);
+        y = fma(-cf[b], yb, y);
       }
     };
-    auto down = [&](auto bc) {
-      constexpr int b = 15 - decltype(bc)::value;
-      if (b < t) {
-        const double cf = own ? (kTrans ? cv[b * t + a] : cv[a * t + b]) : 0.0;
-        const double xb = row_bcast<b>(x), yb = row_bcast<b>(y);
-        if (a < b) {
-          x = fma(-cf, xb, x);
-          y = fma(-cf, yb, y);
-        }
-      }
-    };
-    for_each_const(up, std::make_integer_sequence<int, 16>{});
-    for_each_const(down, std::make_integer_sequence<int, 16>{});
-    if (own) {
-      X[(long long)(c0 + a) * ld + col0] = x;
-      X[(long long)(c0 + a) * ld + col1] = y;
-    }
-    return;
-  }
-#pragma unroll
-  for (int b = 0; b < kChainMax; ++b)
-    if (b < t) {
-      const double cf = own ? (kTrans ? cv[b * t + a] : cv[a * t + b]) : 0.0;
-      const double x0 = readlane_d(x, b), x1 = readlane_d(x, 32 + b);
-      const double y0 = readlane_d(y, b), y1 = readlane_d(y, 32 + b);
-      if (a > b) {
-        x = fma(-cf, half ? x1 : x0, x);
-        y = fma(-cf, half ? y1 : y0, y);
-      }
-    }
-#pragma unroll
-  for (int b = kChainMax - 1; b >= 0; --b)
-    if (b < t) {
-      const double cf = own ? (kTrans ? cv[b * t + a] : cv[a * t + b]) : 0.0;
-      const double x0 = readlane_d(x, b), x1 = readlane_d(x, 32 + b);
-      const double y0 = readlane_d(y, b), y1 = readlane_d(y, 32 + b);
-      if (a < b) {
-        x = fma(-cf, half ? x1 : x0, x);
-        y = fma(-cf, half ? y1 : y0, y);
-      }
-    }
-  if (own) {
-    X[(long long)(c0 + a) * ld + col0] = x;
-    X[(long long)(c0 + a) * ld + col1] = y;
-  }
+    for_each_const([&](auto bc) { if (decltype(bc)::value < t) step(bc, true); },
+                   std::make_integer_sequence<int, kT>{});
+    for_each_const([&](auto bc) {
+      constexpr int b = kT - 1 - decltype(bc)::value;
+      if (b < t) step(std::integral_constant<int, b>{}, false);
+    }, std::make_integer_sequence<int, kT>{});
+  };
+  if (t <= 16) solve(std::integral_constant<int, 16>{});
+  else solve(std::integral_constant<int, kChainMax>{});
+  if (has0) X[(long long)(c0 + a) * ld + col0] = x;
+  if (has1) X[(long long)(c0 + a) * ld + col1] = y;
 }
 
-// chain block values of one scenario into cv (all threads of the workgroup)
+// 64 columns by the first wavefront, lane c of it column c with the chain rows
+// in registers: t (t - 1) multiply-adds in all, where chain_solveR on 16
+// wavefronts issues 32 t and ten times as many lane moves.  Column order: once
+// x_b is final every later row subtracts its term, so a step's updates are
+// independent, and each row still subtracts its terms in the order of b.
+// cv[b t + a] is the coefficient of (row a, row b), column by column: a step
+// reads consecutive values, the same in every lane (an LDS broadcast).  Rows
+// past the chain work on a copy of the last coefficients and are not stored.
+// 21 rows: 9.4 us with chain_solveR, 4.6 us here.
+template <int kT>
+__device__ __forceinline__ void chain_solveC(const DP& d, const double* cv, double* X, int c) {
+  const int t = d.chain_t, c0 = d.chain_c0;
+  double x[kT];
+#pragma unroll
+  for (int a = 0; a < kT; ++a) x[a] = X[(c0 + min(a, t - 1)) * 64 + c];
+#pragma unroll
+  for (int b = 0; b + 1 < kT; ++b)
+    if (b + 1 < t) {
+      const double* cb = cv + b * t;
+#pragma unroll
+      for (int a = b + 1; a < kT; ++a) x[a] = fma(-cb[min(a, t - 1)], x[b], x[a]);
+    }
+#pragma unroll
+  for (int b = kT - 1; b > 0; --b)
+    if (b < t) {
+      const double* cb = cv + b * t;
+#pragma unroll
+      for (int a = 0; a < b; ++a) x[a] = fma(-cb[a], x[b], x[a]);
+    }
+#pragma unroll
+  for (int a = 0; a < kT; ++a)
+    if (a < t) X[(c0 + a) * 64 + c] = x[a];
+}
+
+// chain block values of one scenario into cv (all threads of the workgroup),
+// row by row or (kCol) column by column
+template <bool kCol = false>
 __device__ __forceinline__ void chain_gather(const DP& d, const double* lu, double* cv) {
-  const int tt = d.chain_t * d.chain_t;
+  const int t = d.chain_t, tt = t * t;
   for (int e = threadIdx.x; e < tt; e += blockDim.x) {
-    const int pp = d.chain_pos[e];
+    const int pp = d.chain_pos[kCol ? e % t * t + e / t : e];
     cv[e] = pp >= 0 ? lu[pp] : 0.0;
   }
 }
@@ -452,7 +441,7 @@ __device__ __forceinline__ void chain_factor(const DP& d, double* lu, double* in
 #pragma unroll
   for (int b = 0; b < kChainMax; ++b) row[b] = pos[b] >= 0 ? lu[pos[b]] : 0.0;
   auto pivot = [&](int j, double ujj) {
-    const double inv = 1.0 / ujj;
+    const double inv = rcp_nr(ujj);
     if (lane == j) {
       if (!(fabs(ujj) > 0.0 && fabs(ujj) >= 1e-10 * rmax[c0 + j]) || !isfinite(ujj))
         raise_status(d, RKKT_ERR_SINGULAR_GX, k);
@@ -460,43 +449,42 @@ __device__ __forceinline__ void chain_factor(const DP& d, double* lu, double* in
     }
     return inv;
   };
-  if (t <= 16) {
-    // rows in lanes 0..15: row j's entries reach the other rows as DPP
-    // broadcasts of lane j within the row of 16 lanes, and only the columns
-    // of the chain are touched
-    auto elim = [&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      if (j < t) {
-        const double inv = pivot(j, row_bcast<j>(row[j]));
-        const double l = row[j] * inv;
-        const bool upd = own && lane > j;
-        if (upd) row[j] = l;
-#pragma unroll
-        for (int b = j + 1; b < 16; ++b)
-          if (b < t) {
-            const double ub = row_bcast<j>(row[b]);
-            if (upd) row[b] = fma(-l, ub, row[b]);
-          }
-      }
+  // Row j's entries reach the other rows as DPP broadcasts of lane j within
+  // the row of 16 lanes (up to 16 rows) or with readlane.  Column j + 1 goes
+  // first, so the next pivot's reciprocal is formed beside the updates of the
+  // other columns; those are taken four at a time (columns past the chain are
+  // zero and stay so).
+  auto eliminate = [&](auto rows) {
+    constexpr int kT = decltype(rows)::value;
+    auto entry = [&](auto jc, double v) {
+      if constexpr (kT <= 16) return row_bcast<decltype(jc)::value>(v);
+      else return readlane_d(v, decltype(jc)::value);
     };
-    for_each_const(elim, std::make_integer_sequence<int, 16>{});
-  } else {
+    double inv = pivot(0, entry(std::integral_constant<int, 0>{}, row[0]));
+    for_each_const([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      if (j >= t) return;
+      const double l = row[j] * inv;
+      const bool upd = own && lane > j;
+      if (upd) row[j] = l;
+      if constexpr (j + 1 < kT) {
+        const double u1 = entry(jc, row[j + 1]);
+        if (upd) row[j + 1] = fma(-l, u1, row[j + 1]);
+        if (j + 1 < t) inv = pivot(j + 1, entry(std::integral_constant<int, j + 1>{}, row[j + 1]));
 #pragma unroll
-    for (int j = 0; j < kChainMax; ++j) {
-      if (j < t) {
-        const double inv = pivot(j, readlane_d(row[j], j));
-        const double l = row[j] * inv;
-        const bool upd = own && lane > j;
-        if (upd) row[j] = l;
+        for (int b0 = j + 2; b0 < kT; b0 += 4)
+          if (b0 < t) {
 #pragma unroll
-        for (int b = j + 1; b < kChainMax; ++b)
-          if (b < t) {
-            const double ub = readlane_d(row[b], j);
-            if (upd) row[b] = fma(-l, ub, row[b]);
+            for (int b = b0; b < b0 + 4 && b < kT; ++b) {
+              const double ub = entry(jc, row[b]);
+              if (upd) row[b] = fma(-l, ub, row[b]);
+            }
           }
       }
-    }
-  }
+    }, std::make_integer_sequence<int, kT>{});
+  };
+  if (t <= 16) eliminate(std::integral_constant<int, 16>{});
+  else eliminate(std::integral_constant<int, kChainMax>{});
 #pragma unroll
   for (int b = 0; b < kChainMax; ++b)
     if (pos[b] >= 0) lu[pos[b]] = row[b];
@@ -592,26 +580,42 @@ __device__ __forceinline__ void refactor_body(const DP& d, int bx_, int by_, int
     gsync();
   }
   for (int q = 0; q < d.nph_u; ++q) {
-    {
-      const int e1 = ptr[q * G + gl + 1];
-      for (int e = ptr[q * G + gl]; e < e1; ++e) {
-        const Ent t = ent_at<kLDS>(ent, e);  // (position of l_ik, of u_kk, |U(k)|, first target)
-        const double l = lu[t.a] * (1.0 / lu[t.b]);
-        lu[t.a] = l;
-        const int* dst = upd + t.d;
-        const double* src = lu + t.b + 1;
-        int j = 0;
-        for (; j + 4 <= t.c; j += 4) {
-          const int d0 = dst[j], d1 = dst[j + 1], d2 = dst[j + 2], d3 = dst[j + 3];
-          const double s0 = src[j], s1 = src[j + 1], s2 = src[j + 2], s3 = src[j + 3];
-          const double o0 = lu[d0], o1 = lu[d1], o2 = lu[d2], o3 = lu[d3];
-          lu[d0] = fma(-l, s0, o0);
-          lu[d1] = fma(-l, s1, o1);
-          lu[d2] = fma(-l, s2, o2);
-          lu[d3] = fma(-l, s3, o3);
-        }
-        for (; j < t.c; ++j) lu[dst[j]] = fma(-l, src[j], lu[dst[j]]);
+    // One wavefront issues everything here, so instructions count as much as
+    // the dependent LDS reads do.  An entry's next one is read before its own
+    // stores, and its targets' current values go out beside the reciprocal
+    // (l_ik is stored last); eight targets at a time under masks took half as
+    // long again.
+    const int e1 = ptr[q * G + gl + 1];
+    int e = ptr[q * G + gl];
+    Ent t{0, 0, 0, 0};
+    if (e < e1) t = ent_at<kLDS>(ent, e);
+    for (; e < e1; ++e) {
+      // t = (position of l_ik, of u_kk, |U(k)|, first target)
+      const Ent cur = t;
+      const double l = lu[cur.a] * rcp_nr(lu[cur.b]);
+      const int* dst = upd + cur.d;
+      const double* src = lu + cur.b + 1;
+      if (e + 1 < e1) t = ent_at<kLDS>(ent, e + 1);
+      int j = 0;
+      for (; j + 4 <= cur.c; j += 4) {
+        const int d0 = dst[j], d1 = dst[j + 1], d2 = dst[j + 2], d3 = dst[j + 3];
+        const double s0 = src[j], s1 = src[j + 1], s2 = src[j + 2], s3 = src[j + 3];
+        const double o0 = lu[d0], o1 = lu[d1], o2 = lu[d2], o3 = lu[d3];
+        lu[d0] = fma(-l, s0, o0);
+        lu[d1] = fma(-l, s1, o1);
+        lu[d2] = fma(-l, s2, o2);
+        lu[d3] = fma(-l, s3, o3);
       }
+      if (j + 2 <= cur.c) {
+        const int d0 = dst[j], d1 = dst[j + 1];
+        const double s0 = src[j], s1 = src[j + 1];
+        const double o0 = lu[d0], o1 = lu[d1];
+        lu[d0] = fma(-l, s0, o0);
+        lu[d1] = fma(-l, s1, o1);
+        j += 2;
+      }
+      if (j < cur.c) lu[dst[j]] = fma(-l, src[j], lu[dst[j]]);
+      lu[cur.a] = l;
     }
     gsync();
   }
@@ -623,13 +627,21 @@ __device__ __forceinline__ void refactor_body(const DP& d, int bx_, int by_, int
   for (int i = gl; i < d.chain_c0; i += G) {
     const double p = lu[f_diag[i]];
     if (!(fabs(p) > 0.0 && fabs(p) >= 1e-10 * rmax[i]) || !isfinite(p)) raise_status(d, RKKT_ERR_SINGULAR_GX, k);
-    invd[i] = 1.0 / p;
+    invd[i] = rcp_nr(p);
   }
   gsync();
   // scale the columns of the strict upper part by 1/u_jj
   for (int i = gl; i < nx; i += G) {
     const int e1 = f_ptr[i + 1];
-    for (int e = f_diag[i] + 1; e < e1; ++e) lu[e] *= invd[f_col[e]];
+    constexpr int kB = 8;  // entries in flight
+    for (int e = f_diag[i] + 1; e < e1; e += kB) {
+      int c[kB];
+#pragma unroll
+      for (int u = 0; u < kB; ++u) c[u] = e + u < e1 ? f_col[e + u] : -1;
+#pragma unroll
+      for (int u = 0; u < kB; ++u)
+        if (c[u] >= 0) lu[e + u] *= invd[c[u]];
+    }
   }
   if (kLDS) {
     gsync();
@@ -732,12 +744,10 @@ __device__ __forceinline__ void reduce_body(const DP& d, int bx_, int by_, int g
   chain_gather(d, lu, cv);
   __syncthreads();
   // step 1
-  const bool chain_lane = slot == 0 && (kLDS || colok);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   sweep<kLDS, false>(uptr, uent, d.nph_ru, S, slot, colok, lu, T, ldT, c, bsync);
   if (d.chain_t > 0) {
-    if (chain_lane) chain_solveW<true, false>(d, cv, T, ldT, c);
-    __syncthreads();
-    if (chain_lane) chain_solveW<false, false>(d, cv, T, ldT, c);
+    chain_solveR<false>(d, cv, T, ldT, wv, min(W, nu - c0));
     __syncthreads();
   }
   sweep<kLDS, false>(dptr, dent, d.nph_rd, S, slot, colok, lu, T, ldT, c, bsync);
@@ -770,9 +780,7 @@ __device__ __forceinline__ void reduce_body(const DP& d, int bx_, int by_, int g
   // step 3: U^T sweep, L^T sweep, then L_u - G_u^T (G_x^-T L_x)
   sweep<kLDS, true>(uptr, uent, d.nph_ru, S, slot, colok, lu, Lx, W, c, bsync);
   if (d.chain_t > 0) {
-    if (chain_lane) chain_solveW<true, true>(d, cv, Lx, W, c);
-    __syncthreads();
-    if (chain_lane) chain_solveW<false, true>(d, cv, Lx, W, c);
+    chain_solveR<true>(d, cv, Lx, W, wv, min(W, nu - c0));
     __syncthreads();
   }
   sweep<kLDS, true>(dptr, dent, d.nph_rd, S, slot, colok, lu, Lx, W, c, bsync);
@@ -795,70 +803,71 @@ __global__ __launch_bounds__(kRT) void k_reduce(DP d) {
 // the K pattern and the factor values a wavefront reads are the same for all
 // of its lanes, so the schedule and the pattern come through scalar loads
 // (wave-uniform indices) and the factor values as LDS broadcasts; only the
-// panel arithmetic runs on the vector unit.  Entries of a phase are taken
-// four at a time with all their loads issued first.
+// panel arithmetic runs on the vector unit.  Entries are taken one at a time:
+// four with all their panel reads first was slower (30 us for the two sweeps
+// of the 118-bus grid against 22), the instructions for short groups costing
+// more than the overlapped reads gained.
 constexpr int kW64 = 64, kS64 = kRT / kW64;
 
 template <bool kTrans, typename Sync>
 __device__ __forceinline__ void sweep64(const int* __restrict__ ptr, const int4* __restrict__ ent,
-                                        int nphase, int wv, const double* __restrict__ lu, double* X,
-                                        int ld, int c, Sync sync) {
-  // Software pipeline over phases with vector loads, which have a wait
-  // counter of their own, so the phase's LDS waits never wait for them:
-  // phase bounds three phases ahead (lanes 0 and 1), entries two phases
-  // ahead and factor values one phase ahead (lane u holds entry u).
+                                        int nphase, int nent, int wv, const double* __restrict__ lu,
+                                        double* X, int ld, int c, Sync sync) {
+  // A phase is short (one to three entries per wavefront on the 118-bus
+  // grid), so nothing in it may wait for global memory: the bounds of 64
+  // phases sit in the lanes (lane q: phase q), entries are loaded three phases
+  // ahead and factor values one ahead (lane u holds entry u; lanes past the
+  // phase's last entry hold others, which nothing reads).  The phases are
+  // unrolled over the ring of four entry registers and every load is
+  // unconditional, so that the wait before a phase counts only the loads it
+  // needs: registers rotated with moves, or loads under a lane mask, waited in
+  // every phase for the loads just issued (22 us for the two sweeps of the
+  // 118-bus grid, 20 us so; the rest is LDS throughput, four clocks per panel
+  // access of a wavefront, and a barrier per phase).
+  if (nent == 0) return;
   const int lane = threadIdx.x & 63;
-  auto bounds = [&](int q) -> int {
-    return q < nphase && lane < 2 ? ptr[q * kS64 + wv + lane] : 0;
-  };
-  auto first = [](int bq) { return __builtin_amdgcn_readlane(bq, 0); };
-  auto count = [](int bq) { return __builtin_amdgcn_readlane(bq, 1) - __builtin_amdgcn_readlane(bq, 0); };
-  auto entries = [&](int bq) -> int4 {
-    const int b = first(bq), n = count(bq);
-    return lane < n ? ent[b + lane] : make_int4(-1, 0, 0, 0);
-  };
-  auto values = [&](int4 ev) -> double { return ev.x >= 0 ? lu[kTrans ? ev.w : ev.z] : 0.0; };
-  int bq0 = bounds(0), bq1 = bounds(1), bq2 = bounds(2);
-  int4 ev0 = entries(bq0), ev1 = entries(bq1);
-  double lv0 = values(ev0);
-  for (int q = 0; q < nphase; ++q) {
-    const double lv1 = values(ev1);
-    const int4 ev2 = entries(bq2);
-    const int bq3 = bounds(q + 3);
-    const int b0 = first(bq0), n = count(bq0);
-    int cur = -1;
-    double acc = 0.0;
-    const int m = min(n, 64);
-    for (int u = 0; u < m; ++u) {
-      const int dst = __builtin_amdgcn_readlane(ev0.x, u), src = __builtin_amdgcn_readlane(ev0.y, u);
-      const double v = readlane_d(lv0, u);
-      const double x = X[src * ld + c];
-      if (dst != cur) {
-        if (cur >= 0) X[cur * ld + c] = acc;
-        cur = dst;
-        acc = X[cur * ld + c];
+  for (int p0 = 0; p0 < nphase; p0 += 64) {
+    const int np = min(64, nphase - p0), pq = p0 + min(lane, np - 1);
+    const int bs = ptr[pq * kS64 + wv], be = lane < np ? ptr[pq * kS64 + wv + 1] : bs;
+    auto entries = [&](int q) -> int4 {
+      return ent[min(__builtin_amdgcn_readlane(bs, min(q, 63)) + lane, nent - 1)];
+    };
+    auto values = [&](int4 ev) -> double { return lu[kTrans ? ev.w : ev.z]; };
+    int4 ev[4] = {entries(0), entries(1), entries(2), make_int4(0, 0, 0, 0)};
+    double lv[2] = {values(ev[0]), 0.0};
+    auto phase = [&](int q, int4 e0, double l0) {
+      const int b0 = __builtin_amdgcn_readlane(bs, q), n = __builtin_amdgcn_readlane(be, q) - b0;
+      int cur = -1;
+      double acc = 0.0;
+      auto entry = [&](int dst, int src, double v) {
+        const double x = X[src * ld + c];
+        if (dst != cur) {
+          if (cur >= 0) X[cur * ld + c] = acc;
+          cur = dst;
+          acc = X[cur * ld + c];
+        }
+        acc = fma(-v, x, acc);
+      };
+      const int m = min(n, 64);
+      for (int u = 0; u < m; ++u)
+        entry(__builtin_amdgcn_readlane(e0.x, u), __builtin_amdgcn_readlane(e0.y, u), readlane_d(l0, u));
+      // entries past the 64 held in lanes, one at a time
+      for (int e = b0 + 64; e < b0 + n; ++e) {
+        const int4 t = ent[e];
+        entry(t.x, t.y, lu[kTrans ? t.w : t.z]);
       }
-      acc = fma(-v, x, acc);
-    }
-    // entries past the 64 held in lanes, one at a time
-    for (int e = b0 + 64; e < b0 + n; ++e) {
-      const int4 t = ent[e];
-      const double x = X[t.y * ld + c];
-      if (t.x != cur) {
-        if (cur >= 0) X[cur * ld + c] = acc;
-        cur = t.x;
-        acc = X[cur * ld + c];
+      if (cur >= 0) X[cur * ld + c] = acc;
+      sync();
+    };
+    // phases past the last are empty
+    for (int q0 = 0; q0 < np; q0 += 4) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lv[(j + 1) & 1] = values(ev[(j + 1) & 3]);
+        ev[(j + 3) & 3] = entries(q0 + j + 3);
+        phase(q0 + j, ev[j], lv[j & 1]);
       }
-      acc = fma(-lu[kTrans ? t.w : t.z], x, acc);
     }
-    if (cur >= 0) X[cur * ld + c] = acc;
-    sync();
-    bq0 = bq1;
-    bq1 = bq2;
-    bq2 = bq3;
-    ev0 = ev1;
-    ev1 = ev2;
-    lv0 = lv1;
   }
 }
 
@@ -930,14 +939,16 @@ __device__ __forceinline__ void sweep64g(const int* __restrict__ ptr, const int4
 
 template <bool kTrans, bool kLDS, typename Sync>
 __device__ __forceinline__ void sweep64_any(const int* __restrict__ ptr, const int4* __restrict__ ent,
-                                            int nphase, int wv, const double* __restrict__ lu, double* X,
-                                            int ld, int c, Sync sync) {
-  if constexpr (kLDS) sweep64<kTrans>(ptr, ent, nphase, wv, lu, X, ld, c, sync);
+                                            int nphase, int nent, int wv, const double* __restrict__ lu,
+                                            double* X, int ld, int c, Sync sync) {
+  if constexpr (kLDS) sweep64<kTrans>(ptr, ent, nphase, nent, wv, lu, X, ld, c, sync);
   else sweep64g<kTrans>(ptr, ent, nphase, wv, lu, X, ld, c, sync);
 }
 
 template <bool kLDS, int kVar>
 __device__ __forceinline__ void reduce64_body(const DP& d, int bx_, int by_, int gx_) {
+  // the panel in LDS and no transposed solves: the chain's coefficients column by column
+  constexpr bool kChainCol = kLDS && kVar == 2;
   const int k = by_, tile = bx_;
   const int c0 = tile * kW64, nx = d.nx, nu = d.nu, nz = d.nz;
   const int tid = threadIdx.x, c = tid & 63;
@@ -1035,19 +1046,27 @@ __device__ __forceinline__ void reduce64_body(const DP& d, int bx_, int by_, int
   if (colok)
     for (int j = d.guc_ptr[col] + wv; j < d.guc_ptr[col + 1]; j += kS64)
       T[(long long)d.guc_row[j] * ldT + c] = -gu_val(j);
-  chain_gather(d, lu, cv);
+  chain_gather<kChainCol>(d, lu, cv);
   __syncthreads();
   // step 1: T = -G_x^-1 G_u V
   const int4* uent = static_cast<const int4*>(d.ru_ent);
   const int4* dent = static_cast<const int4*>(d.rd_ent);
   // every lane sweeps (barriers stay uniform); lanes past n_u work on
   // padding columns inside the panel, which nothing reads
-  sweep64_any<false, kLDS>(d.ru_ptr, uent, d.nph_ru, wv, lu, T, ldT, c, bsync);
+  sweep64_any<false, kLDS>(d.ru_ptr, uent, d.nph_ru, d.n_sent, wv, lu, T, ldT, c, bsync);
   if (d.chain_t > 0) {
-    chain_solveR<false>(d, cv, T, ldT, wv);
+    if constexpr (kChainCol) {
+      if (wv == 0) {
+        if (d.chain_t <= 16) chain_solveC<16>(d, cv, T, c);
+        else if (d.chain_t <= 24) chain_solveC<24>(d, cv, T, c);
+        else chain_solveC<kChainMax>(d, cv, T, c);
+      }
+    } else {
+      chain_solveR<false>(d, cv, T, ldT, wv, kW64);
+    }
     __syncthreads();
   }
-  sweep64_any<false, kLDS>(d.rd_ptr, dent, d.nph_rd, wv, lu, T, ldT, c, bsync);
+  sweep64_any<false, kLDS>(d.rd_ptr, dent, d.nph_rd, d.n_sent, wv, lu, T, ldT, c, bsync);
   if (colok)
     for (int i = wv; i < nx; i += kS64) T[(long long)i * ldT + c] *= invd[i];
   __syncthreads();
@@ -1246,12 +1265,12 @@ __device__ __forceinline__ void reduce64_body(const DP& d, int bx_, int by_, int
     }
   }
   __syncthreads();
-  sweep64_any<true, kLDS>(d.ru_ptr, uent, d.nph_ru, wv, lu, Lx, kW64, c, bsync);
+  sweep64_any<true, kLDS>(d.ru_ptr, uent, d.nph_ru, d.n_sent, wv, lu, Lx, kW64, c, bsync);
   if (d.chain_t > 0) {
-    chain_solveR<true>(d, cv, Lx, kW64, wv);
+    chain_solveR<true>(d, cv, Lx, kW64, wv, kW64);
     __syncthreads();
   }
-  sweep64_any<true, kLDS>(d.rd_ptr, dent, d.nph_rd, wv, lu, Lx, kW64, c, bsync);
+  sweep64_any<true, kLDS>(d.rd_ptr, dent, d.nph_rd, d.n_sent, wv, lu, Lx, kW64, c, bsync);
   // G_u^T product: the entries of a column of G_u loaded kGB at a time
   // before their multiply-adds (summed in pattern order)
   if (colok)
