@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "mlp_dev.h"
 
@@ -54,25 +55,63 @@ __device__ __forceinline__ float gelu_grad(float a) {
   return 0.5f * (1.0f + erff(a * 0.70710678118654752f)) + a * expf(-0.5f * a * a) * 0.39894228040143268f;
 }
 
-// 8 consecutive BF16 values row[kk .. kk + 7], zero from k = K on.  The row's
-// pitch is at least K rounded up to 8, so a granule that starts below K lies
-// inside the row.
-__device__ __forceinline__ uint4 frag8(const uint16_t* __restrict__ row, int kk, int K) {
-  if (kk >= K) return make_uint4(0u, 0u, 0u, 0u);
-  uint4 v = *reinterpret_cast<const uint4*>(row + kk);
-  const int nv = K - kk;
-  if (nv < 8) {
-    uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t lo = 2 * q < nv ? 0x0000ffffu : 0u;
-      const uint32_t hi = 2 * q + 1 < nv ? 0xffff0000u : 0u;
-      w[q] &= lo | hi;
-    }
-    v = make_uint4(w[0], w[1], w[2], w[3]);
+// sum over the kT threads of a workgroup in halving steps (thread 0 returns it)
+__device__ __forceinline__ float block_sum(float v, float* red) {
+  red[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = kT / 2; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
   }
-  return v;
+  return red[0];
 }
+
+// values k + 2 q, k + 2 q + 1 (q = 0..3) of a fragment that has nv <= 8 valid
+// ones left, the others zero
+__device__ __forceinline__ uint4 keep_first(uint4 v, int nv) {
+  uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t lo = 2 * q < nv ? 0x0000ffffu : 0u;
+    const uint32_t hi = 2 * q + 1 < nv ? 0xffff0000u : 0u;
+    w[q] &= lo | hi;
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// A fragment as loaded (8 consecutive k of one row, from kk on) and as the
+// products take it.  Loading neither masks nor converts, so nothing waits for
+// a load before its k step comes up; a granule past K loads the row's last one
+// and is masked then.
+//   BF16 rows: the pitch is at least K rounded up to 8, so every granule that
+//   starts below K lies inside the row.
+struct FragBf16 {
+  uint4 v;
+  __device__ __forceinline__ void load(const uint16_t* row, int kk, int K) {
+    v = *reinterpret_cast<const uint4*>(row + min(kk, (K + 7) / 8 * 8 - 8));
+  }
+  __device__ __forceinline__ uint4 get() const { return v; }
+};
+
+//   FP32 rows (the network's input, pitch K, aligned to 4 bytes): rounded to
+//   BF16 when taken.
+struct FragF32 {
+  float v[8];
+  __device__ __forceinline__ void load(const float* row, int kk, int K) {
+    if (kk + 8 <= K) {
+      __builtin_memcpy(v, row + kk, sizeof(v));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = row[min(kk + j, K - 1)];
+    }
+  }
+  __device__ __forceinline__ uint4 get() const {
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = (uint32_t)to_bf16(v[2 * q]) | ((uint32_t)to_bf16(v[2 * q + 1]) << 16);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  }
+};
 
 __device__ __forceinline__ f32x4 mfma(uint4 a, uint4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
@@ -85,19 +124,35 @@ __device__ __forceinline__ f32x4 mfma(uint4 a, uint4 b, f32x4 c) {
 // wavefront order, and wavefront w then applies the epilogue to block
 // (w / 2, w % 2) of the tile.
 constexpr int kGemmWaves = 4;
+constexpr int kGemmT = 64 * kGemmWaves;
 
-template <int EPI>
-__global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(MlpGemm g) {
-  __shared__ f32x4 part[kGemmWaves][4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+template <int EPI, typename FragA>
+__device__ void gemm_tile(const MlpGemm& g, int bx, int by, int nbx, f32x4 (*part)[4][64]) {
+  constexpr bool kF32 = sizeof(FragA) != sizeof(FragBf16);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = by * 32, n0 = bx * 32;
   const int r16 = lane & 15, kq = (lane >> 4) * 8;
-  const uint16_t* pa[2];
+  const std::conditional_t<kF32, float, uint16_t>* pa[2];
   const uint16_t* pb[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    pa[i] = g.A + (long long)min(m0 + 16 * i + r16, g.M - 1) * g.lda;
+    const long long m = min(m0 + 16 * i + r16, g.M - 1);
+    if constexpr (kF32)
+      pa[i] = g.x + m * g.lda;
+    else
+      pa[i] = g.A + m * g.lda;
     pb[i] = g.B + (long long)min(n0 + 16 * i + r16, g.N - 1) * g.ldb;
+  }
+  // the epilogue of this wavefront: block (i, j) = (w / 2, w % 2), the lane
+  // holds rows mr .. mr + 3 of column nc; what it reads is loaded here
+  constexpr bool kHalf = EPI == kMlpBiasGelu || EPI == kMlpGeluBack || EPI == kMlpOutGrad;
+  const int mr = m0 + 16 * (w >> 1) + 4 * (lane >> 4);
+  const int nc = n0 + 16 * (w & 1) + r16;
+  float bias = 0.0f, zin[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (EPI == kMlpBiasGelu || EPI == kMlpBiasOut || EPI == kMlpOutGrad) bias = g.bias[min(nc, g.N - 1)];
+  if (EPI == kMlpGeluBack || EPI == kMlpOutGrad) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) zin[r] = g.zin[(long long)min(mr + r, g.M - 1) * g.ldz + min(nc, g.N - 1)];
   }
   f32x4 acc[2][2];
 #pragma unroll
@@ -105,19 +160,46 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(MlpGemm g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   constexpr int kStride = 32 * kGemmWaves;
-  uint4 a[2], b[2];
+  FragA fa[2];
+  FragBf16 fb[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    a[i] = frag8(pa[i], 32 * w + kq, g.K);
-    b[i] = frag8(pb[i], 32 * w + kq, g.K);
+    fa[i].load(pa[i], 32 * w + kq, g.K);
+    fb[i].load(pb[i], 32 * w + kq, g.K);
   }
   for (int k0 = 32 * w; k0 < g.K; k0 += kStride) {
-    uint4 an[2], bn[2];
-    const int kn = k0 + kStride + kq;
+    FragA an[2];
+    FragBf16 bn[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      an[i] = frag8(pa[i], kn, g.K);
-      bn[i] = frag8(pb[i], kn, g.K);
+      an[i].load(pa[i], k0 + kStride + kq, g.K);
+      bn[i].load(pb[i], k0 + kStride + kq, g.K);
+    }
+    uint4 a[2], b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a[i] = fa[i].get();
+      b[i] = fb[i].get();
+    }
+    if (k0 + 32 > g.K) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = keep_first(a[i], g.K - k0 - kq);
+        b[i] = keep_first(b[i], g.K - k0 - kq);
+      }
+    }
+    // the input's transposed copy (operand of dW_0): the tiles of a row of
+    // tiles all pass over its k steps and share them out
+    if (kF32 && g.xt && (k0 >> 5) % nbx == bx) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int m = m0 + 16 * i + r16;
+        const uint32_t v[4] = {a[i].x, a[i].y, a[i].z, a[i].w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (m < g.M && k0 + kq + j < g.K)
+            g.xt[(long long)(k0 + kq + j) * g.ldt + m] = (uint16_t)(v[j >> 1] >> (16 * (j & 1)));
+      }
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -125,8 +207,8 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(MlpGemm g) {
       for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i], b[j], acc[i][j]);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      a[i] = an[i];
-      b[i] = bn[i];
+      fa[i] = an[i];
+      fb[i] = bn[i];
     }
   }
 #pragma unroll
@@ -134,47 +216,91 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(MlpGemm g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) part[w][2 * i + j][lane] = acc[i][j];
   __syncthreads();
-  // epilogue of block (i, j) = (w / 2, w % 2): lane holds rows mr .. mr + 3 of column nc
-  const int i = w >> 1, j = w & 1;
   f32x4 t = part[0][w][lane];
 #pragma unroll
   for (int q = 1; q < kGemmWaves; ++q) t += part[q][w][lane];
-  const int mr = m0 + 16 * i + 4 * (lane >> 4);
-  const int nc = n0 + 16 * j + r16;
-  if (nc >= g.N) return;
-  float v[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = t[r];
-  uint16_t h[4];
+  float d[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t h[4];
+  // values first, then the stores: a wait for a load also waits for every
+  // store before it
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int m = mr + r;
-    if (m >= g.M) break;
-    const long long o = (long long)m * g.ldz + nc;
-    if (EPI == kMlpStore) {
-      g.zout[o] = v[r];
-    } else if (EPI == kMlpBiasGelu || EPI == kMlpBiasOut) {
-      const float z = v[r] + g.bias[nc];
-      if (g.zout) g.zout[o] = z;
-      if (EPI == kMlpBiasOut) {
-        if (g.y) g.y[(long long)m * g.N + nc] = z;
-      } else {
-        h[r] = to_bf16(gelu(z));
-        g.hout[(long long)m * g.ldh + nc] = h[r];
-      }
-    } else {  // kMlpGeluBack: dZ_{l-1} = dA g'(Z_{l-1})
-      h[r] = to_bf16(v[r] * gelu_grad(g.zin[o]));
-      g.hout[(long long)m * g.ldh + nc] = h[r];
+    if (EPI == kMlpGeluBack) h[r] = to_bf16(t[r] * gelu_grad(zin[r]));  // dZ_{l-1} = dA g'(Z_{l-1})
+    if (EPI == kMlpBiasGelu || EPI == kMlpBiasOut || EPI == kMlpOutGrad) t[r] += bias;
+    if (EPI == kMlpBiasGelu) h[r] = to_bf16(gelu(t[r]));
+    if (EPI == kMlpOutGrad) {  // dZ = (Y - T) / B
+      const float e = t[r] - zin[r];
+      h[r] = to_bf16(e * g.inv_b);
+      d[r] = mr + r < g.M && nc < g.N ? e : 0.0f;
     }
   }
-  if ((EPI == kMlpBiasGelu || EPI == kMlpGeluBack) && g.tout) {
-    uint16_t* tp = g.tout + (long long)nc * g.ldt + mr;
-    if (mr + 3 < g.M) {
-      *reinterpret_cast<uint2*>(tp) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16),
-                                                 (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-    } else {
-      for (int r = 0; r < 4 && mr + r < g.M; ++r) tp[r] = h[r];
+  if (nc < g.N) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = mr + r;
+      if (m < g.M) {
+        if (EPI == kMlpStore || (EPI == kMlpBiasGelu && g.zout)) g.zout[(long long)m * g.ldz + nc] = t[r];
+        if (EPI == kMlpBiasOut) g.y[(long long)m * g.N + nc] = t[r];
+        if (kHalf) g.hout[(long long)m * g.ldh + nc] = (uint16_t)h[r];
+      }
     }
+    if (kHalf && g.tout) {
+      uint16_t* tp = g.tout + (long long)nc * g.ldt + mr;
+      if (mr + 3 < g.M) {
+        *reinterpret_cast<uint2*>(tp) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          if (mr + r < g.M) tp[r] = (uint16_t)h[r];
+      }
+    }
+  }
+  if (EPI == kMlpOutGrad) {
+    // the tile's sum of (Y - T)^2: a thread takes column tx's rows ty, ty + 8,
+    // ty + 16, ty + 24 (zero outside the batch), then halving steps
+    float* red = reinterpret_cast<float*>(part);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[(mr - m0 + r) * 33 + nc - n0] = d[r];
+    __syncthreads();
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    float sq = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sq = fmaf(red[(ty + 8 * q) * 33 + tx], red[(ty + 8 * q) * 33 + tx], sq);
+    __syncthreads();
+    const float sum = block_sum(sq, red);
+    if (threadIdx.x == 0) g.lpart[by * nbx + bx] = sum;
+  }
+}
+
+template <int EPI, typename FragA>
+__global__ __launch_bounds__(kGemmT) void k_gemm(MlpGemm g) {
+  __shared__ f32x4 part[kGemmWaves][4][64];
+  gemm_tile<EPI, FragA>(g, blockIdx.x, blockIdx.y, gridDim.x, part);
+}
+
+// Everything of the backward pass that follows from dZ_l, in one launch: first
+// the tiles of dZ_{l-1} (the next launch waits for them), then those of
+// [dW_l; db_l], then, with a loss, one workgroup that adds its partial sums.
+// The gradients of 256 rows are bound by their launches (15 of them, 68.5 us):
+// with these merged, the input converted where it is read, the output gradient
+// in the last layer's epilogue and the gradients written to the caller's array
+// it is 8, 49.3 us.
+__global__ __launch_bounds__(kGemmT) void k_back(MlpGemm ga, int na, int nax, MlpGemm gw, int nw, int nwx,
+                                                 const float* __restrict__ lpart, int np, float inv_b,
+                                                 float* __restrict__ loss) {
+  __shared__ f32x4 part[kGemmWaves][4][64];
+  const int b = blockIdx.x;
+  if (b < na) {
+    gemm_tile<kMlpGeluBack, FragBf16>(ga, b % nax, b / nax, nax, part);
+  } else if (b < na + nw) {
+    gemm_tile<kMlpStore, FragBf16>(gw, (b - na) % nwx, (b - na) / nwx, nwx, part);
+  } else {
+    // loss = 0.5 inv_b sum of the partials, in a fixed order
+    float sum = 0.0f;
+    for (int i = threadIdx.x; i < np; i += kGemmT) sum += lpart[i];
+    sum = block_sum(sum, reinterpret_cast<float*>(part));
+    if (threadIdx.x == 0) *loss = 0.5f * inv_b * sum;
   }
 }
 
@@ -187,61 +313,6 @@ __global__ void k_input_bf16(const float* __restrict__ x, int rows, int cols, ui
   const uint16_t v = to_bf16(x[i]);
   h[(long long)r * ldh + c] = v;
   if (t) t[(long long)c * ldt + r] = v;
-}
-
-// dZ = (Y - T) / B in BF16, row-major and transposed, and the per-tile
-// partial sums of (Y - T)^2: one workgroup per 32 x 32 tile, the transposed
-// copy written through LDS so both stores are coalesced
-constexpr int kOG = 32, kOGT = 256;
-__global__ __launch_bounds__(kOGT) void k_out_grad(const float* __restrict__ Y, const float* __restrict__ T,
-                                                   int rows, int cols, float inv_b, uint16_t* __restrict__ h,
-                                                   int ldh, uint16_t* __restrict__ t, int ldt,
-                                                   float* __restrict__ part) {
-  __shared__ uint16_t tile[kOG][kOG + 2];
-  __shared__ float red[kOGT];
-  const int c0 = blockIdx.x * kOG, r0 = blockIdx.y * kOG;
-  const int tx = threadIdx.x % kOG, ty = threadIdx.x / kOG;
-  float sq = 0.0f;
-  for (int rr = ty; rr < kOG; rr += kOGT / kOG) {
-    const int r = r0 + rr, c = c0 + tx;
-    uint16_t v = 0;
-    if (r < rows && c < cols) {
-      const long long i = (long long)r * cols + c;
-      const float d = Y[i] - T[i];
-      sq = fmaf(d, d, sq);
-      v = to_bf16(d * inv_b);
-      h[(long long)r * ldh + c] = v;
-    }
-    tile[rr][tx] = v;
-  }
-  __syncthreads();
-  for (int cc = ty; cc < kOG; cc += kOGT / kOG) {
-    const int c = c0 + cc, r = r0 + tx;
-    if (c < cols && r < rows) t[(long long)c * ldt + r] = tile[tx][cc];
-  }
-  red[threadIdx.x] = sq;
-  __syncthreads();
-  for (int w = kOGT / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
-}
-
-// loss = 0.5 inv_b sum of the partials, in a fixed order
-constexpr int kLossT = 256;
-__global__ __launch_bounds__(kLossT) void k_loss_final(const float* __restrict__ part, int np, float inv_b,
-                                                       float* __restrict__ loss) {
-  __shared__ float red[kLossT];
-  float sum = 0.0f;
-  for (int i = threadIdx.x; i < np; i += kLossT) sum += part[i];
-  red[threadIdx.x] = sum;
-  __syncthreads();
-  for (int w = kLossT / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *loss = 0.5f * inv_b * red[0];
 }
 
 // BF16 copies of parameter i: W_l entries into W_l [fi][pitch fo] and
@@ -293,11 +364,23 @@ __global__ void k_fill_bf16(uint16_t* __restrict__ d, long long n, uint16_t v) {
 void mlp_gemm(int epi, const MlpGemm& g, hipStream_t st) {
   const dim3 grid((unsigned)((g.N + 31) / 32), (unsigned)((g.M + 31) / 32));
   switch (epi) {
-    case kMlpStore: k_gemm<kMlpStore><<<grid, 64 * kGemmWaves, 0, st>>>(g); break;
-    case kMlpBiasGelu: k_gemm<kMlpBiasGelu><<<grid, 64 * kGemmWaves, 0, st>>>(g); break;
-    case kMlpBiasOut: k_gemm<kMlpBiasOut><<<grid, 64 * kGemmWaves, 0, st>>>(g); break;
-    default: k_gemm<kMlpGeluBack><<<grid, 64 * kGemmWaves, 0, st>>>(g); break;
+    case kMlpBiasGelu:
+      if (g.x)
+        k_gemm<kMlpBiasGelu, FragF32><<<grid, kGemmT, 0, st>>>(g);
+      else
+        k_gemm<kMlpBiasGelu, FragBf16><<<grid, kGemmT, 0, st>>>(g);
+      break;
+    case kMlpBiasOut: k_gemm<kMlpBiasOut, FragBf16><<<grid, kGemmT, 0, st>>>(g); break;
+    default: k_gemm<kMlpOutGrad, FragBf16><<<grid, kGemmT, 0, st>>>(g); break;
   }
+}
+
+void mlp_back(const MlpGemm* ga, const MlpGemm& gw, const float* lpart, int np, float inv_b, float* loss,
+              hipStream_t st) {
+  const int nax = ga ? (ga->N + 31) / 32 : 1, na = ga ? nax * ((ga->M + 31) / 32) : 0;
+  const int nwx = (gw.N + 31) / 32, nw = nwx * ((gw.M + 31) / 32);
+  k_back<<<na + nw + (loss ? 1 : 0), kGemmT, 0, st>>>(ga ? *ga : MlpGemm{}, na, nax, gw, nw, nwx, lpart, np,
+                                                      inv_b, loss);
 }
 
 void mlp_input_bf16(const float* x, int rows, int cols, uint16_t* h, int ldh, uint16_t* t, int ldt,
@@ -305,15 +388,7 @@ void mlp_input_bf16(const float* x, int rows, int cols, uint16_t* h, int ldh, ui
   k_input_bf16<<<blocks((long long)rows * cols), kT, 0, st>>>(x, rows, cols, h, ldh, t, ldt);
 }
 
-int mlp_out_grad_tiles(int rows, int cols) { return ((rows + kOG - 1) / kOG) * ((cols + kOG - 1) / kOG); }
-
-void mlp_out_grad(const float* Y, const float* T, int rows, int cols, uint16_t* h, int ldh, uint16_t* t,
-                  int ldt, float* part, float* loss, hipStream_t st) {
-  const dim3 grid((unsigned)((cols + kOG - 1) / kOG), (unsigned)((rows + kOG - 1) / kOG));
-  const float inv_b = 1.0f / (float)rows;
-  k_out_grad<<<grid, kOGT, 0, st>>>(Y, T, rows, cols, inv_b, h, ldh, t, ldt, part);
-  k_loss_final<<<1, kLossT, 0, st>>>(part, mlp_out_grad_tiles(rows, cols), inv_b, loss);
-}
+int mlp_out_grad_tiles(int rows, int cols) { return ((rows + 31) / 32) * ((cols + 31) / 32); }
 
 void mlp_param_copies(const float* p, long long n, const MlpLayers& L, uint16_t* wb, uint16_t* wt,
                       hipStream_t st) {

@@ -57,45 +57,59 @@ int check(rkkt_mlp* m, const char* where) {
   return 0;
 }
 
-// Forward pass over B rows of x.  With `train`, the FP32 pre-activations and
-// the transposed activations (operands of the dW products) are kept;
-// otherwise only y is written.
-int forward_impl(rkkt_mlp* m, const float* x, int B, float* y, bool train, hipStream_t st) {
+// Forward pass over B rows of x with layer inputs act[l] (act[0] is used by
+// one-layer networks only: there y may be x, so x is converted before the
+// product that writes y; deeper networks read x in their first product).  With
+// targets t the FP32 pre-activations and the transposed activations (operands
+// of the dW products) are kept and the last product leaves the output gradient
+// and the loss's partial sums; otherwise only y is written.
+void forward_layers(rkkt_mlp* m, const float* x, int B, float* y, const float* t, uint16_t* const* act,
+                    hipStream_t st) {
   const int L = m->L;
-  rkkt::mlp_input_bf16(x, B, m->sz[0], m->A[0], mlp_pad8(m->sz[0]), train ? m->AT[0] : nullptr, m->bpit, st);
+  if (L == 1)
+    rkkt::mlp_input_bf16(x, B, m->sz[0], act[0], mlp_pad8(m->sz[0]), t ? m->AT[0] : nullptr, m->bpit, st);
   for (int l = 0; l < L; ++l) {
     const int fi = m->sz[l], fo = m->sz[l + 1];
     const bool last = l + 1 == L;
     rkkt::MlpGemm g{};
-    g.A = m->A[l];
+    g.A = act[l];
     g.lda = mlp_pad8(fi);
+    if (l == 0 && !last) {
+      g.x = x;
+      g.lda = fi;
+      g.xt = t ? m->AT[0] : nullptr;
+    }
     g.B = m->wt + m->lay.wt_off[l];
     g.ldb = m->lay.fi_p[l];
     g.M = B;
     g.N = fo;
     g.K = fi;
     g.bias = m->p + m->boff[l];
-    g.zout = train ? m->Z[l] : nullptr;
     g.ldz = fo;
+    g.ldh = mlp_pad8(fo);
+    g.ldt = m->bpit;
     if (!last) {
-      g.hout = m->A[l + 1];
-      g.ldh = mlp_pad8(fo);
-      g.tout = train ? m->AT[l + 1] : nullptr;
-      g.ldt = m->bpit;
+      g.zout = t ? m->Z[l] : nullptr;
+      g.hout = act[l + 1];
+      g.tout = t ? m->AT[l + 1] : nullptr;
+    } else if (t) {
+      g.zin = t;
+      g.inv_b = 1.0f / (float)B;
+      g.hout = m->dZb[0];
+      g.tout = m->dZT[0];
+      g.lpart = m->lpart;
     } else {
       g.y = y;
     }
-    rkkt::mlp_gemm(last ? rkkt::kMlpBiasOut : rkkt::kMlpBiasGelu, g, st);
+    rkkt::mlp_gemm(!last ? rkkt::kMlpBiasGelu : t ? rkkt::kMlpOutGrad : rkkt::kMlpBiasOut, g, st);
   }
-  return check(m, "rkkt_mlp forward");
 }
 
-int gradients_impl(rkkt_mlp* m, const float* x, const float* t, int B, float* loss, hipStream_t st) {
-  if (int rc = forward_impl(m, x, B, nullptr, true, st)) return rc;
+int gradients_impl(rkkt_mlp* m, const float* x, const float* t, int B, float* grads, float* loss,
+                   hipStream_t st) {
+  forward_layers(m, x, B, nullptr, t, m->A.data(), st);
   const int L = m->L;
   int c = 0;
-  rkkt::mlp_out_grad(m->Z[L - 1], t, B, m->sz[L], m->dZb[c], mlp_pad8(m->sz[L]), m->dZT[c], m->bpit, m->lpart,
-                     loss, st);
   for (int l = L - 1; l >= 0; --l) {
     const int fi = m->sz[l], fo = m->sz[l + 1];
     // [dW_l; db_l] = [A_l^T; 1^T] dZ_l: fi + 1 rows, the last one lands on b_l
@@ -107,26 +121,28 @@ int gradients_impl(rkkt_mlp* m, const float* x, const float* t, int B, float* lo
     gw.M = fi + 1;
     gw.N = fo;
     gw.K = B;
-    gw.zout = m->g + m->woff[l];
+    gw.zout = grads + m->woff[l];
     gw.ldz = fo;
-    rkkt::mlp_gemm(rkkt::kMlpStore, gw, st);
-    if (l == 0) break;
     // dZ_{l-1} = (dZ_l W_l^T) g'(Z_{l-1})
     rkkt::MlpGemm ga{};
-    ga.A = m->dZb[c];
-    ga.lda = mlp_pad8(fo);
-    ga.B = m->wb + m->lay.wb_off[l];
-    ga.ldb = m->lay.fo_p[l];
-    ga.M = B;
-    ga.N = fi;
-    ga.K = fo;
-    ga.zin = m->Z[l - 1];
-    ga.ldz = fi;
-    ga.hout = m->dZb[c ^ 1];
-    ga.ldh = mlp_pad8(fi);
-    ga.tout = m->dZT[c ^ 1];
-    ga.ldt = m->bpit;
-    rkkt::mlp_gemm(rkkt::kMlpGeluBack, ga, st);
+    if (l > 0) {
+      ga.A = m->dZb[c];
+      ga.lda = mlp_pad8(fo);
+      ga.B = m->wb + m->lay.wb_off[l];
+      ga.ldb = m->lay.fo_p[l];
+      ga.M = B;
+      ga.N = fi;
+      ga.K = fo;
+      ga.zin = m->Z[l - 1];
+      ga.ldz = fi;
+      ga.hout = m->dZb[c ^ 1];
+      ga.ldh = mlp_pad8(fi);
+      ga.tout = m->dZT[c ^ 1];
+      ga.ldt = m->bpit;
+    }
+    const bool first = l + 1 == L;
+    rkkt::mlp_back(l > 0 ? &ga : nullptr, gw, m->lpart, rkkt::mlp_out_grad_tiles(B, m->sz[L]), 1.0f / (float)B,
+                   first ? loss : nullptr, st);
     c ^= 1;
   }
   return check(m, "rkkt_mlp backward");
@@ -293,7 +309,8 @@ int rkkt_mlp_forward(rkkt_mlp* m, const float* x, int batch, float* y, hipStream
   if (int rc = args_ok(m, batch, "rkkt_mlp_forward")) return rc;
   if (!x || !y) return fail(m, -1, "rkkt_mlp_forward: null array");
   (void)hipGetLastError();
-  return forward_impl(m, x, batch, y, false, st);
+  forward_layers(m, x, batch, y, nullptr, m->A.data(), st);
+  return check(m, "rkkt_mlp forward");
 }
 
 int rkkt_mlp_forward_static(const rkkt_mlp* mc, const float* x, int batch, float* y, hipStream_t st) {
@@ -320,28 +337,7 @@ int rkkt_mlp_forward_static(const rkkt_mlp* mc, const float* x, int batch, float
     act[l] = reinterpret_cast<uint16_t*>(base + off);
     off += align256((size_t)batch * mlp_pad8(m->sz[l]) * sizeof(uint16_t));
   }
-  rkkt::mlp_input_bf16(x, batch, m->sz[0], act[0], mlp_pad8(m->sz[0]), nullptr, 0, st);
-  for (int l = 0; l < m->L; ++l) {
-    const int fi = m->sz[l], fo = m->sz[l + 1];
-    const bool last = l + 1 == m->L;
-    rkkt::MlpGemm g{};
-    g.A = act[l];
-    g.lda = mlp_pad8(fi);
-    g.B = m->wt + m->lay.wt_off[l];
-    g.ldb = m->lay.fi_p[l];
-    g.M = batch;
-    g.N = fo;
-    g.K = fi;
-    g.bias = m->p + m->boff[l];
-    g.ldz = fo;
-    if (!last) {
-      g.hout = act[l + 1];
-      g.ldh = mlp_pad8(fo);
-    } else {
-      g.y = y;
-    }
-    rkkt::mlp_gemm(last ? rkkt::kMlpBiasOut : rkkt::kMlpBiasGelu, g, st);
-  }
+  forward_layers(m, x, batch, y, nullptr, act.data(), st);
   return check(m, "rkkt_mlp_forward_static");
 }
 
@@ -350,12 +346,7 @@ int rkkt_mlp_gradients(rkkt_mlp* m, const float* x, const float* t, int batch, f
   if (int rc = args_ok(m, batch, "rkkt_mlp_gradients")) return rc;
   if (!x || !t || !loss) return fail(m, -1, "rkkt_mlp_gradients: null array");
   (void)hipGetLastError();
-  if (int rc = gradients_impl(m, x, t, batch, loss, st)) return rc;
-  if (grads) {
-    hipError_t e = hipMemcpyAsync(grads, m->g, m->P * sizeof(float), hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return fail(m, -2, std::string("rkkt_mlp_gradients: ") + hipGetErrorString(e));
-  }
-  return 0;
+  return gradients_impl(m, x, t, batch, grads ? grads : m->g, loss, st);
 }
 
 int rkkt_mlp_train_step(rkkt_mlp* m, const float* x, const float* t, int batch, float lr, float* loss,
@@ -363,7 +354,7 @@ int rkkt_mlp_train_step(rkkt_mlp* m, const float* x, const float* t, int batch, 
   if (int rc = args_ok(m, batch, "rkkt_mlp_train_step")) return rc;
   if (!x || !t || !loss) return fail(m, -1, "rkkt_mlp_train_step: null array");
   (void)hipGetLastError();
-  if (int rc = gradients_impl(m, x, t, batch, loss, st)) return rc;
+  if (int rc = gradients_impl(m, x, t, batch, m->g, loss, st)) return rc;
   m->t += 1;
   rkkt::mlp_adam(m->p, m->g, m->m, m->v, m->P, lr, m->t, m->lay, m->wb, m->wt, st);
   return check(m, "rkkt_mlp_train_step");
