@@ -377,6 +377,7 @@ int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const dou
       r.vstride = t.vstride;
       r.ncjob = (int)t.cjobs.size() / 2;
       r.nlev = (int)t.lev_ptr.size() - 1;
+      r.nwide = rkkt::tree_wide_levels(t);
       const size_t ld = (size_t)t.ngroup * t.T * rkkt::kTreeB;
       if ((e = dalloc(p, &r.slab, (size_t)s.N * t.stride)) != hipSuccess) goto hip_error;
       if ((e = hipMemset2D(r.slab + t.zero, sizeof(double) * t.stride, 0,

@@ -23,7 +23,7 @@ struct TreeDP {
   const int *pair_g, *pair_ptr, *pair_nodes, *gstrip;
   const int *cjobs, *sn_ptr, *sn;
   const short *rmap, *smap;
-  int vstride, ncjob, nlev;
+  int vstride, ncjob, nlev, nwide;
   int npool, nstrip, T, ngroup, parts, sparts, npair, nkuu;
   long long stride, zero;
   double *slab;  // [N][stride] fronts

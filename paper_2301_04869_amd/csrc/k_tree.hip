@@ -851,32 +851,105 @@ __device__ __forceinline__ void load_lu(v4d (&lu)[kTreeNB * kTreeNB], const doub
     if (q < nbb) lu[q] = load_blk(p + q * kTreeBlk, lane);
 }
 
-// Sweep up over the levels [l0, l1): workgroup bx of gx takes kTreeStepNodes
-// nodes at a time, kTreeNB wavefronts each: right-hand sides by block rows,
-// V_b by the first wavefront (its LU loads issued first), Y_b by block rows,
-// the interface strips dealt to the wavefronts.  gx > 1 for one level only.
-// Bound by the latency of each step of the chain.
+// a value that every lane holds, in scalar registers: addresses built on it
+// take no vector registers
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni(long long v) {
+  return (long long)(unsigned)uni((int)v) | (long long)uni((int)(v >> 32)) << 32;
+}
+
+// The three blocks of every pivot block row j in a node's interface strip m:
+// G_IJ^T, V, Y in blk[3 j ..] (past the last one the last again, without a
+// branch per load)
+__device__ __forceinline__ void load_strip(v4d (&blk)[3 * kTreeNB], const double* slab, const TreeNode& n,
+                                           int m, int nb, int lane) {
+#pragma unroll
+  for (int j = 0; j < kTreeNB; ++j) {
+    const long long at = (long long)(m * nb + min(j, nb - 1)) * kTreeBlk;
+    blk[3 * j] = load_blk(slab + uni(n.gijt) + at, lane);
+    blk[3 * j + 1] = load_blk(slab + uni(n.v) + at, lane);
+    blk[3 * j + 2] = load_blk(slab + uni(n.y) + at, lane);
+  }
+}
+
+// A workgroup takes kTreeStepNodes nodes at a time, kTreeNB wavefronts each,
+// or one node with all its wavefronts where a level has a workgroup per node
+// or one node is left.
+struct SweepTurn {
+  bool solo, act, own;  // one node; this wavefront has work; its group owns the block rows
+  int node, cnt, me;    // place in the level; wavefronts of the node, this one among them
+};
+__device__ __forceinline__ SweepTurn sweep_turn(int qq, int q1, int step, int wv) {
+  SweepTurn t;
+  const int grp = wv / kTreeNB;
+  t.solo = step == 1 || q1 - qq < 2;
+  t.act = t.solo || qq + grp < q1;
+  t.own = t.solo ? grp == 0 : t.act;
+  t.node = t.solo ? qq : min(qq + grp, q1 - 1);
+  t.cnt = t.solo ? kTreeNB * kTreeStepNodes : kTreeNB;
+  t.me = t.solo ? wv : wv % kTreeNB;
+  return t;
+}
+
+// Sweep up over the levels [l0, l1), workgroup bx of gx: right-hand sides by
+// block rows, V_b by the first wavefront (its LU loads issued first), Y_b by
+// block rows, the interface strips dealt to the wavefronts, the first one last:
+// the others load their first strip and add up its children's parts while V_b
+// is solved.  gx > 1 for one level only.  Bound by
+// the latency of each step of the chain: with a strip's loads in its loop, one
+// pivot block after the other, one child after the other, and half the
+// wavefronts idle in levels of one node, a level took 12.8 us at 1354 buses (11
+// now).  K_JJ is loaded behind the solve: the LU blocks' registers are free then.
 __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k, int l0, int l1) {
   __shared__ double s3[kTreeStepNodes][kTreeRows], s1[kTreeStepNodes][kTreeRows];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lm = lane & 15, lk = lane >> 4, grp = wv / kTreeNB, p = wv % kTreeNB;
+  const int lm = lane & 15, lk = lane >> 4, p = wv % kTreeNB;
   const double* slab = d.tr.slab + (long long)k * d.tr.stride;
   double* vec = d.tr.vec + (long long)k * d.tr.vstride;
-  double *b3 = s3[grp], *b1 = s1[grp];
   for (int l = l0; l < l1; ++l) {
-    const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
-    for (int qq = q0 + bx * kTreeStepNodes; qq < q1; qq += gx * kTreeStepNodes) {
-      const bool act = qq + grp < q1;
-      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[min(qq + grp, q1 - 1)]];
-      const int nb = n.nb, ib = n.ib;
-      const bool row = act && p < nb;
+    const int q0 = uni(d.tr.lev_ptr[l]);
+    const int q1 = uni(d.tr.lev_ptr[l + 1]);
+    const int step = gx > 1 && gx >= q1 - q0 ? 1 : kTreeStepNodes;
+    for (int qq = q0 + bx * step; qq < q1; qq += gx * step) {
+      const SweepTurn tn = sweep_turn(qq, q1, step, wv);
+      const TreeNode& n = d.tr.nodes[uni(d.tr.lev_nodes[tn.node])];
+      double *b3 = s3[tn.solo ? 0 : wv / kTreeNB], *b1 = s1[tn.solo ? 0 : wv / kTreeNB];
+      const int nb = uni(n.nb), ib = uni(n.ib), nchild = uni(n.nchild);
+      const bool row = tn.own && p < nb, pivot = tn.own && p == 0;
+      const int m0 = tn.me == 0 ? tn.cnt - 1 : tn.me - 1;
       v4d lu[kTreeNB * kTreeNB], kr[kTreeNB];
-      if (act && p == 0) load_lu(lu, slab + n.lu, nb * nb, lane);
-      if (row)
-#pragma unroll
-        for (int j = 0; j < kTreeNB; ++j)
-          if (j < nb) kr[j] = load_blk(slab + n.kjj + (j * nb + p) * kTreeBlk, lane);
+      if (pivot) load_lu(lu, slab + uni(n.lu), nb * nb, lane);
       double* nv = vec + n.vec;
+      // the children's parts of r3 and r1 in row r of the node
+      double c3, c1;
+      // (kChildren of them at a time: index loads, then value loads, in flight together)
+      constexpr int kChildren = 4;
+      auto children = [&](int r) {
+        c3 = c1 = 0.0;
+        for (int a0 = 0; a0 < nchild; a0 += kChildren) {
+          int ci[kChildren], at[kChildren], ld[kChildren];
+#pragma unroll
+          for (int u = 0; u < kChildren; ++u) {
+            const int a = min(a0 + u, nchild - 1);
+            const TreeChild& ch = d.tr.children[n.child0 + a];
+            ci[u] = d.tr.rmap[n.rmap0 + a * kTreeB * (nb + ib) + r];
+            at[u] = ch.vec + 2 * kTreeB * ch.nb;
+            ld[u] = kTreeB * ch.ib;
+          }
+          double v3[kChildren], v1[kChildren];
+#pragma unroll
+          for (int u = 0; u < kChildren; ++u) {
+            v3[u] = vec[at[u] + max(ci[u], 0)];
+            v1[u] = vec[at[u] + ld[u] + max(ci[u], 0)];
+          }
+#pragma unroll
+          for (int u = 0; u < kChildren; ++u)
+            if (a0 + u < nchild && ci[u] >= 0) {
+              c3 += v3[u];
+              c1 += v1[u];
+            }
+        }
+      };
       if (row && lane < kTreeB) {
         const int r = p * kTreeB + lane;
         double a3 = 0.0, a1 = 0.0;
@@ -885,20 +958,12 @@ __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k,
           a3 = d.qbuf[at];
           a1 = d.rhat1[at];
         }
-        for (int a = 0; a < n.nchild; ++a) {
-          const TreeChild& ch = d.tr.children[n.child0 + a];
-          const int ci = d.tr.rmap[n.rmap0 + a * kTreeB * (nb + ib) + r];
-          if (ci >= 0) {
-            const double* cv = vec + ch.vec + 2 * kTreeB * ch.nb + ci;
-            a3 += cv[0];
-            a1 += cv[kTreeB * ch.ib];
-          }
-        }
-        b3[r] = a3;
-        b1[r] = a1;
+        children(r);
+        b3[r] = a3 + c3;
+        b1[r] = a1 + c1;
       }
       __syncthreads();
-      if (act && p == 0) {
+      if (pivot) {
         switch (nb) {
           case 1: pivot_solve<1>(lu, b3, lane); break;
           case 2: pivot_solve<2>(lu, b3, lane); break;
@@ -906,9 +971,17 @@ __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k,
           default: pivot_solve<4>(lu, b3, lane); break;
         }
         if (lane < nb * kTreeB) nv[lane] = b3[lane];
+      } else if (tn.act && m0 < ib) {
+        children((nb + m0) * kTreeB + lm);
       }
+      // block rows of Y_b: by the second group where it has no node of its own
+      const bool yrow = tn.solo ? !tn.own && p < nb : row;
+      if (yrow)
+#pragma unroll
+        for (int j = 0; j < kTreeNB; ++j)
+          if (j < nb) kr[j] = load_blk(slab + uni(n.kjj) + (j * nb + p) * kTreeBlk, lane);
       __syncthreads();
-      if (row) {
+      if (yrow) {
         double acc = 0.0;
 #pragma unroll
         for (int j = 0; j < kTreeNB; ++j)
@@ -921,29 +994,21 @@ __device__ __forceinline__ void tree_up_body(const DP& d, int bx, int gx, int k,
         }
       }
       __syncthreads();
-      if (act)
-        for (int m = p; m < ib; m += kTreeNB) {
+      if (tn.act)
+        for (int m = m0; m < ib; m += tn.cnt) {
+          v4d blk[3 * kTreeNB];
+          load_strip(blk, slab, n, m, nb, lane);
+          if (pivot || m != m0) children((nb + m) * kTreeB + lm);
           double a3 = 0.0, a1 = 0.0;
-          for (int j = 0; j < nb; ++j) {
-            const long long at = (long long)(m * nb + j) * kTreeBlk;
-            const v4d g = load_blk(slab + n.gijt + at, lane), v = load_blk(slab + n.v + at, lane),
-                      y = load_blk(slab + n.y + at, lane);
-            a3 = dot_rows(g, b3 + j * kTreeB, lk, a3);
-            a1 = dot_rows(v, b1 + j * kTreeB, lk, a1);
-            a1 = dot_rows(y, b3 + j * kTreeB, lk, a1);
-          }
-          a3 = -sum_rows(a3);
-          a1 = -sum_rows(a1);
-          const int r = (nb + m) * kTreeB + lm;
-          for (int a = 0; a < n.nchild; ++a) {
-            const TreeChild& ch = d.tr.children[n.child0 + a];
-            const int ci = d.tr.rmap[n.rmap0 + a * kTreeB * (nb + ib) + r];
-            if (ci >= 0) {
-              const double* cv = vec + ch.vec + 2 * kTreeB * ch.nb + ci;
-              a3 += cv[0];
-              a1 += cv[kTreeB * ch.ib];
+#pragma unroll
+          for (int j = 0; j < kTreeNB; ++j)
+            if (j < nb) {
+              a3 = dot_rows(blk[3 * j], b3 + j * kTreeB, lk, a3);
+              a1 = dot_rows(blk[3 * j + 1], b1 + j * kTreeB, lk, a1);
+              a1 = dot_rows(blk[3 * j + 2], b3 + j * kTreeB, lk, a1);
             }
-          }
+          a3 = c3 - sum_rows(a3);
+          a1 = c1 - sum_rows(a1);
           if (lk == 0) {
             double* o = nv + 2 * kTreeB * nb + m * kTreeB + lm;
             o[0] = a3;
@@ -1034,7 +1099,10 @@ __device__ __forceinline__ void tree_rec_u_body(const DP& d, int job, int k, con
 // Sweep down over the levels l1 - 1 .. l0, workgroups and wavefronts as in the
 // sweep up: x_J and the right-hand side of y_J by block rows, y_J by the
 // node's first wavefront.  Every load that does not wait for the node's own
-// x_J is issued before the first barrier.
+// x_J is issued before the first barrier, the interface strips kStripsDown at a
+// time; with a node to itself the second group of wavefronts takes every other
+// strip.
+constexpr int kStripsDown = 4;
 __device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int k, int l0, int l1, double* px,
                                                double* py) {
   __shared__ double sx[kTreeStepNodes][kTreeRows], st[kTreeStepNodes][kTreeRows + kTreeB];
@@ -1045,53 +1113,86 @@ __device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int 
   const double* vec = d.tr.vec + (long long)k * d.tr.vstride;
   double* xk = d.tr.x + (long long)k * d.nx;
   double* yk = d.tr.y + (long long)k * d.nx;
-  double *xs = sx[grp], *ts = st[grp], *red = sr[wv];
+  double* red = sr[wv];
   for (int l = l1 - 1; l >= l0; --l) {
-    const int q0 = d.tr.lev_ptr[l], q1 = d.tr.lev_ptr[l + 1];
-    for (int qq = q0 + bx * kTreeStepNodes; qq < q1; qq += gx * kTreeStepNodes) {
-      const bool act = qq + grp < q1;
-      const TreeNode& n = d.tr.nodes[d.tr.lev_nodes[min(qq + grp, q1 - 1)]];
-      const int nb = n.nb, ib = n.ib;
-      const bool row = act && p < nb;
+    const int q0 = uni(d.tr.lev_ptr[l]), q1 = uni(d.tr.lev_ptr[l + 1]);
+    const int step = gx > 1 && gx >= q1 - q0 ? 1 : kTreeStepNodes;
+    for (int qq = q0 + bx * step; qq < q1; qq += gx * step) {
+      const SweepTurn tn = sweep_turn(qq, q1, step, wv);
+      const TreeNode& n = d.tr.nodes[uni(d.tr.lev_nodes[tn.node])];
+      double *xs = sx[tn.solo ? 0 : grp], *ts = st[tn.solo ? 0 : grp];
+      const int nb = uni(n.nb), ib = uni(n.ib);
+      const bool row = tn.own && p < nb, pivot = tn.own && p == 0;
       v4d lu[kTreeNB * kTreeNB], kr[kTreeNB], t = {0.0, 0.0, 0.0, 0.0};
-      double base = 0.0;
+      double base = 0.0, bx0 = 0.0;
+      int at = -1;
       if (row) {
 #pragma unroll
         for (int j = 0; j < kTreeNB; ++j)
-          if (j < nb) kr[j] = load_blk(slab + n.kjj + (p * nb + j) * kTreeBlk, lane);
-        double bx0 = 0.0;
-        int at = 0;
+          if (j < nb) kr[j] = load_blk(slab + uni(n.kjj) + (p * nb + j) * kTreeBlk, lane);
         if (lane < kTreeB) {
           const double* up = d.tr.upart + ((long long)k * d.tr.ncjob + n.cjob0) * 2 * kTreeRows + p * kTreeB + lane;
           bx0 = vec[n.vec + p * kTreeB + lane];
           base = vec[n.vec + nb * kTreeB + p * kTreeB + lane];
-          for (int c = 0; c < n.ncjob; ++c) {
-            bx0 += up[c * 2 * kTreeRows];
-            base += up[(c * 2 + 1) * kTreeRows];
+          const int nc = n.ncjob;
+          for (int c0 = 0; c0 < nc; c0 += 4) {
+            double ux[4], uy[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              ux[u] = up[min(c0 + u, nc - 1) * 2 * kTreeRows];
+              uy[u] = up[(min(c0 + u, nc - 1) * 2 + 1) * kTreeRows];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (c0 + u < nc) {
+                bx0 += ux[u];
+                base += uy[u];
+              }
           }
           at = p * kTreeB + lane < n.s ? d.tr.rows[n.row0 + p * kTreeB + lane] : -1;
         }
+      }
+      if (tn.act && p < nb) {
         v4d acc = {0.0, 0.0, 0.0, 0.0};
-        for (int m = 0; m < ib; ++m) {
-          const int j = m * kTreeB + lm;
-          const long long o = (long long)(m * nb + p) * kTreeBlk;
-          const v4d bv = load_blk(slab + n.v + o, lane), by = load_blk(slab + n.y + o, lane),
-                    bg = load_blk(slab + n.gijt + o, lane);
-          double x = 0.0, y = 0.0;
-          if (j < n.i) {
-            const int r = d.tr.rows[n.row0 + n.s + j];
-            x = xk[r];
-            y = yk[r];
-          }
-          dot_cols(bv, x, acc);
-          dot_cols(by, x, t);
-          dot_cols(bg, y, t);
+        const int ms = tn.solo ? kTreeStepNodes : 1;
+        for (int mb = tn.solo ? grp : 0; mb < ib; mb += kStripsDown * ms) {
+          int r[kStripsDown];
+          double x[kStripsDown], y[kStripsDown];
+#pragma unroll
+          for (int u = 0; u < kStripsDown; ++u)
+            if (mb + u * ms < ib) {
+              r[u] = d.tr.rows[n.row0 + n.s + min((mb + u * ms) * kTreeB + lm, n.i - 1)];
+              const long long o = (long long)((mb + u * ms) * nb + p) * kTreeBlk;
+              lu[3 * u] = load_blk(slab + uni(n.v) + o, lane);
+              lu[3 * u + 1] = load_blk(slab + uni(n.y) + o, lane);
+              lu[3 * u + 2] = load_blk(slab + uni(n.gijt) + o, lane);
+            }
+#pragma unroll
+          for (int u = 0; u < kStripsDown; ++u)
+            if (mb + u * ms < ib) {
+              x[u] = xk[r[u]];
+              y[u] = yk[r[u]];
+            }
+#pragma unroll
+          for (int u = 0; u < kStripsDown; ++u)
+            if (mb + u * ms < ib) {
+              const bool in = (mb + u * ms) * kTreeB + lm < n.i;
+              dot_cols(lu[3 * u], in ? x[u] : 0.0, acc);
+              dot_cols(lu[3 * u + 1], in ? x[u] : 0.0, t);
+              dot_cols(lu[3 * u + 2], in ? y[u] : 0.0, t);
+            }
         }
-        if (p == 0) load_lu(lu, slab + n.lu, nb * nb, lane);
+        if (pivot) load_lu(lu, slab + uni(n.lu), nb * nb, lane);
         put_rows(acc, red, lane);
+        if (!row) put_rows(t, red + kTreeB, lane);
+      }
+      if (tn.solo) __syncthreads();
+      const double* red2 = sr[(wv + kTreeNB) % (kTreeStepNodes * kTreeNB)];  // the second group's, with solo
+      if (row) {
         wave_sync();
         if (lane < kTreeB) {
-          const double x = at >= 0 ? -(bx0 + red[lane]) : 0.0;
+          const double x = at >= 0 ? -(bx0 + red[lane] + (tn.solo ? red2[lane] : 0.0)) : 0.0;
+          if (tn.solo) base += red2[kTreeB + lane];
           xs[p * kTreeB + lane] = x;
           if (at >= 0) {
             xk[at] = x;
@@ -1109,7 +1210,7 @@ __device__ __forceinline__ void tree_down_body(const DP& d, int bx, int gx, int 
         if (lane < kTreeB) ts[p * kTreeB + lane] = base + red[lane];
       }
       __syncthreads();
-      if (act && p == 0) {
+      if (pivot) {
         switch (nb) {
           case 1: pivot_solve_t<1>(lu, ts, ts + kTreeRows, lane); break;
           case 2: pivot_solve_t<2>(lu, ts, ts + kTreeRows, lane); break;
@@ -1228,7 +1329,7 @@ __global__ __launch_bounds__(kTT) void k_tree_resid_m(RKKT_MULTI_ARGS) {
 }
 __global__ __launch_bounds__(kTS) void k_tree_up_m(RKKT_MULTI_ARGS, int l0, int l1) {
   RKKT_MULTI_PROLOGUE
-  tree_up_body(d, mb.bx, mb.gx, mb.by, l0, l1 ? l1 : d.tr.nlev);
+  tree_up_body(d, mb.bx, mb.gx, mb.by, l1 ? l0 : d.tr.nwide, l1 ? l1 : d.tr.nlev);
 }
 __global__ __launch_bounds__(kTT) void k_tree_rhs_u_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
@@ -1240,7 +1341,7 @@ __global__ __launch_bounds__(kTT) void k_tree_rec_u_m(RKKT_MULTI_ARGS) {
 }
 __global__ __launch_bounds__(kTS) void k_tree_down_m(RKKT_MULTI_ARGS, int l0, int l1) {
   RKKT_MULTI_PROLOGUE
-  tree_down_body(d, mb.bx, mb.gx, mb.by, l0, l1 ? l1 : d.tr.nlev, it.px, it.py);
+  tree_down_body(d, mb.bx, mb.gx, mb.by, l1 ? l0 : d.tr.nwide, l1 ? l1 : d.tr.nlev, it.px, it.py);
 }
 __global__ __launch_bounds__(kTT) void k_tree_hp_m(RKKT_MULTI_ARGS) {
   RKKT_MULTI_PROLOGUE
@@ -1280,15 +1381,19 @@ void launch_tree_sum(const DP& d, const double* su, double dw, double* khat, hip
   k_tree_kuu<<<cdiv(d.tr.nkuu, kTT), kTT, 0, s>>>(d, khat);
 }
 
-// workgroups per scenario of a level's part of a sweep
-static int wide_groups(const Tree& t, int l) { return (int)cdiv(t.lev_ptr[l + 1] - t.lev_ptr[l], kTreeStepNodes); }
+// workgroups per scenario of a level's part of a sweep: one per node while all of
+// them run at once (their registers leave one to a CU)
+static int wide_groups(const Tree& t, int l, int n_scen) {
+  const int nodes = t.lev_ptr[l + 1] - t.lev_ptr[l];
+  return (long long)nodes * n_scen <= 256 ? nodes : (int)cdiv(nodes, kTreeStepNodes);
+}
 
 void launch_tree_rhs(const DP& d, const double* r1x, const double* r2, const double* r3, const double* r4,
                      const double* ss, hipStream_t s) {
   const Tree& t = *d.tr.host;
   k_tree_resid<<<dim3(cdiv(d.nz, kTT), d.N), kTT, 0, s>>>(d, r1x, r2, r3, r4, ss);
   const int nw = tree_wide_levels(t);
-  for (int l = 0; l < nw; ++l) k_tree_up<<<dim3(wide_groups(t, l), d.N), kTS, 0, s>>>(d, l, l + 1);
+  for (int l = 0; l < nw; ++l) k_tree_up<<<dim3(wide_groups(t, l, d.N), d.N), kTS, 0, s>>>(d, l, l + 1);
   if (nw < d.tr.nlev) k_tree_up<<<dim3(1, d.N), kTS, 0, s>>>(d, nw, d.tr.nlev);
   k_tree_rhs_u<<<dim3(d.tr.nstrip, d.N), kTT, 0, s>>>(d);
 }
@@ -1299,11 +1404,14 @@ void launch_tree_recover(const DP& d, const double* r2, const double* r4, const 
   if (d.tr.ncjob > 0) k_tree_rec_u<<<dim3(d.tr.ncjob, d.N), kTT, 0, s>>>(d, pu);
   const int nw = tree_wide_levels(t);
   if (nw < d.tr.nlev) k_tree_down<<<dim3(1, d.N), kTS, 0, s>>>(d, nw, d.tr.nlev, px, py);
-  for (int l = nw - 1; l >= 0; --l) k_tree_down<<<dim3(wide_groups(t, l), d.N), kTS, 0, s>>>(d, l, l + 1, px, py);
+  for (int l = nw - 1; l >= 0; --l) k_tree_down<<<dim3(wide_groups(t, l, d.N), d.N), kTS, 0, s>>>(d, l, l + 1, px, py);
   k_tree_hp<<<dim3(cdiv(d.m, kTT), d.N), kTT, 0, s>>>(d, r2, r4, ss, pu, ps, pz);
 }
 
-// jb of a sweep's launch: first level | level after the last << 16 (0: the tree's last)
+// jb of a sweep's launch: first level | level after the last << 16; 0: the levels
+// that one workgroup per scenario takes, whichever they are in each instance (one
+// launch: one per first level, one after the other, took 213 us up and 188 down
+// for 16 grids)
 void launches_tree(const DP& d, std::vector<Launch>& out) {
   const Tree& t = *d.tr.host;
   const int R = kStReduce * 4096;
@@ -1327,12 +1435,12 @@ void launches_tree(const DP& d, std::vector<Launch>& out) {
   out.push_back(Launch{H, kKTreeResid, 0, (int)cdiv(d.nz, kTT), d.N, kTT, 0, 0});
   out.push_back(Launch{B, kKTreeRecU, 0, d.tr.ncjob, d.N, kTT, 0, 0});
   for (int l = 0; l < nw; ++l) {
-    out.push_back(Launch{H + 1 + l, kKTreeUp, 0, wide_groups(t, l), d.N, kTS, l | (l + 1) << 16, 0});
-    out.push_back(Launch{B + 2047 - l, kKTreeDown, 0, wide_groups(t, l), d.N, kTS, l | (l + 1) << 16, 0});
+    out.push_back(Launch{H + 1 + l, kKTreeUp, 0, wide_groups(t, l, d.N), d.N, kTS, l | (l + 1) << 16, 0});
+    out.push_back(Launch{B + 2047 - l, kKTreeDown, 0, wide_groups(t, l, d.N), d.N, kTS, l | (l + 1) << 16, 0});
   }
   if (nw < nlev) {
-    out.push_back(Launch{H + 2048, kKTreeUp, 0, 1, d.N, kTS, nw, 0});
-    out.push_back(Launch{B + 1, kKTreeDown, 0, 1, d.N, kTS, nw, 0});
+    out.push_back(Launch{H + 2048, kKTreeUp, 0, 1, d.N, kTS, 0, 0});
+    out.push_back(Launch{B + 1, kKTreeDown, 0, 1, d.N, kTS, 0, 0});
   }
   out.push_back(Launch{H + 2049, kKTreeRhsU, 0, d.tr.nstrip, d.N, kTT, 0, 0});
   out.push_back(Launch{B + 2048, kKTreeHp, 0, (int)cdiv(d.m, kTT), d.N, kTT, 0, 0});

@@ -108,9 +108,12 @@ std::string build_tree(const Sym& s, Tree& t);
 
 // Levels whose nodes are spread over several workgroups per scenario in the
 // step's sweeps (one launch each): the first levels, while they hold more
-// than kTreeWide nodes.  The rest run in one workgroup per scenario, which
-// takes kTreeStepNodes nodes at a time, kTreeNB wavefronts each.
-constexpr int kTreeWide = 4, kTreeStepNodes = 2;
+// than kTreeWide nodes (a level inside a longer launch costs what a launch
+// does, 9-13 us, and more with several nodes: from 5 nodes on 16 grids took
+// 1393 us, from 2 1358).  The rest run in one workgroup per scenario.  A
+// workgroup takes one node, or kTreeStepNodes at a time with kTreeNB wavefronts
+// each.
+constexpr int kTreeWide = 1, kTreeStepNodes = 2;
 int tree_wide_levels(const Tree& t);
 
 }  // namespace rkkt
