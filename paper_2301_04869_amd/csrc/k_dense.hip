@@ -607,50 +607,57 @@ __device__ __forceinline__ void chol_strip(const double* A, int n, int row0, int
 }
 
 // Factorises the 64 x 64 tile at jb held (lower triangle, padded with identity
-// rows) in sa: L to A's lower triangle, the blocks to cw.  256 threads:
-// wavefront 0 takes the pivots of each 16-column panel (tile_chain, which also
-// gives the block's inverse), the others the blocks below; two barriers per
-// panel.  Returns 0 or the 1-based column (in the tile) of the first bad pivot.
+// rows) in sa: L to A's lower triangle, the blocks to cw.  256 threads, 16
+// columns at a time with look-ahead as in chol_small_body: wavefront 0 owns the
+// next block row, updates its diagonal block first and takes its pivots
+// (tile_chain, which also gives the block's inverse) while the others finish
+// their rows; the last wavefront, which never has a row, writes the diagonal
+// blocks.  Two barriers per panel; raw: two staged blocks, by panel parity.
+// Returns 0 or the 1-based column (in the tile) of the first bad pivot.
 __device__ __forceinline__ int chol_tile64(double* sa, double* raw, int* sflag, double* A, int n, int jb, double* cw) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int lm = lane & 15, lk = lane >> 4;
+  auto pivots = [&](int k) {
+    const int b0 = kPB * k;
+    double x[kPB], y[kPB], dpv = 0.0;
+#pragma unroll
+    for (int q = 0; q < kPB; ++q) {
+      x[q] = lane < kPB ? sa[(b0 + lane) * kCtLd + b0 + q] : 0.0;
+      y[q] = lane == q ? 1.0 : 0.0;
+    }
+    tile_chain<0>(x, y, row_bcast<0>(x[0]), 0.0, dpv, lane);
+    const int bad = chol_tile16_stage(x, y, dpv, b0, raw + (k & 1) * kRawSize, lane);
+    if (bad && lane == 0) *sflag = bad;
+  };
   if (tid == 0) *sflag = 0;
   __syncthreads();
+  if (wv == 0) pivots(0);
+  __syncthreads();
   for (int k = 0; k < kNBB; ++k) {
-    const int b0 = kPB * k;
-    if (wv == 0) {
-      double x[kPB], y[kPB], dpv = 0.0;
-#pragma unroll
-      for (int q = 0; q < kPB; ++q) {
-        x[q] = lane < kPB ? sa[(b0 + lane) * kCtLd + b0 + q] : 0.0;
-        y[q] = lane == q ? 1.0 : 0.0;
-      }
-      tile_chain<0>(x, y, row_bcast<0>(x[0]), 0.0, dpv, lane);
-      const int bad = chol_tile16_stage(x, y, dpv, b0, raw, lane);
-      if (bad && lane == 0) *sflag = bad;
-    }
-    __syncthreads();
     if (*sflag) return *sflag;
-    // block row of this wavefront (wavefront 0 writes the diagonal block)
-    const int i = k + wv;
-    v4d li = {0.0, 0.0, 0.0, 0.0};
-    if (wv == 0) {
+    const int b0 = kPB * k;
+    const double* rk = raw + (k & 1) * kRawSize;
+    if (wv == kNBB - 1) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int t = lane + 64 * u, r = t / kPB, p = t % kPB;
         // cw: [p][r] = (L^-1)[r][p] = d_r^-1/2 (W^-T D)[p][r]
-        const double rs = raw[kRawRs + p];
-        cw[(kNBB + 1) * k * kPB * kPB + r * kPB + p] = r <= p ? rs * raw[kRawE + r * kTileLd + p] : 0.0;
+        const double rs = rk[kRawRs + p];
+        cw[(kNBB + 1) * k * kPB * kPB + r * kPB + p] = r <= p ? rs * rk[kRawE + r * kTileLd + p] : 0.0;
         if (p <= r && jb + b0 + r < n)
           A[(long long)(jb + b0 + r) * n + jb + b0 + p] =
-              p < r ? raw[kRawW + r * kTileLd + p] * rs : raw[kRawD + p] * rs;
+              p < r ? rk[kRawW + r * kTileLd + p] * rs : rk[kRawD + p] * rs;
       }
-    } else if (i < kNBB) {
-      const int i0 = kPB * i;
-      const double rsl = raw[kRawRs + lm];
+    }
+    if (k + 1 == kNBB) break;
+    const int i = k + 1 + wv, i0 = kPB * i;
+    const bool own = i < kNBB;
+    v4d li = {0.0, 0.0, 0.0, 0.0};
+    if (own) {
+      const double rsl = rk[kRawRs + lm];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const double m1 = 4 * j + lk <= lm ? rsl * raw[kRawE + (4 * j + lk) * kTileLd + lm] : 0.0;
+        const double m1 = 4 * j + lk <= lm ? rsl * rk[kRawE + (4 * j + lk) * kTileLd + lm] : 0.0;
         const double b = sa[(i0 + lm) * kCtLd + b0 + 4 * j + lk];
         li = __builtin_amdgcn_mfma_f64_16x16x4f64(m1, b, li, 0, 0, 0);
       }
@@ -663,9 +670,8 @@ __device__ __forceinline__ int chol_tile64(double* sa, double* raw, int* sflag, 
       }
     }
     __syncthreads();
-    if (wv > 0 && i < kNBB) {
-      const int i0 = kPB * i;
-      for (int l = k + 1; l <= i; ++l) {
+    if (own)
+      for (int l = i; l > k; --l) {
         const int l0 = kPB * l;
         v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -674,6 +680,9 @@ __device__ __forceinline__ int chol_tile64(double* sa, double* raw, int* sflag, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) sa[(i0 + lk + 4 * r) * kCtLd + l0 + lm] -= acc[r];
       }
+    if (wv == 0) {
+      wave_sync();
+      pivots(k + 1);
     }
     __syncthreads();
   }
@@ -693,7 +702,7 @@ __device__ __forceinline__ void chol_first_body(int bx_, int gx_, const double* 
     return;
   }
   __shared__ double sa[kNB * kCtLd];
-  __shared__ double raw[kRawSize];
+  __shared__ double raw[2 * kRawSize];
   __shared__ int sflag;
   for (int t = threadIdx.x; t < kNB * kNB; t += kThreads) {
     const int r = t / kNB, c = t % kNB;
@@ -709,7 +718,7 @@ __device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k,
   if (*info != 0) return;
   __shared__ double sx[kNB * kNB];   // L_jk^T, block rows by strips of 16
   __shared__ double sa[kNB * kCtLd];
-  __shared__ double raw[kRawSize];
+  __shared__ double raw[2 * kRawSize];
   __shared__ int sflag;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lm = lane & 15, lk = lane >> 4;
@@ -736,6 +745,15 @@ __device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k,
   while ((ti + 1) * (ti + 2) / 2 <= bx_) ++ti;
   const int tj = bx_ - ti * (ti + 1) / 2;
   const int i0 = (k + 1 + ti) * kNB, j0 = (k + 1 + tj) * kNB, jb = k * kNB;
+  // the tile's own values first, in flight behind everything below (read after
+  // the products, 16 columns at a time, they were four trips to memory in a row:
+  // the launch of one panel 24 us, 19 us so and with chol_tile64's look-ahead)
+  double av[kNBB][4];
+#pragma unroll
+  for (int q = 0; q < kNBB; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      av[q][r] = A[(long long)min(i0 + kPB * wv + lk + 4 * r, n - 1) * n + min(j0 + kPB * q + lm, n - 1)];
   // L_jk^T strips to LDS, L_ik^T strip of this wavefront in registers
   chol_strip(A, n, j0 + kPB * wv, jb, cwk, lane, x);
 #pragma unroll
@@ -763,9 +781,9 @@ __device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k,
       if (next) {
         const bool in = row < n && col < n;
         sa[(row - i0) * kCtLd + col - j0] =
-            in ? A[(long long)row * n + col] - acc[r] : (row == col ? 1.0 : 0.0);
+            in ? av[q][r] - acc[r] : (row == col ? 1.0 : 0.0);
       } else if (row < n && col <= row) {
-        A[(long long)row * n + col] -= acc[r];
+        A[(long long)row * n + col] = av[q][r] - acc[r];
       }
     }
   }
