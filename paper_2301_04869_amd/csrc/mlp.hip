@@ -19,7 +19,7 @@ struct rkkt_mlp {
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   rkkt::MlpLayers lay{};
   uint16_t *wb = nullptr, *wt = nullptr;  // BF16 W_l [fi][fo_p] and W_l^T [fo][fi_p]
-  std::vector<uint16_t*> A;           // A_l [bmax][pad8(sz[l])], BF16 (A_0 = input)
+  std::vector<uint16_t*> A;           // A_l [bmax][pad8(sz[l])], BF16 (A_0, the input, in one-layer networks only)
   std::vector<uint16_t*> AT;          // A_l^T [sz[l] + 1][bpit], BF16, last row ones
   std::vector<float*> Z;              // Z_l [bmax][sz[l + 1]], FP32 pre-activations
   uint16_t *dZb[2] = {nullptr, nullptr}, *dZT[2] = {nullptr, nullptr};  // output gradients, both orientations
