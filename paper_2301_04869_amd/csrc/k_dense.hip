@@ -713,9 +713,14 @@ __device__ __forceinline__ void chol_first_body(int bx_, int gx_, const double* 
 }
 
 // launch k: see above.  bx: tiles of the trailing matrix (row by row, its
-// first tile first), then the tiles of panel k - 1
+// first tile first), then the tiles of panel k - 1.  A bad pivot found by an
+// earlier launch lies in tile k or before it and ends the launch; one that the
+// first workgroup finds during this launch lies behind tile k, and whether the
+// others see it yet must not matter: they finish their tiles, all wavefronts of
+// a workgroup alike.
 __device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k, int* info, double* cw) {
-  if (*info != 0) return;
+  const int bad = *info;
+  if (bad != 0 && bad <= (k + 1) * kNB) return;
   __shared__ double sx[kNB * kNB];   // L_jk^T, block rows by strips of 16
   __shared__ double sa[kNB * kCtLd];
   __shared__ double raw[2 * kRawSize];
@@ -788,8 +793,8 @@ __device__ __forceinline__ void chol_step_body(int bx_, double* A, int n, int k,
     }
   }
   if (next) {
-    const int bad = chol_tile64(sa, raw, &sflag, A, n, i0, cw + (long long)(k + 1) * kCwTile);
-    if (threadIdx.x == 0 && bad) *info = i0 + bad;
+    const int col = chol_tile64(sa, raw, &sflag, A, n, i0, cw + (long long)(k + 1) * kCwTile);
+    if (threadIdx.x == 0 && col) *info = i0 + col;
   }
 }
 
