@@ -19,7 +19,7 @@ struct rkkt_mlp {
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   rkkt::MlpLayers lay{};
   uint16_t *wb = nullptr, *wt = nullptr;  // BF16 W_l [fi][fo_p] and W_l^T [fo][fi_p]
-  std::vector<uint16_t*> A;           // A_l [bmax][pad8(sz[l])], BF16 (A_0, the input, in one-layer networks only)
+  std::vector<uint16_t*> A;           // A_l [bmax][pad8(sz[l])], BF16 (A_0, the input, unless the first product reads it)
   std::vector<uint16_t*> AT;          // A_l^T [sz[l] + 1][bpit], BF16, last row ones
   std::vector<float*> Z;              // Z_l [bmax][sz[l + 1]], FP32 pre-activations
   uint16_t *dZb[2] = {nullptr, nullptr}, *dZT[2] = {nullptr, nullptr};  // output gradients, both orientations
@@ -57,16 +57,31 @@ int check(rkkt_mlp* m, const char* where) {
   return 0;
 }
 
-// Forward pass over B rows of x with layer inputs act[l] (act[0] is used by
-// one-layer networks only: there y may be x, so x is converted before the
-// product that writes y; deeper networks read x in their first product).  With
+// Whether the first product of a forward pass over B rows reads the FP32 input
+// itself: it saves the conversion's launch, but every 32-column tile of the
+// product then reads FP32 rows (at any alignment, so one value per load), which
+// pays only while a wavefront has at most two k steps and every tile a compute
+// unit to itself.  Forward passes, input read / converted, us: [198, 512, 512,
+// 200] x 512 rows 16.3 / 17.0, x 1024 21.2 / 19.9; [256, 512, 512, 200] x 256
+// 16.6 / 15.5; [1000, 512, 512, 200] x 256 26.3 / 18.2; [2000, 2048, 2048,
+// 2000] x 2048 624 / 319.
+constexpr int kDirectInputs = 255, kDirectTiles = 256;
+bool reads_input(const rkkt_mlp* m, int B) {
+  return m->L > 1 && m->sz[0] <= kDirectInputs &&
+         (long long)((B + 31) / 32) * ((m->sz[1] + 31) / 32) <= kDirectTiles;
+}
+
+// Forward pass over B rows of x with layer inputs act[l].  act[0] gets the
+// rounded input, before any product writes y (which may be x in one-layer
+// networks), unless the first product reads x itself.  With
 // targets t the FP32 pre-activations and the transposed activations (operands
 // of the dW products) are kept and the last product leaves the output gradient
 // and the loss's partial sums; otherwise only y is written.
 void forward_layers(rkkt_mlp* m, const float* x, int B, float* y, const float* t, uint16_t* const* act,
                     hipStream_t st) {
   const int L = m->L;
-  if (L == 1)
+  const bool direct = reads_input(m, B);
+  if (!direct)
     rkkt::mlp_input_bf16(x, B, m->sz[0], act[0], mlp_pad8(m->sz[0]), t ? m->AT[0] : nullptr, m->bpit, st);
   for (int l = 0; l < L; ++l) {
     const int fi = m->sz[l], fo = m->sz[l + 1];
@@ -74,7 +89,7 @@ void forward_layers(rkkt_mlp* m, const float* x, int B, float* y, const float* t
     rkkt::MlpGemm g{};
     g.A = act[l];
     g.lda = mlp_pad8(fi);
-    if (l == 0 && !last) {
+    if (l == 0 && direct) {
       g.x = x;
       g.lda = fi;
       g.xt = t ? m->AT[0] : nullptr;
