@@ -277,7 +277,6 @@ static int solve_impl(rkkt_problem* p, const rkkt_ipm_options* uopt, const doubl
     }
     fresh = false;
     if (!ok || code != 0) {
-      values();
       status = ok ? 4 : 3;
       if (ok) p->err = "rkkt_solve: device status raised";
       if (!ok) {  // stays for the caller's rkkt_status
@@ -343,6 +342,7 @@ static int solve_impl(rkkt_problem* p, const rkkt_ipm_options* uopt, const doubl
   CK(after(side, st, p->join_ev[0]));  // what is left on the second stream ends before the call does
   if (fresh) CK(hipMemsetAsync(d.status, 0, 2 * sizeof(int), st));
   if (status >= 2) {
+    values();  // of the iterate: the last evaluation was a trial point's
     rkkt::ipm_resid(d, s, mu, s.hs, st);
     CK(hipStreamSynchronize(st));
     kkt_err(0.0, &emu, &e0);
