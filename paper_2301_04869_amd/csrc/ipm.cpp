@@ -230,6 +230,19 @@ static int solve_impl(rkkt_problem* p, const rkkt_ipm_options* uopt, const doubl
   // The refactorisation of an accepted iterate starts before its KKT error is
   // known; one that convergence makes superfluous leaves no status behind.
   bool fresh = false;  // G_x factors of the iterate exist or are being computed
+  // a return from inside the loop (a runtime call failed) leaves nothing on the
+  // second stream either
+  struct Join {
+    hipStream_t side, st;
+    int* status;
+    const bool& fresh;
+    bool armed = true;
+    ~Join() {
+      if (!armed) return;
+      (void)hipStreamSynchronize(side);
+      if (fresh) (void)hipMemsetAsync(status, 0, 2 * sizeof(int), st);
+    }
+  } join{side, st, d.status, fresh};
   for (k = 0; k <= o.max_iter; ++k) {
     CK(after(st, side, p->fork_ev[0]));
     if (k > 0) { refactor(); fresh = true; }
@@ -340,6 +353,7 @@ static int solve_impl(rkkt_problem* p, const rkkt_ipm_options* uopt, const doubl
                   a_z);
   }
   CK(after(side, st, p->join_ev[0]));  // what is left on the second stream ends before the call does
+  join.armed = false;
   if (fresh) CK(hipMemsetAsync(d.status, 0, 2 * sizeof(int), st));
   if (status >= 2) {
     values();  // of the iterate: the last evaluation was a trial point's

@@ -1,6 +1,7 @@
 """The interior-point driver's order of calls, on the host: ipm.cpp linked with
-stand-ins that compute nothing (ipm_calls.cpp).  Residuals are formed from the
-iterate's values only."""
+stand-ins that compute nothing (ipm_calls.cpp).  Every way out of a solve, those
+after a failing runtime call included, leaves no work behind on the handle's
+second stream, and residuals are formed from the iterate's values only."""
 import os
 import subprocess
 
@@ -33,3 +34,7 @@ def test_every_exit_is_reached(solves):
 
 def test_residuals_come_from_the_iterate(solves):
     assert [s for s in solves if s[2] == 0 and not s[5]] == []
+
+
+def test_nothing_is_left_on_the_second_stream(solves):
+    assert [s for s in solves if not s[4]] == []
