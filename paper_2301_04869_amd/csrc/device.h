@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "layout.h"
+#include "lds_limit.h"
 #include "rkkt.h"
 #include "tree.h"
 

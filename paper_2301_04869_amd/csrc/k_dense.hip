@@ -1221,21 +1221,10 @@ __global__ __launch_bounds__(kIThreads) void k_reduced_solve_blk(DP d, const dou
 
 }  // namespace
 
-// raise the dynamic LDS limit of a kernel to what this problem needs (never lowered)
-static hipError_t allow_lds(const void* fn, int* cur, int need) {
-  if (need <= *cur) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, need);
-  if (e == hipSuccess) *cur = need;
-  return e;
-}
-
 hipError_t configure_dense_kernels(const DP& d) {
-  static int c1 = 0, c5 = 0;
-  hipError_t e = hipSuccess;
-  if (d.nu <= kSmallN) e = allow_lds((const void*)k_chol_small, &c1, chol_small_lds_bytes(d.nu));
-  if (e == hipSuccess && d.nu <= kSmallN)
-    e = allow_lds((const void*)k_reduced_solve_blk, &c5, (int)rsolve_blk_lds_bytes(d.nu));
-  return e;
+  if (d.nu > kSmallN) return hipSuccess;
+  hipError_t e = raise_lds((const void*)k_chol_small, chol_small_lds_bytes(d.nu));
+  return e == hipSuccess ? raise_lds((const void*)k_reduced_solve_blk, rsolve_blk_lds_bytes(d.nu)) : e;
 }
 
 void launch_scenario_sum(const DP& d, const double* su, double dw, double* khat, hipStream_t s) {
@@ -1396,31 +1385,30 @@ hipError_t multi_dense(const Launch& l, unsigned nblk, long long lds, const DP* 
   *handled = true;
   const size_t L = (size_t)lds;
   const unsigned T = (unsigned)l.threads;
-  static int cur[8] = {};
-  auto go = [&](const void* fn, int slot, auto launch) -> hipError_t {
-    if (prepare) return slot >= 0 ? allow_lds(fn, &cur[slot], (int)lds) : hipSuccess;
+  auto go = [&](const void* fn, auto launch) -> hipError_t {
+    if (prepare) return fn ? raise_lds(fn, lds) : hipSuccess;
     launch();
     return hipSuccess;
   };
   switch (l.kernel) {
-    case kKSymSum: return go(nullptr, -1, [&] { k_sym_sum_m<<<nblk, T, 0, s>>>(dps, its, blk); });
+    case kKSymSum: return go(nullptr, [&] { k_sym_sum_m<<<nblk, T, 0, s>>>(dps, its, blk); });
     case kKStacked:
       switch (l.variant) {
-        case 0: return go(nullptr, -1, [&] { k_stacked_product_m<1><<<nblk, T, 0, s>>>(dps, its, blk); });
-        case 1: return go(nullptr, -1, [&] { k_stacked_product_m<2><<<nblk, T, 0, s>>>(dps, its, blk); });
-        case 2: return go(nullptr, -1, [&] { k_stacked_product_m<4><<<nblk, T, 0, s>>>(dps, its, blk); });
-        case 3: return go(nullptr, -1, [&] { k_stacked_product_m<7><<<nblk, T, 0, s>>>(dps, its, blk); });
-        default: return go(nullptr, -1, [&] { k_stacked_product_m<kSBMax><<<nblk, T, 0, s>>>(dps, its, blk); });
+        case 0: return go(nullptr, [&] { k_stacked_product_m<1><<<nblk, T, 0, s>>>(dps, its, blk); });
+        case 1: return go(nullptr, [&] { k_stacked_product_m<2><<<nblk, T, 0, s>>>(dps, its, blk); });
+        case 2: return go(nullptr, [&] { k_stacked_product_m<4><<<nblk, T, 0, s>>>(dps, its, blk); });
+        case 3: return go(nullptr, [&] { k_stacked_product_m<7><<<nblk, T, 0, s>>>(dps, its, blk); });
+        default: return go(nullptr, [&] { k_stacked_product_m<kSBMax><<<nblk, T, 0, s>>>(dps, its, blk); });
       }
     case kKCholSmall:
-      return go((const void*)k_chol_small_m, 0, [&] { k_chol_small_m<<<nblk, T, L, s>>>(dps, its, blk); });
-    case kKCholFirst: return go(nullptr, -1, [&] { k_chol_first_m<<<nblk, T, 0, s>>>(dps, its, blk); });
-    case kKCholStep: return go(nullptr, -1, [&] { k_chol_step_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
+      return go((const void*)k_chol_small_m, [&] { k_chol_small_m<<<nblk, T, L, s>>>(dps, its, blk); });
+    case kKCholFirst: return go(nullptr, [&] { k_chol_first_m<<<nblk, T, 0, s>>>(dps, its, blk); });
+    case kKCholStep: return go(nullptr, [&] { k_chol_step_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
     case kKRSolveBlk:
-      return go((const void*)k_reduced_solve_blk_m, 1, [&] { k_reduced_solve_blk_m<<<nblk, T, L, s>>>(dps, its, blk); });
-    case kKRSolvePrep: return go(nullptr, -1, [&] { k_rsolve_prep_m<<<nblk, T, 0, s>>>(dps, its, blk); });
-    case kKRSolvePanel: return go(nullptr, -1, [&] { k_rsolve_panel_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
-    case kKRSolveUpdate: return go(nullptr, -1, [&] { k_rsolve_update_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
+      return go((const void*)k_reduced_solve_blk_m, [&] { k_reduced_solve_blk_m<<<nblk, T, L, s>>>(dps, its, blk); });
+    case kKRSolvePrep: return go(nullptr, [&] { k_rsolve_prep_m<<<nblk, T, 0, s>>>(dps, its, blk); });
+    case kKRSolvePanel: return go(nullptr, [&] { k_rsolve_panel_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
+    case kKRSolveUpdate: return go(nullptr, [&] { k_rsolve_update_m<<<nblk, T, 0, s>>>(dps, its, blk, l.jb); });
     default:
       *handled = false;
       return hipSuccess;

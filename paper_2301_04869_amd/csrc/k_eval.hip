@@ -536,12 +536,7 @@ static long long line_lds_bytes(const DP& d) { return 8LL * d.nl * kLVsize; }
 static bool line_fused(const DP& d) { return line_lds_bytes(d) <= 96 * 1024; }
 
 hipError_t configure_eval_kernels(const DP& d) {
-  static int cur = 0;
-  if (!line_fused(d) || line_lds_bytes(d) <= cur) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute((const void*)k_line_eval_gather, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)line_lds_bytes(d));
-  if (e == hipSuccess) cur = (int)line_lds_bytes(d);
-  return e;
+  return line_fused(d) ? raise_lds((const void*)k_line_eval_gather, line_lds_bytes(d)) : hipSuccess;
 }
 
 void launch_evaluate_values(const DP& d, const double* x, const double* u, hipStream_t s) {
@@ -616,14 +611,7 @@ void launches_eval(const DP& d, std::vector<Launch>& out) {
 hipError_t multi_eval(const Launch& l, unsigned nblk, long long lds, const DP* dps, const rkkt_iteration* its,
                       const MultiBlk* blk, hipStream_t s, bool prepare, bool* handled) {
   *handled = true;
-  if (prepare) {
-    static int cur = 0;
-    if (l.kernel != kKLineEvalGather || lds <= cur) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void*)k_line_eval_gather_m,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) cur = (int)lds;
-    return e;
-  }
+  if (prepare) return l.kernel == kKLineEvalGather ? raise_lds((const void*)k_line_eval_gather_m, lds) : hipSuccess;
   switch (l.kernel) {
     case kKLineEvalGather: k_line_eval_gather_m<<<nblk, kLvT, (size_t)lds, s>>>(dps, its, blk); break;
     case kKLineEval: k_line_eval_m<<<nblk, kBlock, 0, s>>>(dps, its, blk); break;

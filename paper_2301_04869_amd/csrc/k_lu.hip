@@ -1886,13 +1886,6 @@ __global__ void k_identity_rows(DP d) {
   d.Zst[((long long)k * d.nz + d.nx + j) * d.nu_pad + j] = 1.0;
 }
 
-hipError_t allow_lds(const void* fn, int* cur, long long need) {
-  if (need <= *cur) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-  if (e == hipSuccess) *cur = (int)need;
-  return e;
-}
-
 int ntiles(const DP& d) { return (d.nu + d.col_tile - 1) / d.col_tile; }
 
 // ---- entry points: several instances (block b is block (blk[b].bx,
@@ -1946,29 +1939,27 @@ __global__ __launch_bounds__(kT) void k_step_recover2_m(RKKT_MULTI_ARGS) {
 }  // namespace
 
 hipError_t configure_lu_kernels(const DP& d) {
-  static int c1 = 0, c2 = 0, c3 = 0, c4 = 0, c5 = 0, c6 = 0, c7 = 0, c8 = 0;
   const LdsSizes z = sizes_of(d);
   hipError_t e = hipSuccess;
   if (d.lds_grp) {
-    if (d.upd_lds) e = allow_lds((const void*)k_refactor<true, kGT, true>, &c1, refactor_lds_bytes(z));
-    else e = allow_lds((const void*)k_refactor<true, kGT, false>, &c6, refactor_lds_bytes(z));
+    if (d.upd_lds) e = raise_lds((const void*)k_refactor<true, kGT, true>, refactor_lds_bytes(z));
+    else e = raise_lds((const void*)k_refactor<true, kGT, false>, refactor_lds_bytes(z));
   }
   if (e == hipSuccess && d.lds_stp) {
-    e = allow_lds((const void*)k_step_rhs<true, kGT>, &c3, step_lds_bytes(z));
-    if (e == hipSuccess) e = allow_lds((const void*)k_step_recover<true, kGT>, &c4, step_lds_bytes(z));
+    e = raise_lds((const void*)k_step_rhs<true, kGT>, step_lds_bytes(z));
+    if (e == hipSuccess) e = raise_lds((const void*)k_step_recover<true, kGT>, step_lds_bytes(z));
     if (e == hipSuccess && d.variant == 2) {
-      static int c9 = 0, c10 = 0;
-      e = allow_lds((const void*)k_step_rhs2<kGT>, &c9, step2_lds_bytes(z, kGT));
-      if (e == hipSuccess) e = allow_lds((const void*)k_step_recover2<kGT>, &c10, step2_lds_bytes(z, kGT));
+      e = raise_lds((const void*)k_step_rhs2<kGT>, step2_lds_bytes(z, kGT));
+      if (e == hipSuccess) e = raise_lds((const void*)k_step_recover2<kGT>, step2_lds_bytes(z, kGT));
     }
   }
   if (e == hipSuccess && d.lds_red) {
     if (d.col_tile == kW64) {
-      if (d.variant == 2) e = allow_lds((const void*)k_reduce64<true, 2>, &c7, reduce_lds_bytes(z));
-      else e = allow_lds((const void*)k_reduce64<true, 1>, &c8, reduce_lds_bytes(z));
+      if (d.variant == 2) e = raise_lds((const void*)k_reduce64<true, 2>, reduce_lds_bytes(z));
+      else e = raise_lds((const void*)k_reduce64<true, 1>, reduce_lds_bytes(z));
     } else {
-      if (d.variant == 2) e = allow_lds((const void*)k_reduce<true, 2>, &c5, reduce_lds_bytes(z));
-      else e = allow_lds((const void*)k_reduce<true, 1>, &c2, reduce_lds_bytes(z));
+      if (d.variant == 2) e = raise_lds((const void*)k_reduce<true, 2>, reduce_lds_bytes(z));
+      else e = raise_lds((const void*)k_reduce<true, 1>, reduce_lds_bytes(z));
     }
   }
   return e;
@@ -2080,51 +2071,49 @@ hipError_t multi_lu(const Launch& l, unsigned nblk, long long lds, const DP* dps
   *handled = true;
   const size_t L = (size_t)lds;
   const unsigned T = (unsigned)l.threads;
-  // one dynamic-LDS limit per multi-instance kernel, raised as needed
-  static int cur[32] = {};
-  auto go = [&](const void* fn, int slot, auto launch) -> hipError_t {
-    if (prepare) return allow_lds(fn, &cur[slot], lds);
+  auto go = [&](const void* fn, auto launch) -> hipError_t {
+    if (prepare) return raise_lds(fn, lds);
     launch();
     return hipSuccess;
   };
   switch (l.kernel) {
     case kKRefactor:
       if (l.variant == 0)
-        return go((const void*)k_refactor_m<true, kGT, true>, 0,
+        return go((const void*)k_refactor_m<true, kGT, true>,
                   [&] { k_refactor_m<true, kGT, true><<<nblk, T, L, s>>>(dps, its, blk); });
       if (l.variant == 1)
-        return go((const void*)k_refactor_m<true, kGT, false>, 1,
+        return go((const void*)k_refactor_m<true, kGT, false>,
                   [&] { k_refactor_m<true, kGT, false><<<nblk, T, L, s>>>(dps, its, blk); });
-      return go((const void*)k_refactor_m<false, kRT, false>, 2,
+      return go((const void*)k_refactor_m<false, kRT, false>,
                 [&] { k_refactor_m<false, kRT, false><<<nblk, T, L, s>>>(dps, its, blk); });
     case kKReduce64:
       switch (l.variant) {
-        case 0: return go((const void*)k_reduce64_m<false, 1>, 3, [&] { k_reduce64_m<false, 1><<<nblk, T, L, s>>>(dps, its, blk); });
-        case 1: return go((const void*)k_reduce64_m<false, 2>, 4, [&] { k_reduce64_m<false, 2><<<nblk, T, L, s>>>(dps, its, blk); });
-        case 2: return go((const void*)k_reduce64_m<true, 1>, 5, [&] { k_reduce64_m<true, 1><<<nblk, T, L, s>>>(dps, its, blk); });
-        default: return go((const void*)k_reduce64_m<true, 2>, 6, [&] { k_reduce64_m<true, 2><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 0: return go((const void*)k_reduce64_m<false, 1>, [&] { k_reduce64_m<false, 1><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 1: return go((const void*)k_reduce64_m<false, 2>, [&] { k_reduce64_m<false, 2><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 2: return go((const void*)k_reduce64_m<true, 1>, [&] { k_reduce64_m<true, 1><<<nblk, T, L, s>>>(dps, its, blk); });
+        default: return go((const void*)k_reduce64_m<true, 2>, [&] { k_reduce64_m<true, 2><<<nblk, T, L, s>>>(dps, its, blk); });
       }
     case kKReduce:
       switch (l.variant) {
-        case 0: return go((const void*)k_reduce_m<false, 1>, 7, [&] { k_reduce_m<false, 1><<<nblk, T, L, s>>>(dps, its, blk); });
-        case 1: return go((const void*)k_reduce_m<false, 2>, 8, [&] { k_reduce_m<false, 2><<<nblk, T, L, s>>>(dps, its, blk); });
-        case 2: return go((const void*)k_reduce_m<true, 1>, 9, [&] { k_reduce_m<true, 1><<<nblk, T, L, s>>>(dps, its, blk); });
-        default: return go((const void*)k_reduce_m<true, 2>, 10, [&] { k_reduce_m<true, 2><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 0: return go((const void*)k_reduce_m<false, 1>, [&] { k_reduce_m<false, 1><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 1: return go((const void*)k_reduce_m<false, 2>, [&] { k_reduce_m<false, 2><<<nblk, T, L, s>>>(dps, its, blk); });
+        case 2: return go((const void*)k_reduce_m<true, 1>, [&] { k_reduce_m<true, 1><<<nblk, T, L, s>>>(dps, its, blk); });
+        default: return go((const void*)k_reduce_m<true, 2>, [&] { k_reduce_m<true, 2><<<nblk, T, L, s>>>(dps, its, blk); });
       }
     case kKStepRhs2:
-      return go((const void*)k_step_rhs2_m<kGT>, 11, [&] { k_step_rhs2_m<kGT><<<nblk, T, L, s>>>(dps, its, blk); });
+      return go((const void*)k_step_rhs2_m<kGT>, [&] { k_step_rhs2_m<kGT><<<nblk, T, L, s>>>(dps, its, blk); });
     case kKStepRec2:
-      return go((const void*)k_step_recover2_m<kGT>, 12,
+      return go((const void*)k_step_recover2_m<kGT>,
                 [&] { k_step_recover2_m<kGT><<<nblk, T, L, s>>>(dps, its, blk); });
     case kKStepRhs:
       if (l.variant == 1)
-        return go((const void*)k_step_rhs_m<true, kGT>, 13, [&] { k_step_rhs_m<true, kGT><<<nblk, T, L, s>>>(dps, its, blk); });
-      return go((const void*)k_step_rhs_m<false, kRT>, 14, [&] { k_step_rhs_m<false, kRT><<<nblk, T, L, s>>>(dps, its, blk); });
+        return go((const void*)k_step_rhs_m<true, kGT>, [&] { k_step_rhs_m<true, kGT><<<nblk, T, L, s>>>(dps, its, blk); });
+      return go((const void*)k_step_rhs_m<false, kRT>, [&] { k_step_rhs_m<false, kRT><<<nblk, T, L, s>>>(dps, its, blk); });
     case kKStepRec:
       if (l.variant == 1)
-        return go((const void*)k_step_recover_m<true, kGT>, 15,
+        return go((const void*)k_step_recover_m<true, kGT>,
                   [&] { k_step_recover_m<true, kGT><<<nblk, T, L, s>>>(dps, its, blk); });
-      return go((const void*)k_step_recover_m<false, kRT>, 16,
+      return go((const void*)k_step_recover_m<false, kRT>,
                 [&] { k_step_recover_m<false, kRT><<<nblk, T, L, s>>>(dps, its, blk); });
     default:
       *handled = false;

@@ -1453,18 +1453,14 @@ bool tree_fits(const Tree& t) {
   return true;
 }
 
+// The pivot kernel's dynamic LDS is what tree_fits admits, beside its static
+// arrays (the children's records, row maxima and pivots).
 hipError_t configure_tree_kernels() {
-  // the pivot kernel's LDS never passes 64 KiB + 1 KiB of statics by more
-  // than the row maps it accepts
-  static bool done = false;
-  if (done) return hipSuccess;
-  const int need = kFrontLdsMax;
   hipError_t e = hipSuccess;
   for (const void* fn : {(const void*)k_tree_front<true, true>, (const void*)k_tree_front<false, true>,
                          (const void*)k_tree_front<true, false>, (const void*)k_tree_front<false, false>,
                          (const void*)k_tree_front_m<true>, (const void*)k_tree_front_m<false>})
-    if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, need);
-  done = e == hipSuccess;
+    if (e == hipSuccess) e = raise_lds(fn, kFrontLdsMax);
   return e;
 }
 
