@@ -11,8 +11,8 @@ namespace rkkt {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kNB = 64;          // panel width of the blocked factorisation
+constexpr int kThreads = kCholThreads;
+constexpr int kNB = kCholTile;   // panel width of the blocked factorisation
 constexpr int kSmallN = 128;     // whole matrix (padded to a multiple of 16) in LDS up to this order
 
 // K_hat = sum_c src_c + diag(sigma_u) + delta_w I over `cnt` n_u x n_u
@@ -804,14 +804,6 @@ __global__ __launch_bounds__(kThreads) void k_chol_first(const double* src, doub
 __global__ __launch_bounds__(kThreads) void k_chol_step(double* A, int n, int k, int* info, double* cw) {
   chol_step_body(blockIdx.x, A, n, k, info, cw);
 }
-
-int chol_tiles(int n) { return (n + kNB - 1) / kNB; }
-// workgroups of launch k, and of the first launch
-int chol_step_blocks(int n, int k) {
-  const int nt = chol_tiles(n), T = nt - 1 - k;
-  return T * (T + 1) / 2 + (k > 0 ? nt - k : 0);
-}
-int chol_first_blocks(int n) { return 1 + std::min(512, (n * n + 4 * kThreads - 1) / (4 * kThreads)); }
 
 // p_u = K_hat^-1 rhs, rhs = -r1u + sum_i rpart_i, from the Cholesky factor of
 // more than kSmallN columns (lower triangle of `L`, row-major), by tiles of 64

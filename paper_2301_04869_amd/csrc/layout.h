@@ -87,4 +87,18 @@ __host__ __device__ inline long long step2_lds_bytes(const LdsSizes& z, int thre
                 z.nph_u + z.nph_d + 2);
 }
 
+// Blocked Cholesky of an n x n matrix: tiles per side, workgroups of launch k
+// (the trailing tiles and the tiles of panel k - 1) and of the first launch (the
+// first tile, and copies of four elements per thread up to 512 workgroups).
+constexpr int kCholTile = 64, kCholThreads = 256;
+constexpr int chol_tiles(int n) { return (n + kCholTile - 1) / kCholTile; }
+constexpr int chol_step_blocks(int n, int k) {
+  const int nt = chol_tiles(n), T = nt - 1 - k;
+  return T * (T + 1) / 2 + (k > 0 ? nt - k : 0);
+}
+constexpr int chol_first_blocks(int n) {
+  const long long want = ((long long)n * n + 4 * kCholThreads - 1) / (4 * kCholThreads);
+  return 1 + (int)(want < 512 ? want : 512);
+}
+
 }  // namespace rkkt
