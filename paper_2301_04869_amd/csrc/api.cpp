@@ -461,6 +461,10 @@ static int create_impl(const rkkt_network* net, int n_scen, const double* pd, co
     } else {
       if ((e = hipMemset(d.pdb, 0, N * s.nb * sizeof(double))) != hipSuccess) goto hip_error;
       if ((e = hipMemset(d.qdb, 0, N * s.nb * sizeof(double))) != hipSuccess) goto hip_error;
+      // what was enqueued above (the tree's zero blocks, line and device status
+      // among it) is done before a caller's stream, which need not wait for the
+      // null stream, can read it
+      if ((e = hipDeviceSynchronize()) != hipSuccess) goto hip_error;
     }
   }
   *out = p;
