@@ -200,6 +200,18 @@ static int create_impl(const rkkt_network* net, int n_scen, const double* pd, co
     delete p;
     return rc;
   }
+  if (p->sym.tree) {
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo(&free, &total) == hipSuccess &&
+        !rkkt::tree_affordable(rkkt::tree_bytes(p->sym, p->tree), rkkt::panel_bytes(p->sym), (long long)free)) {
+      p->tree = rkkt::Tree();
+      m = rkkt::build_symbolic(*net, n_scen, opt, p->sym, true, false);
+      if (!m.empty()) {
+        delete p;
+        return fail(nullptr, RKKT_ERR_ARG, "rkkt_create: " + m);
+      }
+    }
+  }
 
   const rkkt::Sym& s = p->sym;
   rkkt::DP& d = p->d;
@@ -481,9 +493,7 @@ hip_error : {
 }
 }
 
-// Below about 1000 buses the tree takes more memory than the panels (200 buses
-// x 600 scenarios 1.03 against 0.64 GB; at 9241 x 16 3.0 against 14.2), so a
-// handle that does not fit with it is made without.
+// A handle that does not fit with the tree after all is made without it.
 int rkkt_create(const rkkt_network* net, int n_scen, const double* pd, const double* qd,
                 const rkkt_options* opt, rkkt_problem** out) {
   bool no_memory = false;

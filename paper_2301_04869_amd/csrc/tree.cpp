@@ -455,6 +455,18 @@ std::string build_tree(const Sym& s, Tree& t) {
   return "";
 }
 
+long long tree_bytes(const Sym& s, const Tree& t) {
+  const long long ld = (long long)t.ngroup * t.T * kTreeB, ncjob = (long long)t.cjobs.size() / 2;
+  return 8 * (s.N * (t.stride + (long long)t.npool * kTreeBlk + t.vstride + 2LL * s.nx + 2 * ncjob * kTreeRows) +
+              t.parts * ld * ld);
+}
+
+long long panel_bytes(const Sym& s) {
+  const long long ntile = (s.nu + s.col_tile - 1) / s.col_tile;
+  return 8LL * s.N * (2LL * s.nx * (s.lds_reduce ? 1 : ntile * s.col_tile) + (long long)s.nu * s.nu +
+                      (long long)s.f_col.size() + s.nx + s.m);
+}
+
 int tree_wide_levels(const Tree& t) {
   int l = 0;
   while (l + 1 < (int)t.lev_ptr.size() && t.lev_ptr[l + 1] - t.lev_ptr[l] > kTreeWide) ++l;

@@ -106,6 +106,20 @@ constexpr int kTreeMapLds = 16384;
 // Builds the tree from the filled pattern; empty string on success.
 std::string build_tree(const Sym& s, Tree& t);
 
+// Device bytes of the arrays that a handle has on the tree, or with panels in
+// device memory instead.
+long long tree_bytes(const Sym& s, const Tree& t);
+long long panel_bytes(const Sym& s);
+
+// Whether the tree is worth its memory with `free` bytes left on the device.
+// Below about 1000 buses it takes more than the panels (200 buses x 600
+// scenarios 0.87 against 0.46 GiB; at 9241 x 16 2.4 against 13), and what it
+// takes in addition is missing when the handle's solve or the caller allocate
+// next, so it may be a sixteenth of what is free.
+constexpr bool tree_affordable(long long tree, long long panel, long long free) {
+  return tree - panel <= free / 16;
+}
+
 // Levels whose nodes are spread over several workgroups per scenario in the
 // step's sweeps (one launch each): the first levels, while they hold more
 // than kTreeWide nodes (a level inside a longer launch costs what a launch
