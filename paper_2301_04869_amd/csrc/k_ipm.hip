@@ -356,6 +356,21 @@ __global__ __launch_bounds__(kBlock) void k_step_scalars(DP d, IpmDev s, double 
     for (int q = 0; q < 3; ++q) s.part[3LL * blockIdx.x + q] = v[q];
 }
 
+// Many parts of k_step_scalars down to one, in place, by one workgroup in the
+// order in which a workgroup of k_trial adds them.  Every workgroup of k_trial
+// reads all parts, work that grows with the square of their number: beyond 2048
+// (of 256 elements each) this launch comes first.  118 buses x 4000 scenarios 5296
+// to 5230 us per iteration; x 256 (636 parts) it would cost 3 us more than it saves.
+constexpr int kTrialParts = 2048;
+__global__ __launch_bounds__(kBlock) void k_step_fin(IpmDev s, int nparts) {
+  const double init[3] = {1.0, 1.0, 0.0};
+  double v[3];
+  parts_reduce<kBlock / 64, kMin, kMin, kSum>(s.part, nparts, init, v);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.part[q] = v[q];
+}
+
 // trial point x + alpha p.  With nparts > 0, alpha is the largest primal step
 // of k_step_scalars' parts, which every workgroup reduces for itself; the
 // first also reports them to the host: out [0] alpha_max primal, [1] alpha_z,
@@ -594,7 +609,9 @@ void ipm_merit(const DP& d, const IpmDev& s, bool trial, double* out, hipStream_
 void ipm_step_trial(const DP& d, const IpmDev& s, double mu, double tau, double* out, hipStream_t st) {
   const unsigned nb = grid_for((long long)d.N * (d.nx + d.m) + d.nu);
   k_step_scalars<<<nb, kBlock, 0, st>>>(d, s, mu, tau);
-  k_trial<<<nb, kBlock, 0, st>>>(d, s, 0.0, (int)nb, out);
+  const bool many = nb > (unsigned)kTrialParts;
+  if (many) k_step_fin<<<1, kBlock, 0, st>>>(s, (int)nb);
+  k_trial<<<nb, kBlock, 0, st>>>(d, s, 0.0, many ? 1 : (int)nb, out);
 }
 
 void ipm_trial(const DP& d, const IpmDev& s, double alpha, hipStream_t st) {
