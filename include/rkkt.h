@@ -91,6 +91,9 @@ typedef struct {
                      exact arithmetic):
                      1 adjoint: khat_i V = L_u - G_u^T G_x^-T L_x, two more
                        sparse triangular solves per column (the paper's form);
+                       where the panels do not fit on chip, the same elimination
+                       on a tree of dense fronts (rkkt_dims.tree), with the same
+                       pivot test, in an elimination order of its own;
                      2 stacked product: khat = sum_i Z_i^T (K_i Z_i) as one
                        dense FP64 matrix-core product over the stacked rows of
                        all scenarios;
@@ -111,7 +114,11 @@ typedef struct {
                           2 pull: every row subtracts all its terms once, in
                             the phase of its own level, which needs its sources
                             only (forces the reduction's panels into device
-                            memory, where it writes each row once per solve);
+                            memory, where it writes each row once per solve;
+                            with variant 1 and tiles of min(64, n_u) columns,
+                            what the elimination tree is chosen by: panels of
+                            that shape are used only where the tree's memory
+                            does not fit);
                           0 push when the reduction runs in LDS, else pull   */
 } rkkt_options;
 
@@ -139,6 +146,11 @@ typedef struct {
                                        from rkkt_analyze                        */
   int n_load;                       /* load buses                               */
   int sweep_form;                   /* reduction solve schedules: 1 push, 2 pull */
+  int tree;                         /* 1: the reduction and the step run on the
+                                       elimination tree, which does not use the
+                                       LU pattern, levels, chain and groups above
+                                       (rkkt_analyze: unless rkkt_create gives it
+                                       up for its memory)                       */
 } rkkt_dims;
 
 /*

@@ -77,7 +77,8 @@ class Dims(ctypes.Structure):
                 ("lds_step", ctypes.c_int), ("chain_rows", ctypes.c_int),
                 ("nnz_kxx", ctypes.c_longlong), ("nnz_kxu", ctypes.c_longlong),
                 ("nnz_kuu", ctypes.c_longlong), ("idx_bytes", ctypes.c_longlong),
-                ("n_load", ctypes.c_int), ("sweep_form", ctypes.c_int)]
+                ("n_load", ctypes.c_int), ("sweep_form", ctypes.c_int),
+                ("tree", ctypes.c_int)]
 
     def as_dict(self):
         return {k: getattr(self, k) for k, _ in self._fields_}

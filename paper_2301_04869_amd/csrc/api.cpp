@@ -90,6 +90,7 @@ void fill_dims(const rkkt::Sym& s, rkkt_dims* o, long long bytes, long long idx_
   o->idx_bytes = idx_bytes;
   o->n_load = s.nload;
   o->sweep_form = s.sweep_form;
+  o->tree = s.tree ? 1 : 0;
 }
 
 // Appends the entries of a level-sliced schedule packed as two words of
