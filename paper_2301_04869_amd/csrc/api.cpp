@@ -1029,8 +1029,9 @@ int rkkt_autotune(const rkkt_network* net, int n_scen, const double* pd, const d
     rc = rkkt_create(net, n_scen, pd, qd, &o, &h);
     if (rc != RKKT_OK) return 1e300;
     const rkkt::Sym& sy = h->sym;
-    const std::vector<int> key{whole ? 1 : 0, sy.variant, sy.col_tile, sy.spw, sy.chain_t, sy.sweep_form,
-                               sy.lds_reduce ? 1 : 0};
+    // the elimination tree has no groups of scenarios and no chain
+    const std::vector<int> key{whole ? 1 : 0, sy.variant, sy.col_tile, sy.tree ? 0 : sy.spw, sy.tree ? 0 : sy.chain_t,
+                               sy.sweep_form, sy.lds_reduce ? 1 : 0, sy.tree ? 1 : 0};
     if (std::find(seen.begin(), seen.end(), key) != seen.end()) {
       rkkt_destroy(h);
       return 1e300;
