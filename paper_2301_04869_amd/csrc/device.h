@@ -165,31 +165,6 @@ __device__ __forceinline__ double row_bcast(double v) {
   return __builtin_amdgcn_mov_dpp(v, 0x150 + Q, 0xf, 0xf, false);
 }
 
-// dst[i * ldd + j] = src[i * lds + j] for i < rows, j < cols, kStageBatch
-// loads in flight per thread (dst in LDS)
-template <typename T>
-__device__ __forceinline__ void copy2d_overlapped(T* dst, int ldd, const T* __restrict__ src, long long lds,
-                                                  int rows, int cols, int start, int stride) {
-  const int total = rows * cols;
-  for (int t0 = start; t0 < total; t0 += kStageBatch * stride) {
-    T v[kStageBatch];
-    int o[kStageBatch];
-#pragma unroll
-    for (int u = 0; u < kStageBatch; ++u) {
-      const int t = t0 + u * stride;
-      o[u] = -1;
-      if (t < total) {
-        const int i = t / cols, j = t - i * cols;
-        v[u] = src[(long long)i * lds + j];
-        o[u] = i * ldd + j;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kStageBatch; ++u)
-      if (o[u] >= 0) dst[o[u]] = v[u];
-  }
-}
-
 // orders the LDS accesses of one wavefront: what its lanes wrote before is
 // seen by its lanes after.  A wavefront's LDS operations execute in issue
 // order, so this is a compiler barrier only (wavefront-scope fences emit no
