@@ -558,8 +558,9 @@ __device__ __forceinline__ void tree_cols_body(const DP& d, int job, int k) {
 // that a node does not hold from a block of zeros.  Bound by the matrix cores
 // once the operands come from L2 (64 x 64 outputs per wavefront: 8 flops per
 // byte; the probe of independent FP64 matrix instructions reaches 49 TFLOP/s):
-// 9241 buses x 16 scenarios 80 GFLOP in 2.28 ms, 35 TFLOP/s; without the loads
-// ahead and with every part on every die 4.68 ms.
+// 9241 buses x 16 scenarios 95 GFLOP (79 without what fills up strips and groups)
+// in 2.25 ms, 42 TFLOP/s; without the loads ahead and with every part on every
+// die 4.68 ms.
 template <int T>
 struct ProdUnit {
   const double* slab;

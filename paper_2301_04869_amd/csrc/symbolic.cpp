@@ -842,8 +842,10 @@ std::string build_symbolic(const rkkt_network& net, int N, const rkkt_options* o
   // the adjoint closure off chip, unless another shape than its own (64-column
   // panels, pull form) is asked for, runs on the elimination tree.  Whole
   // passes, panels in device memory against the tree: 9241 buses x 16
-  // scenarios 114.6 / 28.3 ms, 2869 x 8 11.1 / 5.9, 1354 x 8 3.70 / 2.47; at
-  // 300 x 16 (0.85 / 0.85), where the panels begin to leave the chip, equal
+  // scenarios 114.5 / 7.6 ms, 2869 x 8 11.2 / 1.62, 1354 x 8 3.69 / 0.84, 300 x
+  // 16 0.86 / 0.42; where the panels begin to leave the chip, 200 x 64 0.785 /
+  // 0.412, 200 x 600 3.21 / 1.80.  On chip the panels are as fast or faster: 118
+  // buses x 16 0.210 / 0.210, x 128 0.233 / 0.318, x 1001 1.11 / 1.82
   s.tree = allow_tree && s.variant == 1 && !s.lds_reduce && s.col_tile == std::min(64, nu) && s.sweep_form == 2;
   // stacked panels of the product variant: rows (x rows then u rows) of every
   // scenario, columns padded to a multiple of 64 (the reduction's widest tile)
